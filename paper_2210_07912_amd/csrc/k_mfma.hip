@@ -21,8 +21,8 @@
 //   tilescan      per point: tiles and work units before each bin
 //   item_scan     tiles and units before each point; per-class counters reset
 //   scatter       a 40-byte record (theta, column, n_k) at the sorted slot
-//   tile_item     point of every tile
-//   unit_kernel   the work units: up to 4 tiles of one bin each
+//   tile_kernel   point of every tile, the work units (up to 4 tiles of one
+//                 bin each) and the padding slots
 //   coef_kernel   one thread per slot, FP64: antenna patterns, harmonics
 //                 (polynomial tables), Y_m (rounded to FP32) and x F_k, the
 //                 quadratic term B, and the interpolation fraction mu_k
@@ -57,24 +57,6 @@ namespace rift {
 constexpr int kRR = 59;
 constexpr int kSortThreads = 1024;  // threads per sort block (kSortBlock samples)
 static_assert(kSortBlock % kSortThreads == 0, "a whole number of samples per sort thread");
-
-__device__ __forceinline__ int item_of_flat(const ItemsDev &it, int64_t f) {
-  int lo = 0, hi = it.n_items;  // samp0[lo] <= f < samp0[hi]
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (it.samp0[mid] <= f) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-__device__ __forceinline__ int item_of_bin(const ItemsDev &it, int b) {
-  int lo = 0, hi = it.n_items;
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (it.bin0[mid] <= b) lo = mid; else hi = mid;
-  }
-  return lo;
-}
 
 // ---- 1. integer delays, bin keys, per-block bin counts ----------------------
 // A sort block is kSortBlock consecutive samples of one point.  Counts go to an
@@ -293,45 +275,47 @@ __global__ void __launch_bounds__(kSortThreads) scatter_kernel(MfmaArgs a) {
   }
 }
 
-// point of every tile (tiles of a point are contiguous)
-__global__ void __launch_bounds__(256) tile_item_kernel(MfmaArgs a) {
-  int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// One thread per tile: its point, the work unit it opens (every fourth tile of
+// a bin opens one, for itself and up to three more), and the padding slots
+// (flag 0) that the scatter leaves: the rest of a bin's last tile and, past
+// the last bin, the tiles that round the point up to groups of 4.  The tile's
+// bin is found by bisection of the point's tile prefixes, so a bin that holds
+// most of a call's samples (a proposal concentrated on a source) costs no more
+// than the same number of tiles in many bins: one thread per bin took 877 us
+// for 1e6 samples with half of them in a few bins, this form 6 us.
+__global__ void __launch_bounds__(64) tile_kernel(MfmaArgs a) {
+  const uint32_t t = blockIdx.x * 64u + threadIdx.x;
   if (t >= a.ctl[0]) return;
   int lo = 0, hi = a.items.n_items;  // item_tiles[lo] <= t < item_tiles[hi]
   while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
+    const int mid = (lo + hi) >> 1;
     if (a.item_tiles[mid] <= t) lo = mid; else hi = mid;
   }
-  a.tile_item[t] = lo;
-}
-
-// work units of every bin: consecutive runs of up to 4 of its tiles.  Also
-// the padding slots (flag 0): the rest of the bin's last tile and, for the
-// last bin of a point, the tiles that round the point up to groups of 4; the
-// scatter fills every other slot of the point's tiles.
-__global__ void __launch_bounds__(64) unit_kernel(MfmaArgs a) {
-  const int g = blockIdx.x * 64 + threadIdx.x;
-  if (g >= a.n_bins) return;
-  const int it = item_of_bin(a.items, g);
-  const uint32_t cnt = a.count[g];
-  const uint32_t tb = (cnt + kTS - 1) / kTS;
-  const uint32_t t0 = a.item_tiles[it] + a.bin_tile[g], u0 = a.item_units[it] + a.bin_unit[g];
-  for (uint32_t c = 0; 4 * c < tb; c++) {
-    WorkUnit w;
-    w.tile = t0 + 4 * c;
-    w.ntiles = min(4u, tb - 4 * c);
-    w.key = (uint32_t)(g - a.items.bin0[it]);
-    a.unit[u0 + c] = w;
+  const int it = lo;
+  a.tile_item[t] = it;
+  const uint32_t x = t - a.item_tiles[it];  // tile within the point
+  const int b0 = a.items.bin0[it];
+  lo = b0;  // last bin with bin_tile <= x (an empty bin shares its prefix with the next one)
+  hi = a.items.bin0[it + 1];
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (a.bin_tile[mid] <= x) lo = mid; else hi = mid;
   }
+  const uint32_t cnt = a.count[lo], c = x - a.bin_tile[lo], tb = (cnt + kTS - 1) / kTS;
+  if (c < tb && (c & 3u) == 0u) {
+    WorkUnit w;
+    w.tile = t;
+    w.ntiles = min(4u, tb - c);
+    w.key = (uint32_t)(lo - b0);
+    a.unit[a.item_units[it] + a.bin_unit[lo] + (c >> 2)] = w;
+  }
+  const uint32_t used = c < tb ? min((uint32_t)kTS, cnt - kTS * c) : 0u;
   SampleRec z;
   for (int d = 0; d < 7; d++) z.th[d] = 0.f;
   z.col = 0;
   z.n[0] = z.n[1] = z.n[2] = 0;
   z.flag = 0;
-  const int64_t s0 = (int64_t)kTS * t0;
-  int64_t s1 = s0 + (int64_t)kTS * tb;
-  if (g == a.items.bin0[it + 1] - 1) s1 = (int64_t)kTS * a.item_tiles[it + 1];
-  for (int64_t q = s0 + cnt; q < s1; q++) a.rec[q] = z;
+  for (uint32_t q = used; q < (uint32_t)kTS; q++) a.rec[(int64_t)kTS * t + q] = z;
 }
 
 // ---- 4. per-sample coefficients (FP64), tile-major ---------------------------
@@ -1001,8 +985,7 @@ hipError_t mfma_prepare(const MfmaArgs &a, const int *mclass_M, const int *mclas
   hipLaunchKernelGGL(tilescan_kernel, dim3(a.items.n_items), dim3(256), 0, st, a);
   hipLaunchKernelGGL(item_scan_kernel, dim3(1), dim3(64), 0, st, a);
   hipLaunchKernelGGL(scatter_kernel, dim3(a.n_sort_blocks), dim3(kSortThreads), lds, st, a);
-  hipLaunchKernelGGL(tile_item_kernel, dim3((unsigned)((a.max_tiles + 255) / 256)), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(unit_kernel, dim3((unsigned)((a.n_bins + 63) / 64)), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(tile_kernel, dim3((unsigned)((a.max_tiles + 63) / 64)), dim3(64), 0, st, a);
   for (int c = 0; c < n_mclasses; c++) {
     const int lo = mclass_item0[c], hi = mclass_item0[c + 1];
     const dim3 grid((unsigned)(((int64_t)kTS * mclass_tiles[c] + 63) / 64));
