@@ -43,7 +43,7 @@ MEASURED_TRAFFIC = {
     # profiles/mfma_kernel_single_1e6.md: 167,358 KiB x 2.0 + 33,832 KiB x 1.0
     "single": {"sha256": "c3e061b9d552391d41c590262f4b80b34a8e358ac83bd7d2a4343f7db9ddf69d", "bytes_per_step": 377393120.0},
 }
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2210_07912_amd", "csrc", "k_mfma.hip")
+KERNEL_SOURCE = os.path.join(ROOT, "paper_2210_07912_amd", "csrc", "k_eval.hip")
 
 
 def flops_per_eval(K, M, n_t):

@@ -50,6 +50,7 @@ constexpr int kMaxDet = RIFT_MAX_DET;
 constexpr int kMaxModes = RIFT_MAX_MODES;
 constexpr int kMaxYTerms = 8;   // Wigner-d sum terms for l <= 8
 constexpr int kMaxHDeg = 8;     // degree of the harmonic polynomial for l <= 8
+constexpr int kBinW = 14;       // rows per delay bin (per detector) of the matrix-core evaluation
 constexpr int kNB = RIFT_NBINS;
 constexpr double kC = 299792458.0;
 constexpr double kPi = 3.14159265358979323846;
@@ -85,6 +86,8 @@ struct PointDev {
   const double *Vpk;           // same packing of V, or nullptr
   const void *Q;               // plain layout: [K][Lpad][M][2] in the bulk precision
   const float *Qm;             // MFMA layout (FP32 handles): [K][Lpad][2 Mp], zero-padded
+  const void *Qs;              // split layout (FP32 handles): [K][3 ceil(Mp / 4)][Lpad][8] BF16, chunk 3 j + i
+                               // the part i of elements 8 j .. 8 j + 7 (zero past 2 M and past L)
   int Mp;                      // modes padded to even
 };
 

@@ -54,6 +54,8 @@ constexpr int kFeedConfigs = 7;  // launch configurations the autotuner measures
 constexpr int kSortBlock = 4096;  // samples per sort block
 constexpr int kLdsBins = 8192;    // delay bins counted in LDS (more: in global memory)
 
+constexpr uint32_t kNoBin = 0xffffffffu;
+
 // one sample at its sorted slot
 struct SampleRec {
   float th[7];
@@ -72,11 +74,14 @@ struct CoefTile {
   int flag[16];              // 0 padding, 1 valid, 2 invalid sample
 };
 
-// Up to four tiles of one delay bin, evaluated by one workgroup that stages
-// the rows of Q they share in LDS once for all of them.
+// matrix-core layouts Qm and Qs of a point (see PointDev) from its rows Q
+hipError_t mfma_layouts(const float *Q, float *Qm, void *Qs, int K, int Lpad, int M2, int E, hipStream_t st);
+
+// Up to MfmaArgs::unit_tiles tiles of one delay bin, evaluated by one workgroup
+// that stages the rows of Q they share in LDS once for all of them.
 struct WorkUnit {
   uint32_t tile;    // first tile
-  uint32_t ntiles;  // 1..4
+  uint32_t ntiles;  // 1..unit_tiles
   uint32_t key;     // the bin, within its point
 };
 
@@ -98,6 +103,7 @@ struct MfmaArgs {
   uint32_t *item_tiles;   // [n_items + 1] tile prefix over items (filled on device)
   SampleRec *rec;         // [16 max_tiles] sorted samples (flag 0: padding)
   int *tile_item;         // [max_tiles]
+  uint32_t *tile_key;     // [max_tiles] the tile's bin within its point (kNoBin: padding past the last bin)
   float *cop;             // per point, per tile [K][2 Mp][16] floats; the coefficient pass fills the first
                           // [2 Mp][16]: Y_m (element 2m + re/im) of the tile's samples
   int64_t *item_cop;      // [n_items] offset of each point's operands in cop
@@ -123,6 +129,7 @@ struct MfmaArgs {
   int max_item_bins;      // largest bin count of one point
   int n_sort_blocks;
   int max_tiles;
+  int unit_tiles;         // tiles of a work unit: 8 (evaluation), 4 (adjoint)
   int grid;               // persistent workgroups
 };
 

@@ -1,0 +1,728 @@
+// FP32 evaluation of ln L_t on the matrix cores (gfx950): the persistent
+// kernel over the sorted tiles that k_mfma.hip prepares (delay-bin sort,
+// coefficients, work units), its launch configurations and their measurement.
+#include "common.h"
+#include "dmarg.h"
+#include "internal.h"
+#include "mfma_tile.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace rift {
+
+// The contraction z_k[r](s) = sum_e Q_k[r][e] a_k[e](s) in FP32 accuracy on
+// the BF16 matrix cores: both factors are split into three BF16 parts (v = v0
+// + v1 + v2, each the rounding of what the ones before leave; 24 bits, so the
+// FP32 value exactly), and the six products q_i a_j with i + j <= 2 are
+// accumulated in FP32, the smallest first.  The three products left out are
+// below 2^-24 of |q a| each, and 18 accumulations of which all but the last
+// few are of terms 2^-8 smaller round less than the FP32 instruction's chain:
+// against FP64 the z of 44 products are 5.5e-8 off (rms, relative) where
+// v_mfma_f32_16x16x4f32 is 1.25e-7 off, and the six products take 18
+// instructions of 32 cycles for 32 rows x 32 samples of 48 elements where
+// FP32 takes 44 of 32 cycles for 44 (measured 2400 against 141 TFLOP/s).
+//
+// A wavefront takes 32 samples (two tiles) of one delay bin, a workgroup four
+// such pairs of tiles.  Base row of detector k: the lower edge of the bin, so
+// every sample's stencil starts 0..bin_w-1 rows above it.  Per block of 32 rows and detector: the products, then the window
+// samples of the block before it, through a 48-row buffer in LDS that the
+// wavefront writes (the previous block's rows, kept in registers, and the
+// first half of this block's) and reads at each sample's own row offset.
+// Rows are 32 floats, one per sample, so every access is free of bank
+// conflicts whatever the offsets, and a lane reads 19 rows for 16 consecutive
+// window samples (a 16 x 16 tile reads 7 for 4).
+//
+// Elements are taken in groups of 8 (G of them), a lane half per group; a
+// remaining odd group puts three of its six products in each half.  Two ways
+// to feed the row operands, chosen per (T, K) class by measurement:
+//  * staged (DIRECT = false): the rows of the next block of every detector are
+//    copied from global memory straight into one of two LDS stages, once per
+//    workgroup (one barrier per block); each wavefront reads them from there
+//    (wavefronts without tiles only help stage);
+//  * direct (DIRECT = true): each wavefront loads its own operands from
+//    global memory one detector ahead, with no stage and no barrier between
+//    blocks; a workgroup takes four consecutive pairs of tiles whatever their
+//    bins, so that sparse bins do not leave wavefronts idle (with many samples
+//    the pairs mostly are of one bin, and three of the four reads hit in L1).
+// Bound: the matrix cores (52 % busy at K = 3, M = 21, where the direct feed
+// keeps the L1's 64 bytes per cycle 78 % busy) and, at few modes, the vector
+// work of the window.  Kernel time of 5e5 samples, before (FP32 instructions,
+// 16 x 16 tiles) and now: K = 3: M = 21, n_t = 820 1294 -> 756 us; n_t = 500:
+// M = 9 442 -> 316, M = 5 441 -> 255, M = 2 269 -> 212; K = 2: 818 -> 500,
+// 294 -> 206, 257 -> 169, 200 -> 145.
+// MODE 0: ln L_t.  Distance marginalization (coefficients at D = D_ref, so
+// the window values are the data terms A_j, base 2): MODE 1 writes each
+// slot's largest A_j; MODE 2 reads it back, places the slot's nodes x_i over
+// D (dmarg.h) and sums exp2(x_i (A_j - A_max)) per node over the window,
+// skipping window samples where even the smallest node's term is below
+// 2^-(T + 10) log2 e (their n_t terms together are far under the rule's
+// error), then combines the nodes in FP64.  Both passes recompute the same
+// window values bit for bit.
+// WPE: wavefronts per SIMD the register allocation must allow.  est_regs
+// counts the parts of the sample operands, the rows kept per detector (of one
+// detector where they stay in LDS), the row operands, the Catmull-Rom weights,
+// the window rows and values and about 25 more, and MODE 2's nodes; from it
+// follow base_wpe (two wavefronts wherever they fit), the classes for which
+// the forms capped for three or four exist as extra configurations for the
+// autotuner, and two choices of the direct form:
+//  * LDS rows (rows_lds): a block's rows are kept in a window buffer per
+//    detector instead of in registers (48 floats fewer at K = 3) where only
+//    that lets two wavefronts share a SIMD; the window buffers then take 18 KB
+//    per wavefront, so nowhere else;
+//  * ahead (1 or K): row operands are loaded one detector or, where registers
+//    allow, one whole block ahead.
+constexpr int n_rows_op(int G) { return 3 * (G / 2) + 2 * (G & 1); }
+constexpr int est_regs(int G, int K, int mode, bool lds, int ahead) {
+  return 12 * K * ((G + 1) / 2) + 16 * (lds ? 1 : K) + 4 * n_rows_op(G) * ahead + 4 * K + 60 +
+         (mode == 2 ? 2 * kDmGL : 0);
+}
+constexpr bool rows_lds(int G, int K, int mode, bool direct, int wpe) {
+  return direct && K > 1 && wpe == 2 && est_regs(G, K, mode, false, 1) > 256;
+}
+constexpr int base_wpe(int G, int K, int mode, bool direct) {
+  return est_regs(G, K, mode, false, 1) <= (direct ? 256 : 272) || (direct && K > 1 && est_regs(G, K, mode, true, 1) <= 256)
+             ? 2
+             : 1;
+}
+constexpr bool can_wpe(int G, int K, int wpe) { return est_regs(G, K, 0, false, 1) <= (wpe == 3 ? 165 : 120); }
+constexpr int rows_ahead(int G, int K, int mode, bool direct, int wpe) {
+  return direct && est_regs(G, K, mode, rows_lds(G, K, mode, direct, wpe), K) <= 512 / wpe ? K : 1;
+}
+constexpr int kWR = 48;  // rows of a wavefront's window buffer: bin_w + 16 + 15 + 3
+
+template <int G, int K, bool DIRECT, int MODE, int WPE = base_wpe(G, K, MODE, DIRECT)>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) mfma_kernel(MfmaArgs a, int item_lo,
+                                                                                         int item_hi, int cls) {
+  constexpr int NP = G / 2, OD = G & 1;      // pairs of element groups; an odd one
+  constexpr int NF = n_rows_op(G);           // row operands of a block and detector
+  constexpr bool PL = rows_lds(G, K, MODE, DIRECT, WPE);
+  constexpr int AB = rows_ahead(G, K, MODE, DIRECT, WPE);
+  constexpr int C = 3 * G;                   // 16-byte chunks of a row: 3 parts of each group
+  constexpr int ND = (C + 1) / 2;            // 1 KB copies of a detector's staged block: two chunks of 32 rows
+  constexpr int SB = K * ND * 1024;          // bytes of one staged block
+  constexpr int WB = kWR * 32;               // floats of a window buffer
+  __shared__ __align__(16) float wbuf_all[kWaves * WB * (PL ? K : 1)];
+  __shared__ __align__(16) char stage[DIRECT ? 16 : 2 * SB];
+  __shared__ WorkUnit unit_sh;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  float *const wbuf = wbuf_all + wave * (WB * (PL ? K : 1));  // [row][sample]
+  const int s = lane & 31, h = lane >> 5, sc = s & (kTS - 1);
+  const uint32_t u_lo = a.item_units[item_lo], u_hi = a.item_units[item_hi];
+  const uint32_t t_lo = a.item_tiles[item_lo], t_hi = a.item_tiles[item_hi];
+  const uint32_t stage_at =
+      __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)stage);
+
+  for (;;) {
+    __syncthreads();  // every wavefront is done with the previous unit
+    if (threadIdx.x == 0) {
+      const uint32_t n = atomicAdd(&a.ctl[1 + cls], 1u);
+      WorkUnit w;
+      w.tile = 0xffffffffu;
+      w.ntiles = 0;
+      w.key = 0;
+      if constexpr (DIRECT) {
+        if (n < (t_hi - t_lo + 7u) / 8u) {
+          w.tile = t_lo + 8u * n;
+          w.ntiles = min(8u, t_hi - w.tile);
+        }
+      } else if (u_lo + n < u_hi) {
+        w = a.unit[u_lo + n];
+      }
+      unit_sh = w;
+    }
+    __syncthreads();
+    const uint32_t tu = __builtin_amdgcn_readfirstlane(unit_sh.tile);
+    const int ntiles = __builtin_amdgcn_readfirstlane(unit_sh.ntiles);
+    if (tu == 0xffffffffu) break;  // the same for the whole workgroup
+    bool active = 2 * wave < ntiles;  // bins hold whole pairs of tiles
+    // this wavefront's pair of tiles, its point and bin (staged: the unit's)
+    const uint32_t t0 = tu + (active ? 2 * wave : 0);
+    uint32_t key = __builtin_amdgcn_readfirstlane(DIRECT ? a.tile_key[t0] : unit_sh.key);
+    if (DIRECT && key == kNoBin) active = false;  // the tiles that round a point up to groups of 4
+    if (DIRECT && !active) continue;
+    const uint32_t t = t0 + (s >> 4);
+    const int it = __builtin_amdgcn_readfirstlane(a.tile_item[t0]);
+    const PointDev &p = a.pts[a.items.point[it]];
+    const int NT = __builtin_amdgcn_readfirstlane(p.n_t), P = __builtin_amdgcn_readfirstlane(p.pad);
+    const int Lpad = __builtin_amdgcn_readfirstlane(p.Lpad), E = 2 * __builtin_amdgcn_readfirstlane(p.Mp);
+    const char *const qsp = uniform_ptr((const char *)p.Qs);
+    const RIFT_GLOBAL char *const qs = gp(qsp);
+    // detector k of the bin: key digit q_k; lowest integer delay of the bin
+    int lo_k[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      const int q = (int)(key % (uint32_t)p.nq);
+      key /= (uint32_t)p.nq;
+      lo_k[k] = __builtin_amdgcn_readfirstlane(q * p.bin_w - P);
+    }
+    const RIFT_GLOBAL CoefTile *ct = gp(a.ctile + t);
+    const int flag = active ? ct->flag[sc] : 0;
+    const int col = ct->col[sc];
+    const float Bf = active ? ct->B[sc] : 0.f;
+    const RIFT_GLOBAL float *yop = gp(a.cop + a.item_cop[it] + (int64_t)(t - a.item_tiles[it]) * K * E * kTS + sc);
+
+    // staged: this wavefront's share of the copies of a block, two chunks each
+    // (a detector's last one alone where their number is odd: both lane halves
+    // copy it, the second into the unused half)
+    const uint32_t lg = 16u * (uint32_t)s, lgh = lg + 16u * (uint32_t)(h * Lpad);
+    auto stage_block = [&](int b, int slot) {
+#pragma unroll
+      for (int i = 0; i < (K * ND + kWaves - 1) / kWaves; i++) {
+        const int q = wave + kWaves * i;
+        if (q < K * ND) {
+          const int k = q / ND, c = 2 * (q % ND);
+          const int lo = K > 2 && k == 2 ? lo_k[K - 1] : K > 1 && k == 1 ? lo_k[K > 1 ? 1 : 0] : lo_k[0];
+          const char *src = qsp + 16 * ((size_t)(k * C + c) * (size_t)Lpad + (size_t)(P + lo + 32 * b));
+          lds_copy16(uniform_ptr(src), c + 1 < C ? lgh : lg, stage_at + (uint32_t)(slot * SB + q * 1024));
+        }
+      }
+    };
+    const int JB = (NT + 31) >> 5;
+    if constexpr (!DIRECT) stage_block(0, 0);  // in flight while the operands are formed
+
+    // sample operands: the three parts of a_k in every group
+    bf8 Bp[K][NP > 0 ? NP : 1][3], Bo[K][3];
+    {
+      float xr[K], xi[K];
+#pragma unroll
+      for (int k = 0; k < K; k++) {
+        xr[k] = active ? ct->xf[k][0][sc] : 0.f;
+        xi[k] = active ? ct->xf[k][1][sc] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < NP + OD; i++) {
+        const int e0 = 8 * (i < NP ? 2 * i + h : G - 1);
+        float y[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) y[e] = (active && e0 + e < E) ? yop[kTS * (e0 + e)] : 0.f;
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+          float v[8];
+#pragma unroll
+          for (int m = 0; m < 4; m++) {  // a = (xr + i xi) (yr + i yi)
+            v[2 * m] = fmaf(xr[k], y[2 * m], -xi[k] * y[2 * m + 1]);
+            v[2 * m + 1] = fmaf(xr[k], y[2 * m + 1], xi[k] * y[2 * m]);
+          }
+          bf8 b0, b1, b2;
+          split3(v, b0, b1, b2);
+          if (i < NP) {
+            Bp[k][i < NP ? i : 0][0] = b0;
+            Bp[k][i < NP ? i : 0][1] = b1;
+            Bp[k][i < NP ? i : 0][2] = b2;
+          } else {
+            Bo[k][0] = b0;
+            Bo[k][1] = b1;
+            Bo[k][2] = h ? b0 : b2;  // partner of the parts (0, 2) of the row operand
+          }
+        }
+      }
+    }
+    float w[K][4];
+    int zb[K];  // this lane's first row of a window read, in floats
+    bool valid = flag == 1;
+    {
+      int sh[K];
+#pragma unroll
+      for (int k = 0; k < K; k++) {
+        cr_weights<float>(ct->mu[k][sc], w[k]);
+        sh[k] = valid ? ct->n[k][sc] - lo_k[k] : 0;
+        if (sh[k] < 0 || sh[k] > kBinW - 1) {
+          valid = false;
+          sh[k] = 0;
+        }
+        zb[k] = (PL ? k * WB : 0) + 32 * (16 * h + sh[k]) + s;
+      }
+    }
+
+    // row operands of detector k, block b: pairs of groups (part 0, 1, 2 each),
+    // then the odd group's two (parts 0 | 2 and 1 | 0 by lane half)
+    const uint32_t lp = s * 16 + h * (3 * (DIRECT ? 16 * Lpad : 512));
+    const uint32_t lx = s * 16 + h * (2 * (DIRECT ? 16 * Lpad : 512));
+    const uint32_t ly = s * 16 + (1 - h) * (DIRECT ? 16 * Lpad : 512);
+    // (PART 0..2: that part of the pairs; 3, 4: the odd group's two).  Direct:
+    // every part has registers of its own.  Staged: a detector's parts are
+    // used in the order 2, 1, 0, each loaded while the one before it is in use,
+    // so they share two sets by turns.
+    constexpr int NX = DIRECT ? 3 * NP : 2 * NP;  // registers sets of the pairs
+    bf8 A[DIRECT ? AB : 1][NX + 2 * OD];
+    auto at = [](int k, int part, int i) { return DIRECT ? 3 * i + part : NP * ((3 * k + 2 - part) & 1) + i; };
+    auto rows = [&](auto part_c, auto k_c, int b, int slot, bf8 (&A)[NX + 2 * OD]) {
+      constexpr int PART = decltype(part_c)::value, k = decltype(k_c)::value;
+      const uint32_t cs = DIRECT ? 16u * (uint32_t)Lpad : 512u;  // bytes of a chunk
+      const uint32_t lane_at = PART < 3 ? lp : PART == 3 ? lx : ly;
+#pragma unroll
+      for (int i = 0; i < (PART < 3 ? NP : 1); i++) {
+        const uint32_t chunk = PART < 3 ? 6 * i + PART : 3 * G - 3;
+        bf8 &x = A[PART < 3 ? at(k, PART, i) : NX + PART - 3];
+        if constexpr (DIRECT)
+          x = *(const RIFT_GLOBAL bf8 *)(qs + 16 * ((size_t)(k * C) * (size_t)Lpad + (size_t)(P + lo_k[k] + 32 * b)) +
+                                         chunk * cs + lane_at);
+        else
+          x = *(const bf8 *)(stage + slot * SB + k * ND * 1024 + chunk * cs + lane_at);
+      }
+    };
+    // what the products of detector k start from: every part (direct), parts 2
+    // and 1 (staged)
+    auto rows_first = [&](auto k_c, int b, int slot, bf8 (&A)[NX + 2 * OD]) {
+      if constexpr (NP > 0) {
+        rows(std::integral_constant<int, 2>{}, k_c, b, slot, A);
+        rows(std::integral_constant<int, 1>{}, k_c, b, slot, A);
+      }
+      if constexpr (OD) {
+        rows(std::integral_constant<int, 3>{}, k_c, b, slot, A);
+        rows(std::integral_constant<int, 4>{}, k_c, b, slot, A);
+      }
+      if constexpr (DIRECT && NP > 0) rows(std::integral_constant<int, 0>{}, k_c, b, slot, A);
+    };
+
+    // window samples 32 c + 16 h + i (i < 16) of the previous block:
+    // interpolation, then the log-sum-exp with a lazy reference m_run: sums
+    // are kept as exp2(ell + B - m_run), m_run is the first block's maximum
+    // and moves only when a value exceeds it by 64, which keeps every sum far
+    // from overflow while terms lost below it are under 2^-126 of the sum.
+    // The quadratic term B is the same for every window sample, so it stays
+    // out of the sums and is subtracted once at the end: the window values
+    // then carry the rounding of the data term only, not of B.
+    const int rem = NT - 32 * (JB - 1);
+    float m_run = 0.f, s_run = 0.f;
+    // distance marginalization: the slot's A_max (MODE 2 reads it), its
+    // nodes and per-node sums
+    constexpr int NN = MODE == 2 ? kDmGL : 1;
+    float am = MODE == 1 ? -INFINITY : 0.f, skip = INFINITY;
+    double ta = 0.0, hq = 0.0;  // the nodes' interval in t = ln x
+    float xs[NN], Sq[NN];
+#pragma unroll
+    for (int q = 0; q < NN; q++) xs[q] = Sq[q] = 0.f;
+    if constexpr (MODE == 2) {
+      const float av = active ? a.amax[(int64_t)t * kTS + sc] : 0.f;
+      if (valid && isfinite(av)) {
+        am = av;
+        // the interval is searched in FP32; an end at the prior's edge takes
+        // the edge's FP64 value, so a range much narrower than the FP32
+        // spacing of t keeps its exact width (the rule's weights scale with it)
+        const double tlo = log(p.d_ref / a.dm_hi), thi = log(p.d_ref / a.dm_lo);
+        float taf, tbf;
+        dm_interval<float>(av * kLn2f, Bf * kLn2f, (float)tlo, (float)thi, (float)DmRule<float>::T, 24, taf, tbf);
+        ta = taf <= (float)tlo ? tlo : (double)taf;
+        const double tb = tbf >= (float)thi ? thi : (double)tbf;
+        hq = tb - ta;
+#pragma unroll
+        for (int q = 0; q < NN; q++) xs[q] = expf((float)(ta + hq * (0.5 + 0.5 * dm_gl_node(q))));
+        skip = -(float)((DmRule<float>::T + 10.0) * kLog2e) / xs[0];
+      }
+    }
+    f16v acc[PL ? 1 : K];  // the last block's rows (8 (i / 4) + 4 h + i % 4 in register i)
+    float ell[16];
+    // rows of the window buffer <- the block in acc (all of it, or its first 16 rows)
+    auto put = [&](int at, const f16v &z, int row, int n) {
+#pragma unroll
+      for (int i = 0; i < 16; i++)
+        if (i < n) wbuf[at + 32 * (row + 8 * (i >> 2) + 4 * h + (i & 3)) + s] = z[i];
+    };
+    // the rows a lane's 16 window samples need, and detector k's terms of them
+    float z[19];
+    auto fetch = [&](auto k_c) {
+      const float *zr = wbuf + zb[decltype(k_c)::value];
+#pragma unroll
+      for (int i = 0; i < 19; i++) z[i] = zr[32 * i];
+    };
+    auto interp = [&](auto k_c, auto lo_c, auto hi_c) {
+      constexpr int k = decltype(k_c)::value;
+      const float base = MODE == 0 ? -m_run : 0.f;
+#pragma unroll
+      for (int i = decltype(lo_c)::value; i < decltype(hi_c)::value; i++) {
+        ell[i] = fmaf(w[k][0], z[i], k == 0 ? base : ell[i]);
+        ell[i] = fmaf(w[k][1], z[i + 1], ell[i]);
+        ell[i] = fmaf(w[k][2], z[i + 2], ell[i]);
+        ell[i] = fmaf(w[k][3], z[i + 3], ell[i]);
+      }
+    };
+    auto window = [&](bool last, bool first) {
+      if (last) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) ell[i] = 16 * h + i < rem ? ell[i] : -INFINITY;
+      }
+      float c4[4];
+#pragma unroll
+      for (int q = 0; q < 4; q++)
+        c4[q] = fmaxf(fmaxf(ell[4 * q], ell[4 * q + 1]), fmaxf(ell[4 * q + 2], ell[4 * q + 3]));
+      const float cmax = fmaxf(fmaxf(c4[0], c4[1]), fmaxf(c4[2], c4[3]));
+      if constexpr (MODE == 1) {
+        am = fmaxf(am, cmax);
+      } else if constexpr (MODE == 2) {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) {
+          if (c4[q4] - am >= skip) {
+            float d[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) d[i] = ell[4 * q4 + i] - am;
+#pragma unroll
+            for (int q = 0; q < NN; q++) {
+              float e = 0.f;
+#pragma unroll
+              for (int i = 0; i < 4; i++) e += __builtin_amdgcn_exp2f(xs[q] * d[i]);
+              Sq[q] += e;
+            }
+          }
+        }
+      } else {
+        if ((first || cmax > 64.f) && cmax > -3.0e38f) {  // rare after the first block
+          // (the first block starts from an empty sum; its maximum can be far
+          // below zero, where exp2(-cmax) would overflow)
+          s_run = first ? 0.f : s_run * __builtin_amdgcn_exp2f(-cmax);
+          m_run += cmax;
+#pragma unroll
+          for (int i = 0; i < 16; i++) ell[i] -= cmax;
+        }
+        float e4[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+          e4[q] = (__builtin_amdgcn_exp2f(ell[4 * q]) + __builtin_amdgcn_exp2f(ell[4 * q + 1])) +
+                  (__builtin_amdgcn_exp2f(ell[4 * q + 2]) + __builtin_amdgcn_exp2f(ell[4 * q + 3]));
+        s_run += (e4[0] + e4[1]) + (e4[2] + e4[3]);
+      }
+    };
+    // Block b of every detector and the window samples of block b - 1.  Each
+    // detector's products are issued with the interpolation of the one before
+    // it between them (the last detector's with the next block's first): a few
+    // vector instructions fit in the shadow of a matrix instruction, where a
+    // burst of one after a burst of the other adds up, also across wavefronts.
+    // Each part of the row operands is loaded anew as soon as its products are
+    // issued; the parts of the smallest products come first, so the largest
+    // (0, 0), which round the sum, are the last.  LDS accesses of a wavefront
+    // complete in order, so rows may be written over ones whose reads are issued.
+    constexpr int NM = 6 * NP + 3 * OD;                            // products of a block and detector
+    constexpr int I2 = NP > 0 ? (16 * 2 * NP) / (NM - NP) : 0;     // window samples interpolated beside part 1
+    auto det = [&](auto k_c, auto mode_c, int b, int slot) {
+      constexpr int k = decltype(k_c)::value, kp = k > 0 ? k - 1 : K - 1;
+      // 0: block 0, 1: block 1 (nothing pending before its first detector), 2: later
+      constexpr int md = decltype(mode_c)::value;
+      constexpr bool pending = md == 2 || (md == 1 && k > 0);
+      constexpr bool more = DIRECT || k + 1 < K;  // the next operands can be loaded in place
+      constexpr int kn = AB > 1 ? k : (k + 1) % K;
+      bf8 (&Ak)[NX + 2 * OD] = A[AB > 1 ? k : 0];
+      const int bn = AB > 1 || k + 1 == K ? min(b + 1, JB) : b;
+      auto reload = [&](auto part_c) {
+        if constexpr (more) rows(part_c, std::integral_constant<int, kn>{}, bn, slot, Ak);
+      };
+      f16v &ac = acc[PL ? 0 : k];
+      if constexpr (!PL && md > 0) put(0, ac, 0, 16);
+      f16v c;
+#pragma unroll
+      for (int i = 0; i < 16; i++) c[i] = 0.f;
+      auto mm = [&](const bf8 &x, const bf8 &y) { c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0); };
+      auto pairs = [&](int qa, int qb) {
+#pragma unroll
+        for (int i = 0; i < NP; i++) mm(Ak[at(k, qa, i)], Bp[k][i][qb]);
+      };
+      // n matrix instructions, v vector instructions after each
+      auto mix = [&](auto n_c, auto v_c) {
+#pragma unroll
+        for (int i = 0; i < decltype(n_c)::value; i++) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, decltype(v_c)::value, 0);
+        }
+      };
+      using KP = std::integral_constant<int, kp>;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (NP > 0) {
+        pairs(2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (DIRECT) reload(std::integral_constant<int, 2>{});
+        else rows(std::integral_constant<int, 0>{}, k_c, b, slot, Ak);
+        pairs(1, 1);
+        pairs(1, 0);
+        if constexpr (pending) {
+          interp(KP{}, std::integral_constant<int, 0>{}, std::integral_constant<int, I2>{});
+          mix(std::integral_constant<int, 2 * NP>{}, std::integral_constant<int, (4 * I2 + 2 * NP - 1) / (2 * NP)>{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        reload(std::integral_constant<int, DIRECT ? 1 : 2>{});
+      }
+      if constexpr (OD) mm(Ak[NX], Bo[k][2]);  // (0, 2) | (2, 0)
+      pairs(0, 2);
+      pairs(0, 1);
+      if constexpr (OD) {
+        mm(Ak[NX + 1], Bo[k][1]);  // (1, 1) | (0, 1)
+        mm(Ak[NX + 1], Bo[k][0]);  // (1, 0) | (0, 0)
+      }
+      pairs(0, 0);
+      if constexpr (pending) {
+        interp(KP{}, std::integral_constant<int, I2>{}, std::integral_constant<int, 16>{});
+        constexpr int n3 = 3 * NP + 3 * OD;
+        mix(std::integral_constant<int, n3>{}, std::integral_constant<int, (4 * (16 - I2) + n3 - 1) / n3>{});
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (OD) {
+        reload(std::integral_constant<int, 3>{});
+        reload(std::integral_constant<int, 4>{});
+      }
+      if constexpr (NP > 0) reload(std::integral_constant<int, DIRECT ? 0 : 1>{});
+      if constexpr (md == 2 && k == 0) window(false, b == 2);
+      ac = c;
+      constexpr int wat = PL ? k * WB : 0;
+      if constexpr (md > 0) {
+        put(wat, ac, 32, 8);
+        wave_sync();
+        fetch(k_c);
+        wave_sync();
+      }
+      if constexpr (PL) put(wat, ac, 0, 16);
+    };
+    auto block = [&](auto mode_c, int b, int slot) {
+      if constexpr (!DIRECT) rows_first(std::integral_constant<int, 0>{}, b, slot, A[0]);
+      det(std::integral_constant<int, 0>{}, mode_c, b, slot);
+      if constexpr (K > 1) det(std::integral_constant<int, 1>{}, mode_c, b, slot);
+      if constexpr (K > 2) det(std::integral_constant<int, 2>{}, mode_c, b, slot);
+    };
+    using M0 = std::integral_constant<int, 0>;
+    using M1 = std::integral_constant<int, 1>;
+    using M2 = std::integral_constant<int, 2>;
+    if constexpr (DIRECT) {
+      if (active) {
+        rows_first(M0{}, 0, 0, A[0]);
+        if constexpr (AB > 1) rows_first(M1{}, 0, 0, A[AB > 1 ? 1 : 0]);
+        if constexpr (AB > 2) rows_first(M2{}, 0, 0, A[AB > 2 ? 2 : 0]);
+        block(M0{}, 0, 0);
+        block(M1{}, 1, 0);
+        for (int b = 2; b <= JB; b++) block(M2{}, b, 0);
+      }
+    } else {
+      auto staged = [&](auto mode_c, int b) {
+        lds_copy_wait();
+        __syncthreads();  // block b is in its stage, every wavefront is done with the other one
+        if (b < JB) stage_block(b + 1, (b + 1) & 1);
+        if (active) block(mode_c, b, b & 1);
+      };
+      staged(M0{}, 0);
+      staged(M1{}, 1);
+      for (int b = 2; b <= JB; b++) staged(M2{}, b);
+    }
+    if (active) {
+      interp(std::integral_constant<int, K - 1>{}, M0{}, std::integral_constant<int, 16>{});
+      window(true, JB == 1);
+    }
+    if (active && MODE == 1) {
+      // the slot's largest data term over the two lanes of the sample
+      float mo = am;
+      mo = fmaxf(mo, __shfl_xor(mo, 32));
+      if (h == 0) gpw(a.amax)[(int64_t)t * kTS + sc] = valid ? mo : NAN;
+    } else if (active && MODE == 2) {
+      // per-node sums over the two lanes, then the nodes in FP64:
+      // ln L_tD = ln sum_i W_i exp(x_i A_max - x_i^2 B) S_i - ln n_t (nats)
+#pragma unroll
+      for (int q = 0; q < NN; q++) {
+        Sq[q] += __shfl_xor(Sq[q], 32);
+      }
+      float lt = NAN;
+      if (valid && h == 0 && hq > 0.0) {
+        const double A = (double)am * (double)kLn2f, Bv = (double)Bf * (double)kLn2f;
+        const double c = 3.0 * p.d_ref * p.d_ref * p.d_ref / (a.dm_hi * a.dm_hi * a.dm_hi - a.dm_lo * a.dm_lo * a.dm_lo);
+        const double lc = log(0.5 * hq * c);
+        double cmax = -INFINITY, acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < NN; q++) {
+          const double tq = ta + hq * (0.5 + 0.5 * dm_gl_node(q));
+          const double xd = (double)xs[q];
+          const double ci = lc + log(dm_gl_weight(q)) - 3.0 * tq + xd * A - xd * xd * Bv + log((double)Sq[q]);
+          if (ci > cmax) {
+            acc = acc * exp(cmax - ci) + 1.0;
+            cmax = ci;
+          } else {
+            acc += exp(ci - cmax);
+          }
+        }
+        lt = (float)(cmax + log(acc) - log((double)NT));
+      }
+      if (!isfinite(lt)) lt = NAN;
+      if (flag != 0 && h == 0) {
+        if (a.lnL) gpw(a.lnL)[col] = lt;
+        if (a.lnw) gpw(a.lnw)[col] = lt + (a.ln_ratio ? gp(a.ln_ratio)[col] : 0.f);
+      }
+    } else if (active) {
+      // combine the two lanes of each sample (base 2), then ln L_t
+      float mo = m_run;
+      mo = fmaxf(mo, __shfl_xor(mo, 32));
+      float sum = s_run * __builtin_amdgcn_exp2f(m_run - mo);
+      sum += __shfl_xor(sum, 32);
+      float lt = ((mo - Bf) + __log2f(sum)) * kLn2f - __logf((float)NT);
+      if (!valid || !isfinite(lt)) lt = NAN;
+      if (flag != 0 && h == 0) {
+        if (a.lnL) gpw(a.lnL)[col] = lt;
+        if (a.lnw) gpw(a.lnw)[col] = lt + (a.ln_ratio ? gp(a.ln_ratio)[col] : 0.f);
+      }
+    }
+  }
+}
+
+// Persistent grid: as many workgroups as the device keeps resident
+// (residency 0), or half as many per compute unit, at least one (residency 1:
+// fewer workgroups sharing a compute unit's LDS, caches and issue slots).
+template <int G, int K, bool D, int MODE, int WPE = base_wpe(G, K, MODE, D)>
+static void launch_tk(const MfmaArgs &a, int lo, int hi, int cls, hipStream_t st, int residency) {
+  static int per_cu = 0;
+  if (per_cu == 0) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mfma_kernel<G, K, D, MODE, WPE>, 256, 0) != hipSuccess ||
+        nb < 1)
+      nb = 1;
+    per_cu = nb;
+  }
+  const int pc = residency ? std::max(1, per_cu / 2) : per_cu;
+  const int grid = std::max(1, a.grid / 4 * pc);  // a.grid = 4 per compute unit
+  hipLaunchKernelGGL((mfma_kernel<G, K, D, MODE, WPE>), dim3(grid), dim3(256), 0, st, a, lo, hi, cls);
+}
+
+// pass: 0 ln L_t (staged or direct feed); 1, 2 the passes of distance
+// marginalization (staged feed)
+template <int G, int K>
+static void launch_tkm(const MfmaArgs &a, bool direct, int pass, int lo, int hi, int cls, hipStream_t st, int res,
+                       int wpe) {
+  // a cap the class cannot meet without spilling runs the uncapped form
+  constexpr int D3 = can_wpe(G, K, 3) ? 3 : base_wpe(G, K, 0, true), D4 = can_wpe(G, K, 4) ? 4 : base_wpe(G, K, 0, true);
+  constexpr int S3 = can_wpe(G, K, 3) ? 3 : base_wpe(G, K, 0, false);
+  if (pass == 1) launch_tk<G, K, true, 1>(a, lo, hi, cls, st, res);
+  else if (pass == 2) launch_tk<G, K, true, 2>(a, lo, hi, cls, st, res);
+  else if (direct && wpe == 3) launch_tk<G, K, true, 0, D3>(a, lo, hi, cls, st, res);
+  else if (wpe == 3) launch_tk<G, K, false, 0, S3>(a, lo, hi, cls, st, res);
+  else if (direct && wpe == 4) launch_tk<G, K, true, 0, D4>(a, lo, hi, cls, st, res);
+  else if (direct) launch_tk<G, K, true, 0>(a, lo, hi, cls, st, res);
+  else launch_tk<G, K, false, 0>(a, lo, hi, cls, st, res);
+}
+
+template <int G>
+static void launch_class(const MfmaArgs &a, int K, bool direct, int pass, int lo, int hi, int cls, hipStream_t st,
+                         int res, int wpe) {
+  if (K == 1) launch_tkm<G, 1>(a, direct, pass, lo, hi, cls, st, res, wpe);
+  else if (K == 2) launch_tkm<G, 2>(a, direct, pass, lo, hi, cls, st, res, wpe);
+  else launch_tkm<G, 3>(a, direct, pass, lo, hi, cls, st, res, wpe);
+}
+
+// Launch configuration of a class, as the autotuner numbers it: 1 staged,
+// 2 direct, 3 staged at half residency, 4 direct at half residency, 5 and 6
+// direct with registers capped so that three (5) or four (6) wavefronts fit
+// on a SIMD, 7 staged capped for three
+static bool cfg_direct(int mode) { return mode == 2 || (mode >= 4 && mode <= 6); }
+static int cfg_residency(int mode) { return mode == 3 || mode == 4 ? 1 : 0; }
+static int cfg_wpe(int mode) { return mode == 5 || mode == 7 ? 3 : mode == 6 ? 4 : 1; }
+// whether configuration mode is a form of its own for the class (else it runs
+// the uncapped form of the same feed)
+static bool cfg_own(int mode, int T, int K) {
+  const int wpe = cfg_wpe(mode);
+  return wpe == 1 || can_wpe((T + 1) / 2, K, wpe);
+}
+
+static hipError_t launch_mode(const MfmaArgs &a, int T, int K, bool direct, int lo, int hi, int cls, hipStream_t st,
+                              int pass = 0, int res = 0, int wpe = 1) {
+  switch ((T + 1) / 2) {  // groups of 8 elements
+#define RIFT_G_CASE(GG) \
+  case GG: launch_class<GG>(a, K, direct, pass, lo, hi, cls, st, res, wpe); break;
+    RIFT_G_CASE(1) RIFT_G_CASE(2) RIFT_G_CASE(3) RIFT_G_CASE(4) RIFT_G_CASE(5) RIFT_G_CASE(6) RIFT_G_CASE(7)
+    RIFT_G_CASE(8)
+#undef RIFT_G_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipSuccess;
+}
+
+// Every launch configuration of class c on the call's own data, one after the
+// other on st, timed with events (the class's work-unit counter cleared
+// before each); the results are bit-identical, so the later runs only
+// rewrite the outputs.  The configurations are run in two passes and each is
+// judged by the faster of its two runs, so none pays alone for the class's
+// first touch of Q and its tile records or for clocks still rising at the
+// start of the pass.  The staged form at full residency is kept unless
+// another configuration is at least 3 % faster.
+static hipError_t tune_class(const MfmaArgs &a, int T, int K, int lo, int hi, int c, hipStream_t st, int &mode) {
+  constexpr int kCfg = kFeedConfigs, kPasses = 2, kEv = 2 * kPasses * kCfg;
+  hipEvent_t ev[kEv] = {};
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < kEv && e == hipSuccess; i++) e = hipEventCreate(&ev[i]);
+  for (int r = 0; r < kPasses; r++)
+    for (int m = 1; m <= kCfg && e == hipSuccess; m++) {
+      hipEvent_t *em = ev + 2 * (r * kCfg + m - 1);
+      if (!cfg_own(m, T, K)) {
+        if (r == kPasses - 1 && m == kCfg) e = hipEventRecord(em[1], st);  // the event waited for below
+        continue;
+      }
+      if (r > 0 || m > 1) e = fill_u32(a.ctl + 1 + c, 1, 0u, st);
+      if (e == hipSuccess) e = hipEventRecord(em[0], st);
+      if (e == hipSuccess) e = launch_mode(a, T, K, cfg_direct(m), lo, hi, c, st, 0, cfg_residency(m), cfg_wpe(m));
+      if (e == hipSuccess) e = hipEventRecord(em[1], st);
+    }
+  if (e == hipSuccess) e = hipEventSynchronize(ev[kEv - 1]);
+  float best = 0.f;
+  int pick = 1;
+  for (int m = 1; m <= kCfg && e == hipSuccess; m++) {
+    if (!cfg_own(m, T, K)) continue;
+    float t = 0.f;
+    for (int r = 0; r < kPasses && e == hipSuccess; r++) {
+      const hipEvent_t *em = ev + 2 * (r * kCfg + m - 1);
+      float tr = 0.f;
+      e = hipEventElapsedTime(&tr, em[0], em[1]);
+      t = r == 0 ? tr : std::min(t, tr);
+    }
+    if (e != hipSuccess) break;
+    if (m == 1 || t < 0.97f * best) {
+      best = t;
+      pick = m;
+    }
+  }
+  if (e == hipSuccess) mode = pick;
+  for (int i = 0; i < kEv; i++)
+    if (ev[i]) (void)hipEventDestroy(ev[i]);
+  return e;
+}
+
+hipError_t mfma_forward(const MfmaArgs &a, const int *class_T, const int *class_K, const int *class_item0, int n_classes,
+                        const int *mclass_M, const int *mclass_item0, const int64_t *mclass_tiles, int n_mclasses,
+                        int *class_mode, bool tune, hipStream_t st, const Fanout &fo, hipEvent_t ev0,
+                        hipEvent_t ev1) {
+  if (a.total <= 0) return hipSuccess;
+  hipError_t e = mfma_prepare(a, mclass_M, mclass_item0, mclass_tiles, n_mclasses, st);
+  if (e != hipSuccess) return e;
+  uint64_t done = 0;  // classes evaluated while being measured
+  if (tune && !a.dmarg)
+    for (int c = 0; c < n_classes && c < 64; c++)
+      if (class_mode[c] == 0) {
+        e = tune_class(a, class_T[c], class_K[c], class_item0[c], class_item0[c + 1], c, st, class_mode[c]);
+        if (e != hipSuccess) return e;
+        done |= 1ull << c;
+      }
+  if (ev0) (void)hipEventRecord(ev0, st);
+  if (a.dmarg) {
+    // distance marginalization: every class's largest data terms, then (the
+    // work-unit counters cleared by a fill kernel) the integrals over D
+    for (int pass = 1; pass <= 2; pass++) {
+      if (pass == 2) {
+        e = fill_u32(a.ctl + 1, n_classes, 0u, st);
+        if (e != hipSuccess) return e;
+      }
+      fan_fork(fo, st, n_classes);
+      for (int c = 0; c < n_classes; c++) {
+        e = launch_mode(a, class_T[c], class_K[c], false, class_item0[c], class_item0[c + 1], c,
+                        fan_stream(fo, st, c), pass);
+        if (e != hipSuccess) return e;
+      }
+      e = hipGetLastError();
+      fan_join(fo, st, n_classes);
+      if (e != hipSuccess) return e;
+    }
+    if (ev1) (void)hipEventRecord(ev1, st);
+    return e;
+  }
+  fan_fork(fo, st, n_classes);
+  for (int c = 0; c < n_classes; c++) {
+    if (c < 64 && (done >> c) & 1) continue;
+    e = launch_mode(a, class_T[c], class_K[c], cfg_direct(class_mode[c]), class_item0[c], class_item0[c + 1], c,
+                    fan_stream(fo, st, c), 0, cfg_residency(class_mode[c]), cfg_wpe(class_mode[c]));
+    if (e != hipSuccess) return e;
+  }
+  e = hipGetLastError();
+  fan_join(fo, st, n_classes);
+  if (ev1) (void)hipEventRecord(ev1, st);
+  return e;
+}
+
+}  // namespace rift

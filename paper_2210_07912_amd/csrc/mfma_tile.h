@@ -9,6 +9,8 @@
 namespace rift {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
 constexpr int kTS = 16;          // samples per tile (MFMA columns)
 constexpr int kWaves = 4;        // wavefronts per workgroup
@@ -24,6 +26,32 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// 16 bytes per lane from base + off straight into LDS at dst + 16 lane (base
+// and dst the same for the wavefront).  An instruction of its own rather than
+// the compiler's builtin: after that, the compiler waits for the copy before
+// the wavefront's next read of any LDS, so the copy of the next block would
+// not overlap the work on this one.  Nothing may read the destination before
+// lds_copy_wait() and a barrier.
+__device__ __forceinline__ void lds_copy16(const void *base, uint32_t off, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
+               :
+               : "s"(base), "v"(off), "s"(dst)
+               : "memory", "m0");
+}
+__device__ __forceinline__ void lds_copy_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// v = v0 + v1 + v2 in BF16, each the rounding (to nearest) of what the ones
+// before leave: 3 x 8 bits and the signs cover the 24 bits of an FP32 value.
+__device__ __forceinline__ void split3(const float (&v)[8], bf8 &v0, bf8 &v1, bf8 &v2) {
+#pragma unroll
+  for (int e = 0; e < 8; e++) {
+    v0[e] = (__bf16)v[e];
+    const float r1 = v[e] - (float)v0[e];
+    v1[e] = (__bf16)r1;
+    v2[e] = (__bf16)(r1 - (float)v1[e]);
+  }
 }
 
 // Element of the (re, im)-interleaved operand vector (length 2 Mp = 4 T) that

@@ -329,12 +329,12 @@ rift_status build_point(rift_ile *h, const rift_ile_point &q, PointDev &p) {
   p.n_t = q.n_t;
   p.pad = q.pad;
   p.L = q.n_t + 2 * q.pad + 3;
-  p.Lpad = p.L + 32;
+  p.Lpad = p.L + 64;  // a block of 32 rows past the last window row of any bin
   p.f_s = q.f_s;
   p.d_ref = q.d_ref;
   p.gmst = q.gmst;
   p.Mp = (M + 1) & ~1;
-  p.bin_w = 14;
+  p.bin_w = kBinW;
   p.nq = (2 * q.pad) / p.bin_w + 1;
   long long nb = 1;
   for (int k = 0; k < K; k++) nb *= p.nq;
@@ -401,19 +401,18 @@ rift_status build_point(rift_ile *h, const rift_ile_point &q, PointDev &p) {
     HIPCHK(h, hipMemcpy(d, qv.data(), sizeof(R) * qv.size(), hipMemcpyHostToDevice));
     p.Q = d;
   }
-  // Q for the matrix cores (FP32 handles): [K][Lpad][2 Mp], element e = 2m + part,
-  // zero past M and past L
+  // Q for the matrix cores (FP32 handles), laid out on the device: rows
+  // [K][Lpad][2 Mp] (element e = 2m + part, zero past M and past L), and the
+  // same values as three BF16 parts
   if (sizeof(R) == 4) {
-    const int E = 2 * p.Mp;
-    std::vector<float> qm((size_t)K * E * p.Lpad, 0.f);
-    for (int k = 0; k < K; k++)
-      for (int r = 0; r < p.L; r++)
-        for (int e = 0; e < 2 * M; e++)
-          qm[((size_t)k * p.Lpad + r) * E + e] = (float)q.Q[((size_t)k * p.L + r) * M * 2 + e];
-    HIPCHK(h, hipMalloc(&d, sizeof(float) * qm.size()));
+    const int E = 2 * p.Mp, C = 3 * ((E + 7) / 8);
+    HIPCHK(h, hipMalloc(&d, sizeof(float) * (size_t)K * E * p.Lpad));
     h->owned.push_back(d);
-    HIPCHK(h, hipMemcpy(d, qm.data(), sizeof(float) * qm.size(), hipMemcpyHostToDevice));
     p.Qm = (const float *)d;
+    HIPCHK(h, hipMalloc(&d, 16 * (size_t)K * C * p.Lpad));
+    h->owned.push_back(d);
+    p.Qs = d;
+    HIPCHK(h, mfma_layouts((const float *)p.Q, (float *)p.Qm, (void *)p.Qs, K, p.Lpad, 2 * M, E, h->stream));
   }
   return RIFT_OK;
 }
@@ -585,7 +584,8 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
       class_K.push_back(p.K);
       class_item0.push_back((int)i);
     }
-    const int64_t tiles_i = (it.cnt[i] + 15) / 16 + p.n_bins_key + 4;
+    // bins are padded to whole pairs of tiles, a point to whole groups of 4
+    const int64_t tiles_i = (it.cnt[i] + 15) / 16 + 2 * std::min<int64_t>(p.n_bins_key, it.cnt[i]) + 4;
     const int mkey = p.Vpk ? -p.M : p.M;  // V tables: the general coefficient kernel
     if (mclass_M.empty() || mclass_M.back() != mkey) {
       mclass_M.push_back(mkey);
@@ -645,6 +645,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
   a.ln_ratio = ln_ratio;
   a.n_bins = bin0.back();
   a.max_tiles = (int)max_tiles;
+  a.unit_tiles = grad ? 4 : 8;
   void *p;
   if ((s = ws_get(h, W_KEY, 4 * total, &p)) != RIFT_OK) return s;
   a.key = (uint32_t *)p;
@@ -660,8 +661,9 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
   a.item_tiles = (uint32_t *)p;
   if ((s = ws_get(h, W_PERM, sizeof(SampleRec) * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
   a.rec = (SampleRec *)p;
-  if ((s = ws_get(h, W_TILES, 4 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
+  if ((s = ws_get(h, W_TILES, 8 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
   a.tile_item = (int *)p;
+  a.tile_key = (uint32_t *)p + max_tiles;
   if ((s = ws_get(h, W_COP, sizeof(float) * (size_t)cop_floats, &p)) != RIFT_OK) return s;
   a.cop = (float *)p;
   if (grad) {  // the adjoint's per-tile G_k (cop layout) and H_k

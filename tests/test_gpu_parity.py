@@ -803,6 +803,53 @@ def test_single_detector_ragged_window(ile, orc):
     assert np.all(np.abs(out - ref64) <= 1e-9 * (1 + np.abs(ref64)))
 
 
+@pytest.mark.parametrize("M,K,n_t,n", [
+    (1, 1, 1, 1), (1, 3, 31, 33), (2, 2, 32, 32), (3, 1, 33, 31), (4, 3, 63, 129), (5, 2, 64, 257), (8, 3, 65, 700),
+    (12, 1, 96, 300), (13, 2, 97, 127), (16, 3, 40, 500), (20, 2, 32, 255), (21, 3, 100, 1025), (24, 1, 129, 90),
+    (28, 3, 70, 300), (29, 2, 33, 64), (32, 3, 64, 200), (32, 1, 5, 40)])
+def test_matrix_core_shapes(ile, orc, M, K, n_t, n):
+    """Every group count of the split operands (8 elements each, odd and even
+    ones), detector count and edge of the 32-row blocks and 32-sample tiles, in
+    both feeds and the forms capped for registers, against the oracle; the
+    feeds bit-identical; the distance-marginalized value finite where ln L_t is
+    and, on a narrow prior, equal to ln L_t at its distance."""
+    rng = np.random.default_rng([91, M, K, n_t])
+    dets = ("H1", "L1", "V1")[:K]
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1400 + M, dets=dets, n_modes=2, n_t=n_t, snr=1.0, kernel="none")
+    d = dict(synth.make_point(spec))
+    lm = [(l, m) for l in range(2, 9) for m in range(-l, l + 1)]
+    pick = rng.choice(len(lm), M, replace=False)
+    d["ell"] = np.array([lm[i][0] for i in pick], dtype=np.int32)
+    d["em"] = np.array([lm[i][1] for i in pick], dtype=np.int32)
+    L = d["Q"].shape[1]
+    G = rng.standard_normal((K, M, M + 2)) + 1j * rng.standard_normal((K, M, M + 2))
+    d["U"] = 100.0 * G @ G.conj().transpose(0, 2, 1) / (M + 2)
+    d["Q"] = 30.0 * (rng.standard_normal((K, L, M)) + 1j * rng.standard_normal((K, L, M)))
+    th = synth.mixed_samples(d, 33, n)
+    p = orc.Point.from_dict(d, complex64=True)
+    ref = orc.lnL_t(p, th)
+    outs = []
+    for mode in (0, 2, 3, 4, 5):
+        h = _handle(ile, [d], "fp32")
+        h.set_autotune(mode)
+        _say(f"M={M} K={K} n_t={n_t} n={n} feed {mode}")
+        outs.append(h.lnL(torch.tensor(th)).cpu().numpy())
+        h.close()
+    _check_fp32(outs[0], ref, f"M={M} K={K} n_t={n_t}", p, th)
+    for o in outs[1:]:
+        assert np.array_equal(o, outs[0], equal_nan=True)
+    # a prior of relative width 1e-5 at D: ln L_tD = ln L_t(D) to its slope times the width
+    D = 150.0
+    th[5] = D
+    refD = orc.lnL_t(p, th)
+    h = _handle(ile, [d], "fp32", d_min=D * (1 - 5e-6), d_max=D * (1 + 5e-6))
+    h.set_distance_marginalization(True)
+    out = h.lnL(torch.tensor(th)).cpu().numpy()
+    B = _quad(p, th)
+    tol = _fp32_tol(refD, B, K, M) + 2e-5 + 1e-5 * (np.abs(refD) + 3 * np.abs(B) + 3)
+    assert np.all(np.abs(out - refD) <= tol), np.abs(out - refD).max()
+
+
 def test_plain_long_window(ile, orc):
     """FP64 plain form on a long window (n_t = 1900, H1 + L1, two modes): the
     workgroup then holds the fewest samples it allows (4, each sample's window
