@@ -542,9 +542,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
       }
     } else if (active) {
       // combine the two lanes of each sample (base 2), then ln L_t
-      float mo = m_run;
-      mo = fmaxf(mo, __shfl_xor(mo, 32));
-      float sum = s_run * __builtin_amdgcn_exp2f(m_run - mo);
+      // (a lane whose 16 window samples all lie past n_t has no reference)
+      const float mr = s_run > 0.f ? m_run : -INFINITY;
+      const float mo = fmaxf(mr, __shfl_xor(mr, 32));
+      float sum = s_run * __builtin_amdgcn_exp2f(mr - mo);
       sum += __shfl_xor(sum, 32);
       float lt = ((mo - Bf) + __log2f(sum)) * kLn2f - __logf((float)NT);
       if (!valid || !isfinite(lt)) lt = NAN;

@@ -850,6 +850,33 @@ def test_matrix_core_shapes(ile, orc, M, K, n_t, n):
     assert np.all(np.abs(out - refD) <= tol), np.abs(out - refD).max()
 
 
+@pytest.mark.parametrize("n_t", [1, 5, 13, 16, 17])
+def test_short_window_far_below_zero(ile, orc, n_t):
+    """Windows that leave some lanes of a sample without window samples, with
+    data terms hundreds of nats below zero: a lane with nothing to add must not
+    set the reference the others are summed against."""
+    rng = np.random.default_rng([92, n_t])
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1500, dets=("H1", "L1"), n_modes=5, n_t=n_t, snr=1.0, kernel="none")
+    d = dict(synth.make_point(spec))
+    L = d["Q"].shape[1]
+    d["Q"] = 300.0 * (rng.standard_normal((2, 1, 5)) + 1j * rng.standard_normal((2, 1, 5))) * np.ones((2, L, 1))
+    d["U"] = np.broadcast_to(1e5 * np.eye(5), (2, 5, 5)).astype(complex)  # data terms below B, as the bound assumes
+    th = synth.mixed_samples(d, 34, 300)
+    th[5] = np.float32(th[5] / 20.0)
+    for prec in ("fp32", "fp64"):
+        p = orc.Point.from_dict(d, complex64=(prec == "fp32"))
+        ref = orc.lnL_t(p, th)
+        assert (ref + _quad(p, th)).min() < -150.0  # the data term alone
+        h = _handle(ile, [d], prec)
+        _say(f"short window n_t={n_t} {prec}")
+        out = h.lnL(torch.tensor(th)).cpu().numpy()
+        h.close()
+        if prec == "fp32":
+            _check_fp32(out, ref, f"short window n_t={n_t}", p, th)
+        else:
+            assert np.all(np.abs(out - ref) <= 1e-9 * (1 + np.abs(ref)))
+
+
 def test_plain_long_window(ile, orc):
     """FP64 plain form on a long window (n_t = 1900, H1 + L1, two modes): the
     workgroup then holds the fewest samples it allows (4, each sample's window
