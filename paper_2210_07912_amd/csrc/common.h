@@ -167,7 +167,8 @@ __device__ __forceinline__ double ipow(double x, int n) {
 }
 
 // Y = ynorm * d(iota) * exp(i m phi); dd = d/diota of the real factor.
-__device__ __forceinline__ void harmonic(const PointDev &p, int m, double ci, double si, double cphi_m,
+template <typename PT>
+__device__ __forceinline__ void harmonic(const PT &p, int m, double ci, double si, double cphi_m,
                                          double sphi_m, double &yr, double &yi, double *dyr = nullptr,
                                          double *dyi = nullptr) {
   double d = 0.0, dd = 0.0;

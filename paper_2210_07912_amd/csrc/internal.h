@@ -64,15 +64,19 @@ struct SampleRec {
   int16_t flag;   // 0 padding slot, 1 valid, 2 invalid sample
 };
 
-// per-tile coefficients written by the coefficient pass (16 samples)
-struct CoefTile {
-  float B[16];               // quadratic term (FP64, rounded), times log2 e
-  float xf[kMaxDet][2][16];  // (D_ref / D) F_k times log2 e (re, im); zero past K
-  float mu[kMaxDet][16];     // interpolation fraction
+// per-tile coefficients written by the coefficient pass (16 samples), in the
+// bulk precision R; FP32 holds B and x F_k times log2 e (its window works in
+// base 2), FP64 holds them as they are
+template <typename R>
+struct CoefTileT {
+  R B[16];                   // quadratic term (FP64, rounded)
+  R xf[kMaxDet][2][16];      // (D_ref / D) F_k (re, im); zero past K
+  R mu[kMaxDet][16];         // interpolation fraction
   int n[kMaxDet][16];        // integer row offset (1<<28 for padding / invalid)
   int col[16];               // output column (-1: padding slot)
   int flag[16];              // 0 padding, 1 valid, 2 invalid sample
 };
+using CoefTile = CoefTileT<float>;
 
 // matrix-core layouts Qm and Qs of a point (see PointDev) from its rows Q
 hipError_t mfma_layouts(const float *Q, float *Qm, void *Qs, int K, int Lpad, int M2, int E, hipStream_t st);
@@ -85,15 +89,18 @@ struct WorkUnit {
   uint32_t key;     // the bin, within its point
 };
 
-struct MfmaArgs {
+// R: the bulk precision (float, or double for FP64 handles).  A record's theta
+// is FP32: FP64 passes after the sort read a sample's theta at its column.
+template <typename R>
+struct MfmaArgsT {
   const PointDev *pts;
   ItemsDev items;
   int64_t stride;
   int64_t total;          // flat samples over all items
-  const float *theta;     // [7][stride]
-  float *lnL;             // [stride] or null
-  float *lnw;             // [stride] or null
-  const float *ln_ratio;  // [stride] or null
+  const R *theta;         // [7][stride]
+  R *lnL;                 // [stride] or null
+  R *lnw;                 // [stride] or null
+  const R *ln_ratio;      // [stride] or null
   // workspace
   uint32_t *key;          // [total] bin of each flat sample within its point
   int16_t *nsh;           // [total][4] integer row offsets n_k (index 3: valid flag)
@@ -104,19 +111,19 @@ struct MfmaArgs {
   SampleRec *rec;         // [16 max_tiles] sorted samples (flag 0: padding)
   int *tile_item;         // [max_tiles]
   uint32_t *tile_key;     // [max_tiles] the tile's bin within its point (kNoBin: padding past the last bin)
-  float *cop;             // per point, per tile [K][2 Mp][16] floats; the coefficient pass fills the first
+  R *cop;                 // per point, per tile [K][2 Mp][16] floats; the coefficient pass fills the first
                           // [2 Mp][16]: Y_m (element 2m + re/im) of the tile's samples
   int64_t *item_cop;      // [n_items] offset of each point's operands in cop
-  CoefTile *ctile;        // [max_tiles]
+  CoefTileT<R> *ctile;    // [max_tiles]
   WorkUnit *unit;         // [max_tiles] work units, bins in order, points in order
   uint32_t *bin_unit;     // [n_bins] first unit of the bin within its item
   uint32_t *item_units;   // [n_items + 1] unit prefix over items (filled on device)
   uint32_t *ctl;          // [0]: number of tiles, [1 + c]: unit counter of class c
   // adjoint (null in the forward pass)
-  const float *gin;       // [stride] upstream d/d ln L_t, or null (= 1)
-  float *grad;            // [7][stride] gradient of ln L_t (times gin)
-  float *gop;             // per point [tiles][K][2 Mp][16]: G_k = sum_r c_k[r] Q_k[r] (cop layout)
-  float *hop;             // [tiles][kMaxDet][16]: H_k = sum_j p_j Re(a^dag Qtilde'_k(j))
+  const R *gin;           // [stride] upstream d/d ln L_t, or null (= 1)
+  R *grad;                // [7][stride] gradient of ln L_t (times gin)
+  R *gop;                 // per point [tiles][K][2 Mp][16]: G_k = sum_r c_k[r] Q_k[r] (cop layout)
+  R *hop;                 // [tiles][kMaxDet][16]: H_k = sum_j p_j Re(a^dag Qtilde'_k(j))
   int *jrng;              // [16 max_tiles][4] or null: the samples to refine, appended in any order (count in
                           // ctl[kCtlRefine]): sorted slot, then the window blocks whose maximum is within
                           // kRefineNats of the sample's (b0 | b1 << 16, b2 | count << 16)
@@ -132,6 +139,7 @@ struct MfmaArgs {
   int unit_tiles;         // tiles of a work unit: 8 (evaluation), 4 (adjoint)
   int grid;               // persistent workgroups
 };
+using MfmaArgs = MfmaArgsT<float>;
 
 // Streams a call may fan out on: the class kernels of one evaluation run
 // concurrently on side streams (default priority), forked from and joined
@@ -192,9 +200,19 @@ constexpr int kRefineBlocks = 3;
 constexpr int kCtlRefine = 1 + kMaxClasses;  // ctl slot of the refinement count
 constexpr float kRefineNats = 40.f;
 hipError_t refine_backward(const MfmaArgs &a, hipStream_t st);
-// the part both share: delay-bin sort, tile records, coefficient pass, work units
-hipError_t mfma_prepare(const MfmaArgs &a, const int *mclass_M, const int *mclass_item0, const int64_t *mclass_tiles,
-                        int n_mclasses, hipStream_t st);
+// the part all share: delay-bin sort, tile records, coefficient pass, work units
+template <typename R>
+hipError_t mfma_prepare(const MfmaArgsT<R> &a, const int *mclass_M, const int *mclass_item0,
+                        const int64_t *mclass_tiles, int n_mclasses, hipStream_t st);
+// the adjoint's chain rule over the sorted slots (k_bwd.hip)
+template <typename R>
+hipError_t chain_launch(const MfmaArgsT<R> &a, const int *mclass_M, const int *mclass_item0,
+                        const int64_t *mclass_tiles, int n_mclasses, hipStream_t st);
+// FP64 handles: ln L_t, or with a.grad its gradient too, on the FP64 matrix
+// cores (k_eval64.hip), from the same sorted tiles
+hipError_t mfma64_run(const MfmaArgsT<double> &a, const int *class_T, const int *class_K, const int *class_item0,
+                      int n_classes, const int *mclass_M, const int *mclass_item0, const int64_t *mclass_tiles,
+                      int n_mclasses, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 
 // ---- sampler / reductions / adaptation -------------------------------------
 // Proposal of one point: per parameter d in mask, either the 100-bin

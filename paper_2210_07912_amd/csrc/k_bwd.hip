@@ -371,8 +371,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
 // polynomial tables: Y = s^par P(u) e^{i m phi} with s = sin(iota)/2 and
 // u = cos^2(iota/2), so dY/diota = (par cos(iota)/2 P(u) - s^(par+1) P'(u))
 // e^{i m phi}, with P and P' by one Horner pass.
-template <int MC>
-__global__ void __launch_bounds__(64) chain_kernel(MfmaArgs a, int item_lo, int item_hi) {
+template <int MC, typename R>
+__global__ void __launch_bounds__(64) chain_kernel(MfmaArgsT<R> a, int item_lo, int item_hi) {
   constexpr int YR = MC > 0 ? MC : kMaxModes;
   const int64_t t_lo = a.item_tiles[item_lo], t_hi = a.item_tiles[item_hi];
   const int64_t t_blk = t_lo + 4 * (int64_t)blockIdx.x;
@@ -388,15 +388,15 @@ __global__ void __launch_bounds__(64) chain_kernel(MfmaArgs a, int item_lo, int 
   const int K = p.K, E = 2 * p.Mp;
   const int M = MC > 0 ? MC : p.M;
   const int64_t col = rec.col;
-  const RIFT_GLOBAL float *gk = gp(a.gop + a.item_cop[it] + (int64_t)(t - a.item_tiles[it]) * K * E * kTS + s);
-  const RIFT_GLOBAL float *hk = gp(a.hop + (size_t)t * (kMaxDet * kTS) + s);
+  const RIFT_GLOBAL R *gk = gp(a.gop + a.item_cop[it] + (int64_t)(t - a.item_tiles[it]) * K * E * kTS + s);
+  const RIFT_GLOBAL R *hk = gp(a.hop + (size_t)t * (kMaxDet * kTS) + s);
   double out[7] = {0, 0, 0, 0, 0, 0, 0};
   bool ok = rec.flag == 1;
   for (int k = 0; k < K && ok; k++) ok = isfinite(hk[k * kTS]);
   if (ok) {
     double th[7];
 #pragma unroll
-    for (int d = 0; d < 7; d++) th[d] = (double)rec.th[d];
+    for (int d = 0; d < 7; d++) th[d] = sizeof(R) == 4 ? (double)rec.th[d] : (double)a.theta[d * a.stride + col];
     const double x = p.d_ref / th[RIFT_DIST];
     SkyTrig tr = sky_trig(th[RIFT_ALPHA], th[RIFT_DELTA], th[RIFT_PSI], p.gmst);
     double ci, si, c1, s1;
@@ -405,6 +405,12 @@ __global__ void __launch_bounds__(64) chain_kernel(MfmaArgs a, int item_lo, int 
     const double u = ci * ci, hs = si * ci, hc = 0.5 * (ci * ci - si * si);
     // Y_m (and, with dy, dY_m / d iota) of mode m
     auto mode = [&](int m, double &yr, double &yi, double *dyr, double *dyi) {
+      if constexpr (sizeof(R) == 8) {  // the Wigner sum, as in the coefficient pass
+        double cm, sm;
+        phase_m(p.em[m], c1, s1, cm, sm);
+        harmonic(p, m, ci, si, cm, sm, yr, yi, dyr, dyi);
+        return;
+      }
       const int deg = p.hdeg[m];
       double P = p.hpoly[m][deg], dP = 0.0;
       for (int j = deg - 1; j >= 0; j--) {
@@ -505,8 +511,29 @@ __global__ void __launch_bounds__(64) chain_kernel(MfmaArgs a, int item_lo, int 
   }
   const double gi = a.gin ? (double)gp(a.gin)[col] : 1.0;
 #pragma unroll
-  for (int d = 0; d < 7; d++) gpw(a.grad)[d * a.stride + col] = ok ? (float)(gi * out[d]) : NAN;
+  for (int d = 0; d < 7; d++) gpw(a.grad)[d * a.stride + col] = ok ? (R)(gi * out[d]) : R(NAN);
 }
+
+template <typename R>
+hipError_t chain_launch(const MfmaArgsT<R> &a, const int *mclass_M, const int *mclass_item0,
+                        const int64_t *mclass_tiles, int n_mclasses, hipStream_t st) {
+  for (int c = 0; c < n_mclasses; c++) {
+    const int lo = mclass_item0[c], hi = mclass_item0[c + 1];
+    const dim3 grid((unsigned)(((int64_t)kTS * mclass_tiles[c] + 63) / 64));
+    switch (mclass_M[c] < 0 ? -mclass_M[c] : mclass_M[c]) {
+      case 2: hipLaunchKernelGGL((chain_kernel<2, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      case 5: hipLaunchKernelGGL((chain_kernel<5, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      case 9: hipLaunchKernelGGL((chain_kernel<9, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      case 21: hipLaunchKernelGGL((chain_kernel<21, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      default: hipLaunchKernelGGL((chain_kernel<0, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+    }
+  }
+  return hipGetLastError();
+}
+template hipError_t chain_launch<float>(const MfmaArgsT<float> &, const int *, const int *, const int64_t *, int,
+                                        hipStream_t);
+template hipError_t chain_launch<double>(const MfmaArgsT<double> &, const int *, const int *, const int64_t *, int,
+                                         hipStream_t);
 
 template <int T, int K>
 static void launch_bwd_tk(const MfmaArgs &a, int lo, int hi, int cls, hipStream_t st) {
@@ -552,18 +579,7 @@ hipError_t mfma_backward(const MfmaArgs &a, const int *class_T, const int *class
   }
   fan_join(fo, st, n_classes);
   if (ev1) (void)hipEventRecord(ev1, st);
-  for (int c = 0; c < n_mclasses; c++) {
-    const int lo = mclass_item0[c], hi = mclass_item0[c + 1];
-    const dim3 grid((unsigned)(((int64_t)kTS * mclass_tiles[c] + 63) / 64));
-    switch (mclass_M[c] < 0 ? -mclass_M[c] : mclass_M[c]) {
-      case 2: hipLaunchKernelGGL(chain_kernel<2>, grid, dim3(64), 0, st, a, lo, hi); break;
-      case 5: hipLaunchKernelGGL(chain_kernel<5>, grid, dim3(64), 0, st, a, lo, hi); break;
-      case 9: hipLaunchKernelGGL(chain_kernel<9>, grid, dim3(64), 0, st, a, lo, hi); break;
-      case 21: hipLaunchKernelGGL(chain_kernel<21>, grid, dim3(64), 0, st, a, lo, hi); break;
-      default: hipLaunchKernelGGL(chain_kernel<0>, grid, dim3(64), 0, st, a, lo, hi); break;
-    }
-  }
-  e = hipGetLastError();
+  e = chain_launch(a, mclass_M, mclass_item0, mclass_tiles, n_mclasses, st);
   if (e != hipSuccess) return e;
   return refine_backward(a, st);
 }

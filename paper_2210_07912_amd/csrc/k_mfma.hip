@@ -77,7 +77,8 @@ __device__ __forceinline__ int block_item(const ItemsDev &it, int b) {
   return lo;
 }
 
-__global__ void __launch_bounds__(kSortThreads) bin_kernel(MfmaArgs a) {
+template <typename R>
+__global__ void __launch_bounds__(kSortThreads) bin_kernel(MfmaArgsT<R> a) {
   extern __shared__ uint32_t cnt_l[];
   const int it = block_item(a.items, blockIdx.x);
   const int lb = blockIdx.x - a.items.blk0[it];
@@ -93,7 +94,7 @@ __global__ void __launch_bounds__(kSortThreads) bin_kernel(MfmaArgs a) {
   // their parameters are loaded before any is used, so the loads of a
   // thread's samples are in flight together
   constexpr int U = kSortBlock / kSortThreads;
-  float th[U][7];
+  R th[U][7];
 #pragma unroll
   for (int u = 0; u < U; u++) {
     const int64_t j = j0 + threadIdx.x + (int64_t)u * kSortThreads;
@@ -140,7 +141,8 @@ __global__ void __launch_bounds__(kSortThreads) bin_kernel(MfmaArgs a) {
 constexpr int kScanBins = 64;
 constexpr int kScanRanges = 16;  // block ranges per column scan: 1024 threads
 
-__global__ void __launch_bounds__(kScanRanges * kScanBins) colscan_kernel(MfmaArgs a) {
+template <typename R>
+__global__ void __launch_bounds__(kScanRanges * kScanBins) colscan_kernel(MfmaArgsT<R> a) {
   __shared__ uint32_t part[kScanRanges][kScanBins];
   const int q = threadIdx.x >> 6, bl = threadIdx.x & 63;
   for (int it = blockIdx.y; it < a.items.n_items; it += gridDim.y) {
@@ -173,12 +175,13 @@ __global__ void __launch_bounds__(kScanRanges * kScanBins) colscan_kernel(MfmaAr
 // tiles of each bin (bins padded to whole tiles, for the evaluation to whole
 // pairs of them, the 32 samples of its wavefronts), work units of each bin
 // (groups of up to unit_tiles of its tiles), and their prefixes per point
-__device__ __forceinline__ uint32_t bin_tiles(const MfmaArgs &a, uint32_t cnt) {
-  const uint32_t w = a.unit_tiles == 8 ? 2u : 1u;
+__device__ __forceinline__ uint32_t bin_tiles(int unit_tiles, uint32_t cnt) {
+  const uint32_t w = unit_tiles == 8 ? 2u : 1u;
   return w * ((cnt + w * kTS - 1) / (w * kTS));
 }
 
-__global__ void __launch_bounds__(256) tilescan_kernel(MfmaArgs a) {
+template <typename R>
+__global__ void __launch_bounds__(256) tilescan_kernel(MfmaArgsT<R> a) {
   __shared__ uint32_t pt[256], pu[256];
   const int it = blockIdx.x;
   const int b0 = a.items.bin0[it], nb = a.items.bin0[it + 1] - b0;
@@ -187,7 +190,7 @@ __global__ void __launch_bounds__(256) tilescan_kernel(MfmaArgs a) {
   const int lo = min(nb, (int)threadIdx.x * per), hi = min(nb, lo + per);
   uint32_t ct = 0, cu = 0;
   for (int b = lo; b < hi; b++) {
-    const uint32_t tb = bin_tiles(a, a.count[b0 + b]);
+    const uint32_t tb = bin_tiles(a.unit_tiles, a.count[b0 + b]);
     ct += tb;
     cu += (tb + U - 1) / U;
   }
@@ -209,7 +212,7 @@ __global__ void __launch_bounds__(256) tilescan_kernel(MfmaArgs a) {
   __syncthreads();
   uint32_t rt = pt[threadIdx.x], ru = pu[threadIdx.x];
   for (int b = lo; b < hi; b++) {
-    const uint32_t tb = bin_tiles(a, a.count[b0 + b]);
+    const uint32_t tb = bin_tiles(a.unit_tiles, a.count[b0 + b]);
     a.bin_tile[b0 + b] = rt;
     a.bin_unit[b0 + b] = ru;
     rt += tb;
@@ -218,7 +221,8 @@ __global__ void __launch_bounds__(256) tilescan_kernel(MfmaArgs a) {
 }
 
 // prefix of tiles over items (one thread); reset of the per-class counters
-__global__ void item_scan_kernel(MfmaArgs a) {
+template <typename R>
+__global__ void item_scan_kernel(MfmaArgsT<R> a) {
   if (threadIdx.x == 0) {
     uint32_t r = 0;
     a.item_tiles[0] = 0;
@@ -246,7 +250,8 @@ __global__ void item_scan_kernel(MfmaArgs a) {
 }
 
 // ---- 3. scatter: one record per sample at its (padded) sorted slot ------------
-__global__ void __launch_bounds__(kSortThreads) scatter_kernel(MfmaArgs a) {
+template <typename R>
+__global__ void __launch_bounds__(kSortThreads) scatter_kernel(MfmaArgsT<R> a) {
   extern __shared__ uint32_t cur_l[];
   const int it = block_item(a.items, blockIdx.x);
   const int lb = blockIdx.x - a.items.blk0[it];
@@ -272,7 +277,7 @@ __global__ void __launch_bounds__(kSortThreads) scatter_kernel(MfmaArgs a) {
     const int64_t col = a.items.off[it] + j;
     key[u] = a.key[f];
 #pragma unroll
-    for (int d = 0; d < 7; d++) rec[u].th[d] = a.theta[d * a.stride + col];
+    for (int d = 0; d < 7; d++) rec[u].th[d] = sizeof(R) == 4 ? (float)a.theta[d * a.stride + col] : 0.f;
     rec[u].col = (int)col;
     const uint2 nw = *(const uint2 *)(a.nsh + f * 4);
     rec[u].n[0] = (int16_t)(nw.x & 0xffffu);
@@ -296,7 +301,8 @@ __global__ void __launch_bounds__(kSortThreads) scatter_kernel(MfmaArgs a) {
 // most of a call's samples (a proposal concentrated on a source) costs no more
 // than the same number of tiles in many bins: one thread per bin took 877 us
 // for 1e6 samples with half of them in a few bins, this form 6 us.
-__global__ void __launch_bounds__(64) tile_kernel(MfmaArgs a) {
+template <typename R>
+__global__ void __launch_bounds__(64) tile_kernel(MfmaArgsT<R> a) {
   const uint32_t t = blockIdx.x * 64u + threadIdx.x;
   if (t >= a.ctl[0]) return;
   int lo = 0, hi = a.items.n_items;  // item_tiles[lo] <= t < item_tiles[hi]
@@ -314,7 +320,7 @@ __global__ void __launch_bounds__(64) tile_kernel(MfmaArgs a) {
     const int mid = (lo + hi) >> 1;
     if (a.bin_tile[mid] <= x) lo = mid; else hi = mid;
   }
-  const uint32_t cnt = a.count[lo], c = x - a.bin_tile[lo], tb = bin_tiles(a, cnt);
+  const uint32_t cnt = a.count[lo], c = x - a.bin_tile[lo], tb = bin_tiles(a.unit_tiles, cnt);
   const uint32_t U = (uint32_t)a.unit_tiles;
   a.tile_key[t] = c < tb ? (uint32_t)(lo - b0) : kNoBin;
   if (c < tb && c % U == 0u) {
@@ -353,8 +359,8 @@ __global__ void __launch_bounds__(64) tile_kernel(MfmaArgs a) {
 // classes of their own: a second unrolled pass would keep every mode product
 // of the first alive).  Padding and invalid slots run the same code on a
 // harmless angle set and store zeros.
-template <int MC>
-__global__ void __launch_bounds__(64) coef_kernel(MfmaArgs a, int item_lo, int item_hi) {
+template <int MC, typename R>
+__global__ void __launch_bounds__(64) coef_kernel(MfmaArgsT<R> a, int item_lo, int item_hi) {
   constexpr int YS = MC > 0 ? 1 : 64;
   constexpr int YM = MC > 0 ? 1 : kMaxModes;
   constexpr int YR = MC > 0 ? MC : 1;
@@ -371,15 +377,19 @@ __global__ void __launch_bounds__(64) coef_kernel(MfmaArgs a, int item_lo, int i
   const RIFT_CONST PointDev &p = *cp(a.pts + pt);
   const int K = p.K, E = 2 * p.Mp;
   const int M = MC > 0 ? MC : p.M;
-  RIFT_GLOBAL float *op = gpw(a.cop + a.item_cop[it] + (int64_t)(t - a.item_tiles[it]) * K * E * kTS + s);
-  RIFT_GLOBAL CoefTile *ct = gpw(a.ctile + t);
+  RIFT_GLOBAL R *op = gpw(a.cop + a.item_cop[it] + (int64_t)(t - a.item_tiles[it]) * K * E * kTS + s);
+  RIFT_GLOBAL CoefTileT<R> *ct = gpw(a.ctile + t);
   const bool pad = rec.flag == 0;
   const bool valid = rec.flag == 1;
   double th[7];
 #pragma unroll
-  for (int d = 0; d < 7; d++) th[d] = valid ? (double)rec.th[d] : (d == RIFT_DIST ? 1.0 : 0.0);
+  for (int d = 0; d < 7; d++) {
+    const double v = sizeof(R) == 4 ? (double)rec.th[d] : (double)a.theta[d * a.stride + (valid ? rec.col : 0)];
+    th[d] = valid ? v : (d == RIFT_DIST ? 1.0 : 0.0);
+  }
   const double x = a.dmarg ? 1.0 : p.d_ref / th[RIFT_DIST];  // distance marginalization: the terms at D_ref
-  const double xl = valid ? x * kLog2e : 0.0;
+  constexpr double kUnit = sizeof(R) == 4 ? kLog2e : 1.0;  // FP32: base-2 units for the window's exp2 / log2
+  const double xl = valid ? x * kUnit : 0.0;
   SkyTrig tr = sky_trig(th[RIFT_ALPHA], th[RIFT_DELTA], th[RIFT_PSI], p.gmst);
   double Fr[kMaxDet], Fi[kMaxDet];
 #pragma unroll
@@ -394,15 +404,14 @@ __global__ void __launch_bounds__(64) coef_kernel(MfmaArgs a, int item_lo, int i
       antenna(D, tr, Fr[k], Fi[k]);
       const int n = (int)rec.n[k];
       const double sk = (th[RIFT_TAU] + delay(rc, tr)) * p.f_s;
-      ct->mu[k][s] = valid ? (float)(sk - (double)n) : 0.f;
+      ct->mu[k][s] = valid ? (R)(sk - (double)n) : R(0);
       ct->n[k][s] = valid ? n : 1 << 28;
     } else {
-      ct->mu[k][s] = 0.f;
+      ct->mu[k][s] = R(0);
       ct->n[k][s] = 1 << 28;
     }
-    // in base-2 units (times log2 e) for the evaluation kernel's exp2/log2
-    ct->xf[k][0][s] = (float)(xl * Fr[k]);
-    ct->xf[k][1][s] = (float)(xl * Fi[k]);
+    ct->xf[k][0][s] = (R)(xl * Fr[k]);
+    ct->xf[k][1][s] = (R)(xl * Fi[k]);
   }
   // harmonics: Y_m = (sin(iota)/2)^par P_m(cos^2(iota/2)) exp(i m phi), with
   // exp(i m phi) by repeated products of exp(i phi)
@@ -416,7 +425,15 @@ __global__ void __launch_bounds__(64) coef_kernel(MfmaArgs a, int item_lo, int i
   for (int m = 0; m < (MC > 0 ? MC : kMaxModes); m++) {
     if (m >= M) break;
     double yr, yi;
-    harmonic_ym(p, m, u, hs, c1, s1, yr, yi);
+    if constexpr (sizeof(R) == 4) {
+      harmonic_ym(p, m, u, hs, c1, s1, yr, yi);
+    } else {
+      // the Wigner sum itself: the polynomial's cancellation costs a digit
+      // (4e-15 of ln L_t at l <= 4 against 4e-16), which only FP64 shows
+      double cm, sm;
+      phase_m(p.em[m], c1, s1, cm, sm);
+      harmonic(p, m, ci, si, cm, sm, yr, yi);
+    }
     if constexpr (MC > 0) {
       Yr[m] = yr;
       Yi[m] = yi;
@@ -426,10 +443,10 @@ __global__ void __launch_bounds__(64) coef_kernel(MfmaArgs a, int item_lo, int i
     }
     // elements 2m, 2m + 1 of the tile's harmonic block; the evaluation
     // kernels form a_km = (x F_k) Y_m from it and xf
-    op[(2 * m) * kTS] = valid ? (float)yr : 0.f;
-    op[(2 * m + 1) * kTS] = valid ? (float)yi : 0.f;
+    op[(2 * m) * kTS] = valid ? (R)yr : R(0);
+    op[(2 * m + 1) * kTS] = valid ? (R)yi : R(0);
   }
-  for (int e = 2 * M; e < E; e++) op[e * kTS] = 0.f;
+  for (int e = 2 * M; e < E; e++) op[e * kTS] = R(0);
   double q[kMaxDet] = {0.0, 0.0, 0.0}, vr[kMaxDet] = {0.0, 0.0, 0.0}, vi[kMaxDet] = {0.0, 0.0, 0.0};
   // conj(Y_m) Y_m' against U, Y_m Y_m' against V
   auto upair = [&](const auto *T, int idx, double ymr, double ymi, double ypr, double ypi) {
@@ -475,33 +492,38 @@ __global__ void __launch_bounds__(64) coef_kernel(MfmaArgs a, int item_lo, int i
     const double F2r = Fr[k] * Fr[k] - Fi[k] * Fi[k], F2i = 2.0 * Fr[k] * Fi[k];
     b += f2 * q[k] + (F2r * vr[k] - F2i * vi[k]);
   }
-  ct->B[s] = valid ? (float)(0.25 * x * x * b * kLog2e) : 0.f;
+  ct->B[s] = valid ? (R)(0.25 * x * x * b * kUnit) : R(0);
   ct->col[s] = pad ? -1 : (int)rec.col;
   ct->flag[s] = valid ? 1 : (pad ? 0 : 2);
 }
 
-hipError_t mfma_prepare(const MfmaArgs &a, const int *mclass_M, const int *mclass_item0, const int64_t *mclass_tiles,
-                        int n_mclasses, hipStream_t st) {
+template <typename R>
+hipError_t mfma_prepare(const MfmaArgsT<R> &a, const int *mclass_M, const int *mclass_item0,
+                        const int64_t *mclass_tiles, int n_mclasses, hipStream_t st) {
   const size_t lds = sizeof(uint32_t) * (size_t)std::min(a.max_item_bins, kLdsBins);
-  hipLaunchKernelGGL(bin_kernel, dim3(a.n_sort_blocks), dim3(kSortThreads), lds, st, a);
-  hipLaunchKernelGGL(colscan_kernel, dim3((unsigned)((a.max_item_bins + kScanBins - 1) / kScanBins), std::min(a.items.n_items, 65535)),
+  hipLaunchKernelGGL(bin_kernel<R>, dim3(a.n_sort_blocks), dim3(kSortThreads), lds, st, a);
+  hipLaunchKernelGGL(colscan_kernel<R>, dim3((unsigned)((a.max_item_bins + kScanBins - 1) / kScanBins), std::min(a.items.n_items, 65535)),
                      dim3(kScanRanges * kScanBins), 0, st, a);
-  hipLaunchKernelGGL(tilescan_kernel, dim3(a.items.n_items), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(item_scan_kernel, dim3(1), dim3(64), 0, st, a);
-  hipLaunchKernelGGL(scatter_kernel, dim3(a.n_sort_blocks), dim3(kSortThreads), lds, st, a);
-  hipLaunchKernelGGL(tile_kernel, dim3((unsigned)((a.max_tiles + 63) / 64)), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(tilescan_kernel<R>, dim3(a.items.n_items), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(item_scan_kernel<R>, dim3(1), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(scatter_kernel<R>, dim3(a.n_sort_blocks), dim3(kSortThreads), lds, st, a);
+  hipLaunchKernelGGL(tile_kernel<R>, dim3((unsigned)((a.max_tiles + 63) / 64)), dim3(64), 0, st, a);
   for (int c = 0; c < n_mclasses; c++) {
     const int lo = mclass_item0[c], hi = mclass_item0[c + 1];
     const dim3 grid((unsigned)(((int64_t)kTS * mclass_tiles[c] + 63) / 64));
     switch (mclass_M[c]) {  // negative: points with a V table, general form
-      case 2: hipLaunchKernelGGL(coef_kernel<2>, grid, dim3(64), 0, st, a, lo, hi); break;
-      case 5: hipLaunchKernelGGL(coef_kernel<5>, grid, dim3(64), 0, st, a, lo, hi); break;
-      case 9: hipLaunchKernelGGL(coef_kernel<9>, grid, dim3(64), 0, st, a, lo, hi); break;
-      case 21: hipLaunchKernelGGL(coef_kernel<21>, grid, dim3(64), 0, st, a, lo, hi); break;
-      default: hipLaunchKernelGGL(coef_kernel<0>, grid, dim3(64), 0, st, a, lo, hi); break;
+      case 2: hipLaunchKernelGGL((coef_kernel<2, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      case 5: hipLaunchKernelGGL((coef_kernel<5, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      case 9: hipLaunchKernelGGL((coef_kernel<9, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      case 21: hipLaunchKernelGGL((coef_kernel<21, R>), grid, dim3(64), 0, st, a, lo, hi); break;
+      default: hipLaunchKernelGGL((coef_kernel<0, R>), grid, dim3(64), 0, st, a, lo, hi); break;
     }
   }
   return hipGetLastError();
 }
+template hipError_t mfma_prepare<float>(const MfmaArgsT<float> &, const int *, const int *, const int64_t *, int,
+                                        hipStream_t);
+template hipError_t mfma_prepare<double>(const MfmaArgsT<double> &, const int *, const int *, const int64_t *, int,
+                                         hipStream_t);
 
 }  // namespace rift

@@ -92,6 +92,18 @@ __device__ __forceinline__ void b_operands(const RIFT_GLOBAL float *yop, const R
   }
 }
 
+// exp(i em phi) by repeated products of exp(i phi) = (c1, s1)
+__device__ __forceinline__ void phase_m(int em, double c1, double s1, double &cm, double &sm) {
+  cm = 1.0;
+  sm = 0.0;
+  for (int q = em < 0 ? -em : em; q > 0; q--) {
+    const double nr = cm * c1 - sm * s1;
+    sm = cm * s1 + sm * c1;
+    cm = nr;
+  }
+  if (em < 0) sm = -sm;
+}
+
 // Harmonic Y_m = (sin(iota)/2)^par P_m(cos^2(iota/2)) exp(i m phi) of one
 // mode from the point's polynomial table (Horner in u = cos^2(iota/2), FP64),
 // with exp(i m phi) by repeated products of exp(i phi) = (c1, s1) and

@@ -441,21 +441,27 @@ rift_status check_items(rift_ile *h, int n_items, const rift_ile_item *items, in
   return RIFT_OK;
 }
 
-template <typename R>
-rift_status run_plain(rift_ile *h, const Items &it, int64_t stride, const R *theta, R *lnL, R *lnw,
-                      const R *ln_ratio, const R *gin, R *grad, bool bwd) {
-  const int n = (int)it.point.size();
-  // samples per workgroup (4, 8 or 16: each sample's window reductions take
-  // 256 / TS lanes of one wavefront): the most that still let two workgroups
-  // share a compute unit's LDS, else the most that fit at all
-  auto lds = [&](int ts) { return plain_lds_bytes(sizeof(R), ts, h->max_L, h->max_nt, bwd); };
+// Samples per workgroup of the plain kernel (4, 8 or 16: each sample's window
+// reductions take 256 / TS lanes of one wavefront): the most that still let
+// two workgroups share a compute unit's LDS, else the most that fit at all; 0
+// where not even 4 samples' windows fit.
+int plain_samples(const rift_ile *h, int elem, bool bwd) {
+  auto lds = [&](int ts) { return plain_lds_bytes(elem, ts, h->max_L, h->max_nt, bwd); };
   int TS = 16;
   while (TS > 4 && lds(TS) > (size_t)h->lds_max / 2) TS >>= 1;
   if (lds(TS) > (size_t)h->lds_max / 2) {
     TS = 16;
     while (TS > 4 && lds(TS) > (size_t)h->lds_max) TS >>= 1;
   }
-  if (lds(TS) > (size_t)h->lds_max) return fail(h, RIFT_E_SHAPE, "window too long for the plain kernel's LDS");
+  return lds(TS) > (size_t)h->lds_max ? 0 : TS;
+}
+
+template <typename R>
+rift_status run_plain(rift_ile *h, const Items &it, int64_t stride, const R *theta, R *lnL, R *lnw,
+                      const R *ln_ratio, const R *gin, R *grad, bool bwd) {
+  const int n = (int)it.point.size();
+  const int TS = plain_samples(h, sizeof(R), bwd);
+  if (TS == 0) return fail(h, RIFT_E_SHAPE, "window too long for the plain kernel's LDS");
   std::vector<int> tile0(n + 1, 0);
   for (int i = 0; i < n; i++) tile0[i + 1] = tile0[i] + (int)((it.cnt[i] + TS - 1) / TS);
   if (tile0[n] == 0) return RIFT_OK;
@@ -569,8 +575,9 @@ rift_status launch_graph(rift_ile *h, const MfmaArgs &a, const std::vector<int> 
 
 // One group of points (already in evaluation order) through the sort, the
 // coefficient pass and the persistent MFMA launches.
-rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const float *theta, float *lnL, float *lnw,
-                           const float *ln_ratio, const float *gin = nullptr, float *grad = nullptr) {
+template <typename R>
+rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R *theta, R *lnL, R *lnw,
+                           const R *ln_ratio, const R *gin, R *grad) {
   std::vector<int64_t> samp0(1, 0), mclass_tiles, hoff;
   std::vector<int> bin0(1, 0), blk0(1, 0), class_T, class_K, class_item0, mclass_M, mclass_item0;
   int64_t hist_total = 0, cop_floats = 0;
@@ -613,7 +620,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
   if (total == 0) return RIFT_OK;
   if (total >= (int64_t)1 << 31 || max_tiles >= (int64_t)1 << 26)
     return fail(h, RIFT_E_SHAPE, "more than 2^31 samples in one call");
-  MfmaArgs a;
+  MfmaArgsT<R> a;
   std::memset(&a, 0, sizeof(a));
   rift_status s;
   int *d_point, *d_bin0, *d_blk0;
@@ -645,7 +652,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
   a.ln_ratio = ln_ratio;
   a.n_bins = bin0.back();
   a.max_tiles = (int)max_tiles;
-  a.unit_tiles = grad ? 4 : 8;
+  a.unit_tiles = grad || sizeof(R) == 8 ? 4 : 8;
   void *p;
   if ((s = ws_get(h, W_KEY, 4 * total, &p)) != RIFT_OK) return s;
   a.key = (uint32_t *)p;
@@ -664,14 +671,14 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
   if ((s = ws_get(h, W_TILES, 8 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
   a.tile_item = (int *)p;
   a.tile_key = (uint32_t *)p + max_tiles;
-  if ((s = ws_get(h, W_COP, sizeof(float) * (size_t)cop_floats, &p)) != RIFT_OK) return s;
-  a.cop = (float *)p;
+  if ((s = ws_get(h, W_COP, sizeof(R) * (size_t)cop_floats, &p)) != RIFT_OK) return s;
+  a.cop = (R *)p;
   if (grad) {  // the adjoint's per-tile G_k (cop layout) and H_k
-    if ((s = ws_get(h, W_GOP, sizeof(float) * (size_t)cop_floats, &p)) != RIFT_OK) return s;
-    a.gop = (float *)p;
-    if ((s = ws_get(h, W_HOP, sizeof(float) * kMaxDet * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-    a.hop = (float *)p;
-    if (h->refine) {
+    if ((s = ws_get(h, W_GOP, sizeof(R) * (size_t)cop_floats, &p)) != RIFT_OK) return s;
+    a.gop = (R *)p;
+    if ((s = ws_get(h, W_HOP, sizeof(R) * kMaxDet * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
+    a.hop = (R *)p;
+    if (h->refine && sizeof(R) == 4) {
       if ((s = ws_get(h, W_JRNG, 4 * sizeof(int) * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
       a.jrng = (int *)p;
     }
@@ -687,8 +694,8 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
   }
   if ((s = ws_get(h, W_ITEM_COP, sizeof(int64_t) * (size_t)ni, &p)) != RIFT_OK) return s;
   a.item_cop = (int64_t *)p;
-  if ((s = ws_get(h, W_CTILE, sizeof(CoefTile) * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-  a.ctile = (CoefTile *)p;
+  if ((s = ws_get(h, W_CTILE, sizeof(CoefTileT<R>) * (size_t)max_tiles, &p)) != RIFT_OK) return s;
+  a.ctile = (CoefTileT<R> *)p;
   if ((s = ws_get(h, W_UNIT, sizeof(WorkUnit) * (size_t)max_tiles, &p)) != RIFT_OK) return s;
   a.unit = (WorkUnit *)p;
   if ((s = ws_get(h, W_BINUNIT, 4 * (size_t)a.n_bins, &p)) != RIFT_OK) return s;
@@ -704,56 +711,61 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
     HIPCHK(h, hipEventCreate(&e1));
     h->prof_ev.emplace_back(e0, e1);
   }
-  // launch configuration of each class (measured on first use when autotuning)
-  std::vector<int> class_mode(class_T.size()), class_ntb(class_T.size(), 0);
-  for (size_t c = 0; c < class_T.size(); c++) {
-    int nt = 1;
-    for (int i = class_item0[c]; i < class_item0[c + 1]; i++) nt = std::max(nt, h->hp[it.point[i]].n_t);
-    int b = 0;
-    while (b + 1 < kNtBuckets && (nt >> (b + 1)) > 0) b++;
-    class_ntb[c] = b;
-  }
-  bool measured = true;
-  for (size_t c = 0; c < class_T.size(); c++) {
-    // feed 0: staged, 1: measured, 2: direct, 3 and 4: direct with registers
-    // capped for three or four wavefronts per SIMD (configurations 5, 6),
-    // 5: staged capped for three (configuration 7)
-    class_mode[c] = h->feed == 1 ? h->tune[class_T[c]][class_K[c]][class_ntb[c]]
-                    : h->feed == 0 ? 1
-                    : h->feed == 2 ? 2
-                                   : h->feed + 2;
-    measured = measured && class_mode[c] != 0;
-  }
-  if (!grad && h->use_graph && !h->prof && measured) {
-    for (size_t c = 0; c < class_T.size(); c++) h->kmode[class_T[c]][class_K[c]] = class_mode[c];
-    return launch_graph(h, a, class_T, class_K, class_item0, mclass_M, mclass_item0, mclass_tiles, class_mode);
-  }
-  if (grad)
-    HIPCHK(h, mfma_backward(a, class_T.data(), class_K.data(), class_item0.data(), (int)class_T.size(),
-                            mclass_M.data(), mclass_item0.data(), mclass_tiles.data(), (int)mclass_M.size(), h->stream,
-                            h->fan, e0, e1));
-  else {
-    HIPCHK(h, mfma_forward(a, class_T.data(), class_K.data(), class_item0.data(), (int)class_T.size(),
-                           mclass_M.data(), mclass_item0.data(), mclass_tiles.data(), (int)mclass_M.size(),
-                           class_mode.data(), h->feed == 1, h->stream, h->fan, e0, e1));
-    std::string lines;
+  if constexpr (sizeof(R) == 8) {
+    HIPCHK(h, mfma64_run(a, class_T.data(), class_K.data(), class_item0.data(), (int)class_T.size(), mclass_M.data(),
+                         mclass_item0.data(), mclass_tiles.data(), (int)mclass_M.size(), h->stream, e0, e1));
+  } else {
+    // launch configuration of each class (measured on first use when autotuning)
+    std::vector<int> class_mode(class_T.size()), class_ntb(class_T.size(), 0);
     for (size_t c = 0; c < class_T.size(); c++) {
-      if (class_mode[c] == 0) continue;  // distance marginalization: the fixed passes
-      h->kmode[class_T[c]][class_K[c]] = class_mode[c];
-      int &slot = h->tune[class_T[c]][class_K[c]][class_ntb[c]];
-      if (h->feed == 1 && slot == 0) {
-        slot = class_mode[c];
-        char ln[96];
-        std::snprintf(ln, sizeof ln, "%s %d %d %d %d\n", h->arch.c_str(), class_T[c], class_K[c], class_ntb[c],
-                      class_mode[c]);
-        lines += ln;
-      }
+      int nt = 1;
+      for (int i = class_item0[c]; i < class_item0[c + 1]; i++) nt = std::max(nt, h->hp[it.point[i]].n_t);
+      int b = 0;
+      while (b + 1 < kNtBuckets && (nt >> (b + 1)) > 0) b++;
+      class_ntb[c] = b;
     }
-    if (!lines.empty() && !h->tune_path.empty()) {
-      // appended in one write; a cache that cannot be written is skipped
-      if (FILE *f = std::fopen(h->tune_path.c_str(), "a")) {
-        (void)std::fwrite(lines.data(), 1, lines.size(), f);
-        std::fclose(f);
+    bool measured = true;
+    for (size_t c = 0; c < class_T.size(); c++) {
+      // feed 0: staged, 1: measured, 2: direct, 3 and 4: direct with registers
+      // capped for three or four wavefronts per SIMD (configurations 5, 6),
+      // 5: staged capped for three (configuration 7)
+      class_mode[c] = h->feed == 1 ? h->tune[class_T[c]][class_K[c]][class_ntb[c]]
+                      : h->feed == 0 ? 1
+                      : h->feed == 2 ? 2
+                                     : h->feed + 2;
+      measured = measured && class_mode[c] != 0;
+    }
+    if (!grad && h->use_graph && !h->prof && measured) {
+      for (size_t c = 0; c < class_T.size(); c++) h->kmode[class_T[c]][class_K[c]] = class_mode[c];
+      return launch_graph(h, a, class_T, class_K, class_item0, mclass_M, mclass_item0, mclass_tiles, class_mode);
+    }
+    if (grad)
+      HIPCHK(h, mfma_backward(a, class_T.data(), class_K.data(), class_item0.data(), (int)class_T.size(),
+                              mclass_M.data(), mclass_item0.data(), mclass_tiles.data(), (int)mclass_M.size(), h->stream,
+                              h->fan, e0, e1));
+    else {
+      HIPCHK(h, mfma_forward(a, class_T.data(), class_K.data(), class_item0.data(), (int)class_T.size(),
+                             mclass_M.data(), mclass_item0.data(), mclass_tiles.data(), (int)mclass_M.size(),
+                             class_mode.data(), h->feed == 1, h->stream, h->fan, e0, e1));
+      std::string lines;
+      for (size_t c = 0; c < class_T.size(); c++) {
+        if (class_mode[c] == 0) continue;  // distance marginalization: the fixed passes
+        h->kmode[class_T[c]][class_K[c]] = class_mode[c];
+        int &slot = h->tune[class_T[c]][class_K[c]][class_ntb[c]];
+        if (h->feed == 1 && slot == 0) {
+          slot = class_mode[c];
+          char ln[96];
+          std::snprintf(ln, sizeof ln, "%s %d %d %d %d\n", h->arch.c_str(), class_T[c], class_K[c], class_ntb[c],
+                        class_mode[c]);
+          lines += ln;
+        }
+      }
+      if (!lines.empty() && !h->tune_path.empty()) {
+        // appended in one write; a cache that cannot be written is skipped
+        if (FILE *f = std::fopen(h->tune_path.c_str(), "a")) {
+          (void)std::fwrite(lines.data(), 1, lines.size(), f);
+          std::fclose(f);
+        }
       }
     }
   }
@@ -763,8 +775,9 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const f
 // Points grouped by MFMA step count T (one persistent launch per group),
 // then mode count, costliest first: the kernels take tiles in this order.
 // The points are evaluated in runs whose workspace stays under a budget.
-rift_status run_mfma(rift_ile *h, const Items &it_in, int64_t stride, const float *theta, float *lnL, float *lnw,
-                     const float *ln_ratio, const float *gin = nullptr, float *grad = nullptr) {
+template <typename R>
+rift_status run_mfma(rift_ile *h, const Items &it_in, int64_t stride, const R *theta, R *lnL, R *lnw,
+                     const R *ln_ratio, const R *gin = nullptr, R *grad = nullptr) {
   const int n = (int)it_in.point.size();
   std::vector<int> order(n);
   std::iota(order.begin(), order.end(), 0);
@@ -789,12 +802,12 @@ rift_status run_mfma(rift_ile *h, const Items &it_in, int64_t stride, const floa
     const PointDev &p = h->hp[it_in.point[oi]];
     int64_t remaining = it_in.cnt[oi], off = it_in.off[oi];
     while (remaining > 0) {
-      const double per = 4.0 + 8.0 + 44.0 + 40.0 + (double)p.K * 2 * p.Mp * 4 * 1.1 * (grad ? 2.0 : 1.0) +
-                         (h->dmarg ? 4.4 : 0.0);
+      const double per = 4.0 + 8.0 + 44.0 + 10.0 * sizeof(R) +
+                         (double)p.K * 2 * p.Mp * sizeof(R) * 1.1 * (grad ? 2.0 : 1.0) + (h->dmarg ? 4.4 : 0.0);
       int64_t take = remaining;
       if (used + per * take > budget) {
         if (!grp.point.empty()) {
-          rift_status s = run_mfma_group(h, grp, stride, theta, lnL, lnw, ln_ratio, gin, grad);
+          rift_status s = run_mfma_group<R>(h, grp, stride, theta, lnL, lnw, ln_ratio, gin, grad);
           if (s != RIFT_OK) return s;
           grp = Items();
           used = 0.0;
@@ -809,7 +822,7 @@ rift_status run_mfma(rift_ile *h, const Items &it_in, int64_t stride, const floa
       remaining -= take;
     }
   }
-  if (!grp.point.empty()) return run_mfma_group(h, grp, stride, theta, lnL, lnw, ln_ratio, gin, grad);
+  if (!grp.point.empty()) return run_mfma_group<R>(h, grp, stride, theta, lnL, lnw, ln_ratio, gin, grad);
   return RIFT_OK;
 }
 
@@ -823,20 +836,44 @@ Items make_items(int n_items, const rift_ile_item *items) {
   return it;
 }
 
+// FP64 calls that go to the sorted matrix-core form: at least sort_work units
+// of K n_t (M + 4) per sample.  Below, the sort's launches cost more than the
+// plain kernel's one: 10007 samples at K = 2, M = 2, n_t = 410 (4.9e7) take 73
+// us there and 85 us sorted, 20000 at K = 3, M = 9 (3.2e8) 2583 and 314 us with
+// the gradient, 2e5 at K = 3, M = 21, n_t = 820 (1.2e10) 10.2 and 1.2 ms.  What the plain form refuses stays
+// refused; what it takes and the sorted form does not (more than 2^31 columns,
+// the bins of a very large pad) stays with it, and so does distance
+// marginalization.
+bool use_sorted64(const rift_ile *h, const Items &it, int64_t stride, bool bwd) {
+  if (h->dmarg && !bwd) return false;
+  if (stride > (int64_t)INT32_MAX || plain_samples(h, 8, bwd) == 0) return false;
+  const double sort_work = bwd ? 1.2e7 : 6.0e7;
+  double work = 0.0;
+  for (size_t i = 0; i < it.point.size(); i++) {
+    const PointDev &p = h->hp[it.point[i]];
+    if (p.n_bins_key > (1 << 16)) return false;
+    work += (double)it.cnt[i] * p.K * p.n_t * (p.M + 4);
+  }
+  return work >= sort_work;
+}
+
 template <typename R>
 rift_status eval(rift_ile *h, const Items &it, int64_t stride, const R *theta, R *lnL, R *lnw, const R *ln_ratio) {
-  if (sizeof(R) == 4 && !(h->flags & 1u))
-    return run_mfma(h, it, stride, (const float *)theta, (float *)lnL, (float *)lnw, (const float *)ln_ratio);
+  if (sizeof(R) == 4 ? !(h->flags & 1u) : use_sorted64(h, it, stride, false)) {
+    const rift_status s = run_mfma<R>(h, it, stride, theta, lnL, lnw, ln_ratio);
+    if (sizeof(R) == 4 || s != RIFT_E_OOM) return s;  // FP64: the plain form needs no workspace
+  }
   return run_plain<R>(h, it, stride, theta, lnL, lnw, ln_ratio, nullptr, nullptr, false);
 }
 
-// ln L_t and its gradient (times gin): the matrix-core adjoint for FP32
-// handles, the plain adjoint otherwise
+// ln L_t and its gradient (times gin): the matrix-core adjoint, or the plain
+// one (FP32 on request, small FP64 calls)
 template <typename R>
 rift_status eval_grad(rift_ile *h, const Items &it, int64_t stride, const R *theta, R *lnL, const R *gin, R *grad) {
-  if (sizeof(R) == 4 && !(h->flags & 1u))
-    return run_mfma(h, it, stride, (const float *)theta, (float *)lnL, nullptr, nullptr, (const float *)gin,
-                    (float *)grad);
+  if (sizeof(R) == 4 ? !(h->flags & 1u) : use_sorted64(h, it, stride, true)) {
+    const rift_status s = run_mfma<R>(h, it, stride, theta, lnL, nullptr, nullptr, gin, grad);
+    if (sizeof(R) == 4 || s != RIFT_E_OOM) return s;
+  }
   return run_plain<R>(h, it, stride, theta, lnL, nullptr, nullptr, gin, grad, true);
 }
 

@@ -877,6 +877,75 @@ def test_short_window_far_below_zero(ile, orc, n_t):
             assert np.all(np.abs(out - ref) <= 1e-9 * (1 + np.abs(ref)))
 
 
+@pytest.mark.parametrize("M,K,n_t,n", [
+    (1, 1, 1, 20000), (1, 2, 17, 9000), (2, 3, 16, 6000), (3, 1, 33, 9000), (4, 2, 31, 4000), (5, 3, 15, 7000),
+    (8, 1, 64, 4000), (9, 2, 65, 2500), (12, 3, 47, 2500), (16, 1, 100, 2000), (21, 3, 48, 2500), (24, 2, 80, 1500),
+    (31, 1, 96, 1500), (32, 3, 33, 1500)])
+def test_fp64_matrix_core_shapes(ile, orc, M, K, n_t, n):
+    """The sorted FP64 form (calls above its size rule: two points in one call,
+    each large enough) at odd and even operand counts, detector counts and the
+    edges of the 16-row blocks, against the oracle on part of the columns, and
+    all columns against calls small enough for the plain form; ln L_t and
+    gradient, with an upstream factor, shuffled columns and invalid samples."""
+    rng = np.random.default_rng([93, M, K, n_t])
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1600 + M, dets=("H1", "L1", "V1")[:K], n_modes=2, n_t=n_t, snr=1.0,
+                           kernel="none")
+    lm = [(l, m) for l in range(2, 9) for m in range(-l, l + 1)]
+    pts = []
+    for q in range(2):
+        d = dict(synth.make_point(spec))
+        pick = rng.choice(len(lm), M, replace=False)
+        d["ell"] = np.array([lm[i][0] for i in pick], dtype=np.int32)
+        d["em"] = np.array([lm[i][1] for i in pick], dtype=np.int32)
+        L = d["Q"].shape[1]
+        G = rng.standard_normal((K, M, M + 2)) + 1j * rng.standard_normal((K, M, M + 2))
+        d["U"] = 100.0 * G @ G.conj().transpose(0, 2, 1) / (M + 2)
+        d["Q"] = 30.0 * (rng.standard_normal((K, L, M)) + 1j * rng.standard_normal((K, L, M)))
+        pts.append(d)
+    n = max(n, int(2.2e7 / (K * n_t * (M + 4))))  # two points: above the forward's 4e7 in all
+    th = np.concatenate([synth.mixed_samples(pts[0], 35, n), synth.mixed_samples(pts[1], 36, n)], axis=1)
+    th[:, 5] = np.nan
+    th[5, n + 7] = np.inf
+    items = [(1, n, n), (0, 0, n)]
+    gin = torch.tensor(rng.standard_normal(2 * n))
+    h = _handle(ile, pts, "fp64")
+    _say(f"fp64 M={M} K={K} n_t={n_t} n={n}")
+    out = h.lnL(torch.tensor(th), items).cpu().numpy()
+    g, lg = h.backward(torch.tensor(th), gin, items, want_lnL=True)
+    g, lg = g.cpu().numpy(), lg.cpu().numpy()
+    assert np.array_equal(out, h.lnL(torch.tensor(th), items).cpu().numpy(), equal_nan=True)
+    bad = np.zeros(2 * n, dtype=bool)
+    bad[[5, n + 7]] = True
+    assert np.array_equal(np.isnan(out), bad) and np.array_equal(np.isnan(lg), bad)
+    assert np.array_equal(np.isnan(g).any(axis=0), bad)
+    cols = np.concatenate([np.arange(0, 60), n + np.arange(0, 60)])
+    for q, c in ((0, cols[:60]), (1, cols[60:])):
+        c = c[~bad[c]]
+        op = orc.Point.from_dict(pts[q])
+        ref = orc.lnL_t(op, th[:, c])
+        assert np.all(np.abs(out[c] - ref) <= 1e-9 * (1 + np.abs(ref)))
+        assert np.all(np.abs(lg[c] - ref) <= 1e-9 * (1 + np.abs(ref)))
+        _, gr = orc.grad(op, th[:, c])
+        cg = _consistent(g[:, c] / gin.numpy()[c], th[:, c], spec.f_s)
+        cr = _consistent(gr, th[:, c], spec.f_s)
+        assert (np.abs(cg - cr) / (np.abs(cr).max(axis=0) + 1e-3)).max() < 1e-9
+    # the plain form on a small call: ln L_t, and the gradient to the rounding
+    # of its terms, which are up to a few times B and |ln L_t| before they cancel
+    # (1e-12 of those: about 100 products of 2^-53 each, ten times over)
+    step = min(n - n // 3, 1000, max(1, int(0.9e7 / (K * n_t * (M + 4)))))
+    for q in range(2):
+        a, b = q * n + n // 3, q * n + n // 3 + step
+        sub, it = torch.tensor(th[:, a:b]), [(q, 0, b - a)]
+        o = h.lnL(sub, it).cpu().numpy()
+        assert np.allclose(o, out[a:b], rtol=1e-11, atol=1e-9, equal_nan=True)
+        gs = h.backward(sub, gin[a:b], it).cpu().numpy()
+        ca, cb = _consistent(gs, th[:, a:b], spec.f_s), _consistent(g[:, a:b], th[:, a:b], spec.f_s)
+        B = _quad(orc.Point.from_dict(pts[q]), th[:, a:b])
+        tol = 1e-9 * np.abs(cb).max(axis=0) + 1e-12 * np.abs(gin.numpy()[a:b]) * (1 + np.abs(o) + 4 * B)
+        assert np.all((np.abs(ca - cb) <= tol)[:, ~bad[a:b]])
+    h.close()
+
+
 def test_plain_long_window(ile, orc):
     """FP64 plain form on a long window (n_t = 1900, H1 + L1, two modes): the
     workgroup then holds the fewest samples it allows (4, each sample's window
