@@ -1320,48 +1320,58 @@ rift_status rift_ile_precompute(const rift_ile_fd_point *in, int64_t row0, int64
                 (long long)n_rows);
   if (!(in->df > 0.0) || !std::isfinite(in->df) || !(in->f_low >= 0.0) || !std::isfinite(in->f_low))
     return fail(nullptr, RIFT_E_INVALID, "precompute: df or f_low invalid");
-  if (!finite_all(in->data, 2 * (size_t)K * N) || !finite_all(in->modes, 2 * (size_t)M * N))
-    return fail(nullptr, RIFT_E_NONFINITE, "precompute: data or modes not finite");
-  for (int64_t i = 0; i < N; i++) {
-    const double f = (double)(i < (N + 1) / 2 ? i : i - N) * in->df;
-    if (std::fabs(f) <= in->f_low) continue;
-    for (int k = 0; k < K; k++) {
-      const double S = in->psd[(size_t)k * N + i];
-      if (!(S > 0.0) || !std::isfinite(S))
-        return fail(nullptr, RIFT_E_NONFINITE, "precompute: psd[%d][%lld] = %g in band", k, (long long)i, S);
-    }
-  }
-  const size_t nd = 2 * (size_t)K * N, np_ = (size_t)K * N, nm = 2 * (size_t)M * N, nx = 2 * (size_t)K * M * N;
-  const size_t nq = 2 * (size_t)K * n_rows * M, nu = 2 * (size_t)K * M * M;
-  std::vector<void *> bufs;
-  auto release = [&]() {
-    for (void *b : bufs) (void)hipFree(b);
+  const size_t nd = 2 * (size_t)K * N, np_ = (size_t)K * N, nm = 2 * (size_t)M * N;
+  const size_t nx = n_rows > 0 ? 2 * (size_t)K * M * N : 0, nq = 2 * (size_t)K * n_rows * M, nu = 2 * (size_t)K * M * M;
+  const size_t ng = 2 * nu * (size_t)quv_part_chunks(N);
+  auto psd_error = [&](uint64_t at) {
+    const int k = (int)(at % (uint64_t)K);
+    const int64_t i = (int64_t)(at / (uint64_t)K);
+    return fail(nullptr, RIFT_E_NONFINITE, "precompute: psd[%d][%lld] = %g in band", k, (long long)i,
+                in->psd[(size_t)k * N + i]);
   };
-  auto alloc = [&](size_t n, double **p) -> bool {
-    void *v = nullptr;
-    if (hipMalloc(&v, sizeof(double) * std::max<size_t>(n, 1)) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
-    bufs.push_back(v);
-    *p = (double *)v;
-    return true;
+  // one allocation for the inputs, the scratch and the outputs (256-byte parts)
+  size_t at = 0;
+  auto part = [&](size_t n) {
+    const size_t p = at;
+    at += (n + 31) & ~(size_t)31;
+    return p;
   };
-  double *dd, *dp, *dm, *dx, *dq, *du, *dv;
-  if (!alloc(nd, &dd) || !alloc(np_, &dp) || !alloc(nm, &dm) || !alloc(nx, &dx) || !alloc(nq, &dq) ||
-      !alloc(nu, &du) || !alloc(nu, &dv)) {
-    release();
+  const size_t od = part(nd), op = part(np_), om = part(nm), ox = part(nx), og = part(ng), oq = part(nq), ou = part(nu),
+               ov = part(nu), ob = part(2);
+  void *mem = nullptr;
+  if (hipMalloc(&mem, sizeof(double) * at) != hipSuccess) {
+    (void)hipGetLastError();
+    // without device memory the inputs are checked here, so that what is wrong
+    // with them is reported first
+    if (!finite_all(in->data, nd) || !finite_all(in->modes, nm))
+      return fail(nullptr, RIFT_E_NONFINITE, "precompute: data or modes not finite");
+    for (int64_t i = 0; i < N; i++)
+      for (int k = 0; k < K && std::fabs((double)(i < (N + 1) / 2 ? i : i - N) * in->df) > in->f_low; k++)
+        if (!(in->psd[(size_t)k * N + i] > 0.0) || !std::isfinite(in->psd[(size_t)k * N + i])) return psd_error(i * K + k);
     return fail(nullptr, RIFT_E_OOM, "precompute: device allocation failed");
   }
-  hipError_t e = hipMemcpy(dd, in->data, sizeof(double) * nd, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(dp, in->psd, sizeof(double) * np_, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(dm, in->modes, sizeof(double) * nm, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = quv_device(K, M, N, in->df, in->f_low, dd, dp, dm, row0, n_rows, dx, dq, du, dv, nullptr);
-  if (e == hipSuccess && n_rows > 0) e = hipMemcpy(Q, dq, sizeof(double) * nq, hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipMemcpy(U, du, sizeof(double) * nu, hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipMemcpy(V, dv, sizeof(double) * nu, hipMemcpyDeviceToHost);
-  release();
+  double *w = (double *)mem;
+  unsigned long long bad[2] = {0ull, ~0ull};
+  hipError_t e = hipMemcpy(w + od, in->data, sizeof(double) * nd, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(w + op, in->psd, sizeof(double) * np_, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(w + om, in->modes, sizeof(double) * nm, hipMemcpyHostToDevice);
+  // the inputs are checked on the device, beside the transform: nothing is
+  // written to the caller's arrays unless they pass
+  if (e == hipSuccess)
+    e = quv_check(K, M, N, in->df, in->f_low, w + od, w + op, w + om, (unsigned long long *)(w + ob), nullptr);
+  if (e == hipSuccess)
+    e = quv_device(K, M, N, in->df, in->f_low, w + od, w + op, w + om, row0, n_rows, w + ox, w + og, w + oq, w + ou,
+                   w + ov, nullptr);
+  if (e == hipSuccess) e = hipMemcpy(bad, w + ob, sizeof bad, hipMemcpyDeviceToHost);
+  if (e == hipSuccess && bad[0] == 0 && bad[1] == ~0ull) {
+    if (n_rows > 0) e = hipMemcpy(Q, w + oq, sizeof(double) * nq, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(U, w + ou, sizeof(double) * nu, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(V, w + ov, sizeof(double) * nu, hipMemcpyDeviceToHost);
+  }
+  (void)hipFree(mem);
   if (e != hipSuccess) return hip_fail(nullptr, e, "precompute");
+  if (bad[0]) return fail(nullptr, RIFT_E_NONFINITE, "precompute: data or modes not finite");
+  if (bad[1] != ~0ull) return psd_error(bad[1]);
   return RIFT_OK;
 }
 

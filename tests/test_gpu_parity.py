@@ -516,6 +516,30 @@ def test_precompute_matches_oracle(ile, orc):
         assert np.abs(Q[k, 0] - U[k] @ c[k]).max() < 1e-10 * np.abs(U[k] @ c[k]).max()
 
 
+@pytest.mark.parametrize("N,K,M,row0,n_rows", [
+    (2, 1, 1, 0, 2), (64, 1, 32, -5, 130), (97, 2, 3, 60, 97), (127, 1, 2, 5, 1), (510, 2, 4, 500, 33), (1000, 3, 9, -1, 63),
+    (4095, 1, 5, 4000, 257), (8192, 2, 2, 8191, 1100), (2057, 1, 21, 3, 40)])
+def test_precompute_pruned_transform(ile, orc, N, K, M, row0, n_rows):
+    """The two-step transform at grids with large and no usable divisors (97
+    and 127 are prime), rows before zero, past the end and more than the grid,
+    the chunk and tile remainders of the Gram sums, against direct sums; the
+    inputs' check, whose order and texts are the host's."""
+    data, psd, modes, f = synth.fd_inputs(60 + N, n_det=K, n_modes=M, N=N, df=0.25, f_low=0.3)
+    _say(f"precompute N={N} K={K} M={M} rows {row0}+{n_rows}")
+    got = ile.precompute(data, psd, modes, 0.25, 0.3, row0, n_rows)
+    for g, r in zip(got, orc.quv(data, psd, modes, 0.25, 0.3, row0, n_rows)):
+        assert np.abs(g - r).max() <= 1e-11 * np.abs(r).max() + 1e-300
+    if N > 90:
+        bad = psd.copy()
+        bad[K - 1, N - 3] = 0.0
+        bad[0, 7] = np.nan
+        with pytest.raises(ile.RiftError, match=r"psd\[0\]\[7\]"):
+            ile.precompute(data, bad, modes, 0.25, 0.3, row0, n_rows)
+        data[0, 9] = np.inf
+        with pytest.raises(ile.RiftError, match="data or modes not finite"):
+            ile.precompute(data, bad, modes, 0.25, 0.3, row0, n_rows)
+
+
 def test_precompute_to_likelihood(ile, orc):
     """From frequency-domain data to ln L: a noise-free signal
     h_k(t) = Re[(D_ref/D) F_k sum_m Y_m h_m(t - t_inj)] in one detector at the
