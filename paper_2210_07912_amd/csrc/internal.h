@@ -16,7 +16,7 @@ struct ItemsDev {
   const int *tile0;     // [n_items + 1] prefix of plain tiles
   const int64_t *samp0; // [n_items + 1] prefix of sample counts (flat index space)
   const int *bin0;      // [n_items + 1] prefix of delay bins
-  const int *blk0;      // [n_items + 1] prefix of sort blocks (kSortBlock samples)
+  const int *blk0;      // [n_items + 1] prefix of sort blocks
   const int64_t *hoff;  // [n_items] offset of the point's block histograms
   int n_items;
 };
@@ -48,10 +48,16 @@ size_t plain_lds_bytes(int elem, int TS, int rows_cap, int nt_cap, bool bwd);
 // ---- FP32 MFMA path -------------------------------------------------------
 constexpr int kMaxT = kMaxModes / 2;  // MFMA steps of 4 elements per detector: M_p / 2
 constexpr int kMaxClasses = 48;  // one persistent launch per distinct (T = Mp / 2, K)
+constexpr int kCtlRefine = 1 + kMaxClasses;  // ctl slot of the refinement count
+constexpr int kCtlScan = 2 + kMaxClasses;    // ctl slot of the points scanned so far
 constexpr int kNtBuckets = 17;   // autotuner key: floor(log2 n_t) of a class's longest window
 constexpr int kFeedConfigs = 7;  // launch configurations the autotuner measures per class
 
-constexpr int kSortBlock = 4096;  // samples per sort block
+// samples per sort block: 4096, or less for a call that would not fill the
+// device with those (64 blocks at 2^18 samples; more, smaller blocks are more
+// rows of the block histogram: at 1e6 samples 1024 take 21 + 32 us in the bin
+// and column passes, 4096 about 30 + 10)
+inline int sort_block_of(int64_t total) { return total <= (1 << 16) ? 256 : total <= (1 << 18) ? 1024 : 4096; }
 constexpr int kLdsBins = 8192;    // delay bins counted in LDS (more: in global memory)
 
 constexpr uint32_t kNoBin = 0xffffffffu;
@@ -118,7 +124,7 @@ struct MfmaArgsT {
   WorkUnit *unit;         // [max_tiles] work units, bins in order, points in order
   uint32_t *bin_unit;     // [n_bins] first unit of the bin within its item
   uint32_t *item_units;   // [n_items + 1] unit prefix over items (filled on device)
-  uint32_t *ctl;          // [0]: number of tiles, [1 + c]: unit counter of class c
+  uint32_t *ctl;          // [0]: number of tiles, [1 + c]: unit counter of class c, then kCtlRefine, kCtlScan
   // adjoint (null in the forward pass)
   const R *gin;           // [stride] upstream d/d ln L_t, or null (= 1)
   R *grad;                // [7][stride] gradient of ln L_t (times gin)
@@ -135,6 +141,8 @@ struct MfmaArgsT {
   int n_bins;
   int max_item_bins;      // largest bin count of one point
   int n_sort_blocks;
+  int sort_block;         // samples per sort block
+  int max_item_blocks;    // most sort blocks of one point
   int max_tiles;
   int unit_tiles;         // tiles of a work unit: 8 (evaluation), 4 (adjoint)
   int grid;               // persistent workgroups
@@ -197,7 +205,6 @@ inline void fan_join(const Fanout &fo, hipStream_t st, int n_classes) {
 // lnL of those samples.  Launched after the
 // chain rule on the same stream.
 constexpr int kRefineBlocks = 3;
-constexpr int kCtlRefine = 1 + kMaxClasses;  // ctl slot of the refinement count
 constexpr float kRefineNats = 40.f;
 hipError_t refine_backward(const MfmaArgs &a, hipStream_t st);
 // the part all share: delay-bin sort, tile records, coefficient pass, work units

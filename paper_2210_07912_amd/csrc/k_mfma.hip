@@ -17,12 +17,13 @@
 //
 // Kernels, in launch order:
 //   bin_kernel    integer delays n_k, bin key, per-sort-block bin counts
-//   colscan       per point: offset of each sort block in each bin
-//   tilescan      per point: tiles and work units before each bin
-//   item_scan     tiles and units before each point; per-class counters reset
-//   scatter       a 40-byte record (theta, column, n_k) at the sorted slot
-//   tile_kernel   point and bin of every tile, the work units (up to unit_tiles tiles
-//                 of one bin each) and the padding slots
+//   colscan       per point of many sort blocks: their offsets in each bin
+//   scan_kernel   per point: the same for few sort blocks, tiles and work
+//                 units before each bin; then before each point; per-class
+//                 counters reset
+//   scatter       a 40-byte record (theta, column, n_k) at the sorted slot; the
+//                 point and bin of every tile, the work units (up to
+//                 unit_tiles tiles of one bin each) and the padding slots
 //   coef_kernel   one thread per slot, FP64: antenna patterns, harmonics
 //                 (polynomial tables), Y_m (rounded to FP32) and x F_k, the
 //                 quadratic term B, and the interpolation fraction mu_k
@@ -34,9 +35,6 @@
 #include <algorithm>
 
 namespace rift {
-
-constexpr int kSortThreads = 1024;  // threads per sort block (kSortBlock samples)
-static_assert(kSortBlock % kSortThreads == 0, "a whole number of samples per sort thread");
 
 // ---- layouts of Q for the matrix cores, once per point ------------------------
 // Qm [K][Lpad][E] (FP32, zero past 2 M) and Qs [K][3 ceil(E / 8)][Lpad][8]
@@ -65,9 +63,12 @@ hipError_t mfma_layouts(const float *Q, float *Qm, void *Qs, int K, int Lpad, in
 }
 
 // ---- 1. integer delays, bin keys, per-block bin counts ----------------------
-// A sort block is kSortBlock consecutive samples of one point.  Counts go to an
-// LDS histogram (the point's bins), then to the block's row of the global
-// block histogram; no global atomics, so no contention on busy bins.
+// A sort block is TH U consecutive samples of one point (a.sort_block: 4096,
+// or 1024 and 256 for calls too small to fill the device with those).  Counts
+// go to an LDS histogram (the point's bins), then to the block's row of the
+// global block histogram; no global atomics, so no contention on busy bins.
+// Bound by the latency of the FP64 sky trigonometry: 4096 samples in one block
+// of 1024 threads took 22 us, in 16 of 256 6 us.
 __device__ __forceinline__ int block_item(const ItemsDev &it, int b) {
   int lo = 0, hi = it.n_items;  // blk0[lo] <= b < blk0[hi]
   while (hi - lo > 1) {
@@ -77,69 +78,86 @@ __device__ __forceinline__ int block_item(const ItemsDev &it, int b) {
   return lo;
 }
 
-template <typename R>
-__global__ void __launch_bounds__(kSortThreads) bin_kernel(MfmaArgsT<R> a) {
+template <typename R, int TH, int U>
+__global__ void __launch_bounds__(TH) bin_kernel(MfmaArgsT<R> a) {
   extern __shared__ uint32_t cnt_l[];
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[kCtlScan] = 0u;  // points scanned (scan_kernel)
   const int it = block_item(a.items, blockIdx.x);
   const int lb = blockIdx.x - a.items.blk0[it];
-  const PointDev &p = a.pts[a.items.point[it]];
+  const RIFT_CONST PointDev &p = *cp(a.pts + __builtin_amdgcn_readfirstlane(a.items.point[it]));
   const int nb = a.items.bin0[it + 1] - a.items.bin0[it];
   const bool lds = nb <= kLdsBins;
   uint32_t *cnt = lds ? cnt_l : a.bhist + a.items.hoff[it] + (int64_t)lb * nb;
-  for (int i = threadIdx.x; i < nb; i += kSortThreads) cnt[i] = 0u;
+  for (int i = threadIdx.x; i < nb; i += TH) cnt[i] = 0u;
   __syncthreads();
   const int64_t n = a.items.cnt[it];
-  const int64_t j0 = (int64_t)lb * kSortBlock, j1 = min(n, j0 + kSortBlock);
-  // the sort block's samples, kSortBlock / kSortThreads per thread: all
-  // their parameters are loaded before any is used, so the loads of a
-  // thread's samples are in flight together
-  constexpr int U = kSortBlock / kSortThreads;
+  const int64_t j0 = (int64_t)lb * (TH * U), j1 = min(n, j0 + TH * U);
+  // the sort block's samples, U per thread: all their parameters are loaded
+  // before any is used, so the loads of a thread's samples are in flight
+  // together
   R th[U][7];
 #pragma unroll
   for (int u = 0; u < U; u++) {
-    const int64_t j = j0 + threadIdx.x + (int64_t)u * kSortThreads;
+    const int64_t j = j0 + threadIdx.x + (int64_t)u * TH;
     const int64_t col = a.items.off[it] + (j < j1 ? j : j0);
 #pragma unroll
     for (int d = 0; d < 7; d++) th[u][d] = a.theta[d * a.stride + col];
   }
+  const int K = p.K, pad = p.pad, bin_w = p.bin_w, nq = p.nq;
 #pragma unroll
   for (int u = 0; u < U; u++) {
-    const int64_t j = j0 + threadIdx.x + (int64_t)u * kSortThreads;
+    const int64_t j = j0 + threadIdx.x + (int64_t)u * TH;
     if (j >= j1) break;
     const int64_t f = a.items.samp0[it] + j;
-    const double al = th[u][RIFT_ALPHA], de = th[u][RIFT_DELTA], io = th[u][RIFT_IOTA], ph = th[u][RIFT_PHI];
-    const double di = th[u][RIFT_DIST], ta = th[u][RIFT_TAU];
-    SkyTrig tr = sky_trig(al, de, 0.0, p.gmst);
-    Shift sh = shifts(p, tr, ta);
-    bool ok = sh.ok && isfinite(io) && isfinite(ph) && (a.dmarg || (isfinite(di) && di > 0.0)) &&
-              isfinite((double)th[u][RIFT_PSI]);
-    uint32_t key = 0, mul = 1;
-    uint32_t nw[2] = {0u, ok ? 1u << 16 : 0u};  // the four int16 of the sample, one 8-byte store
-    for (int k = 0; k < p.K; k++) {
-      int q = ok ? (sh.n[k] + p.pad) / p.bin_w : 0;
-      key += q * mul;
-      mul *= p.nq;
-      const uint32_t v = (uint16_t)(int16_t)(ok ? sh.n[k] : 0);
-      nw[k >> 1] |= (k & 1) ? v << 16 : v;
+    const double io = th[u][RIFT_IOTA], ph = th[u][RIFT_PHI], di = th[u][RIFT_DIST], ta = th[u][RIFT_TAU];
+    const SkyTrig tr = sky_trig(th[u][RIFT_ALPHA], th[u][RIFT_DELTA], 0.0, p.gmst);
+    // n_k = floor((tau + dt_k) f_s), valid when the 4-tap stencil stays inside
+    // the stored rows for every window sample: -pad <= n_k <= pad
+    bool ok = isfinite(ta) && isfinite(tr.ch) && isfinite(tr.sd) && isfinite(io) && isfinite(ph) &&
+              (a.dmarg || (isfinite(di) && di > 0.0)) && isfinite((double)th[u][RIFT_PSI]);
+    int nk[kMaxDet];
+#pragma unroll
+    for (int k = 0; k < kMaxDet; k++) {
+      nk[k] = 0;
+      if (k < K) {
+        const double rc[3] = {p.rc[k][0], p.rc[k][1], p.rc[k][2]};
+        const double sk = (ta + delay(rc, tr)) * p.f_s, fl = floor(sk);
+        const bool okk = isfinite(sk) && fl >= -pad && fl <= pad;
+        ok = ok && okk;
+        nk[k] = okk ? (int)fl : 0;
+      }
     }
-    *(uint2 *)(a.nsh + f * 4) = make_uint2(nw[0], nw[1]);
+    uint32_t key = 0, mul = 1;
+#pragma unroll
+    for (int k = 0; k < kMaxDet; k++) {
+      if (!ok) nk[k] = 0;
+      if (k < K) {
+        key += (ok ? (uint32_t)((nk[k] + pad) / bin_w) : 0u) * mul;
+        mul *= nq;
+      }
+    }
+    // the four int16 of the sample, one 8-byte store
+    *(uint2 *)(a.nsh + f * 4) = make_uint2((uint32_t)(uint16_t)nk[0] | (uint32_t)(uint16_t)nk[1] << 16,
+                                           (uint32_t)(uint16_t)nk[2] | (ok ? 1u << 16 : 0u));
     a.key[f] = key;
     atomicAdd(&cnt[key], 1u);
   }
   __syncthreads();
   if (lds) {
     uint32_t *row = a.bhist + a.items.hoff[it] + (int64_t)lb * nb;
-    for (int i = threadIdx.x; i < nb; i += kSortThreads) row[i] = cnt_l[i];
+    for (int i = threadIdx.x; i < nb; i += TH) row[i] = cnt_l[i];
   }
 }
 
-// ---- 2. per-item scans: block offsets within each bin, tiles before each bin --
-// Column scan of the [sort block][bin] histogram of one point: a workgroup
-// takes 64 bins; its 16 wavefronts each sum a sixteenth of the sort blocks,
-// then rewrite their share as running offsets.  Reads are coalesced along
-// the bins, and every point's bins are spread over many workgroups.
+// ---- 2. scans: block offsets within each bin, tiles before each bin and point --
+// Column scan of the [sort block][bin] histogram of one point with more than
+// kScanRows sort blocks: a workgroup takes 64 bins; its 16 wavefronts each sum
+// a sixteenth of the sort blocks, then rewrite their share as running offsets.
+// Reads are coalesced along the bins, and every point's bins are spread over
+// many workgroups.  (Fewer sort blocks: scan_kernel's own threads do it.)
 constexpr int kScanBins = 64;
 constexpr int kScanRanges = 16;  // block ranges per column scan: 1024 threads
+constexpr int kScanRows = 16;
 
 template <typename R>
 __global__ void __launch_bounds__(kScanRanges * kScanBins) colscan_kernel(MfmaArgsT<R> a) {
@@ -147,8 +165,8 @@ __global__ void __launch_bounds__(kScanRanges * kScanBins) colscan_kernel(MfmaAr
   const int q = threadIdx.x >> 6, bl = threadIdx.x & 63;
   for (int it = blockIdx.y; it < a.items.n_items; it += gridDim.y) {
     const int b0 = a.items.bin0[it], nb = a.items.bin0[it + 1] - b0;
-    if ((int)blockIdx.x * kScanBins >= nb) continue;  // uniform over the workgroup
     const int nblk = a.items.blk0[it + 1] - a.items.blk0[it];
+    if ((int)blockIdx.x * kScanBins >= nb || nblk <= kScanRows) continue;  // uniform over the workgroup
     const int lb_per = (nblk + kScanRanges - 1) / kScanRanges;
     const int b = (int)blockIdx.x * kScanBins + bl;
     const int lo = min(nblk, q * lb_per), hi = min(nblk, lo + lb_per);
@@ -180,130 +198,122 @@ __device__ __forceinline__ uint32_t bin_tiles(int unit_tiles, uint32_t cnt) {
   return w * ((cnt + w * kTS - 1) / (w * kTS));
 }
 
+// exclusive prefix of v over the 1024 threads of a workgroup, and its total
+template <typename V>
+__device__ __forceinline__ V block_scan(V v, V *wsum, V &total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  V x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const V y = (V)__shfl_up((unsigned long long)x, o);
+    if (lane >= o) x += y;
+  }
+  __syncthreads();  // wsum free
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  V before = 0;
+  total = 0;
+  for (int i = 0; i < 16; i++) {
+    if (i < wave) before += wsum[i];
+    total += wsum[i];
+  }
+  return before + x - v;
+}
+
+// One workgroup per point: the column scan of its few sort blocks (more:
+// colscan_kernel has done it), then the tiles and units before each bin.  The
+// workgroup that finishes last (a device counter) also takes the prefixes over
+// the points and resets the per-class counters.
 template <typename R>
-__global__ void __launch_bounds__(256) tilescan_kernel(MfmaArgsT<R> a) {
-  __shared__ uint32_t pt[256], pu[256];
-  const int it = blockIdx.x;
+__global__ void __launch_bounds__(1024) scan_kernel(MfmaArgsT<R> a) {
+  __shared__ uint64_t wsum[16];
+  __shared__ bool last_sh;
+  const int it = blockIdx.x, tid = threadIdx.x;
   const int b0 = a.items.bin0[it], nb = a.items.bin0[it + 1] - b0;
-  const int per = (nb + 255) / 256;
+  const int nblk = a.items.blk0[it + 1] - a.items.blk0[it];
   const uint32_t U = (uint32_t)a.unit_tiles;
-  const int lo = min(nb, (int)threadIdx.x * per), hi = min(nb, lo + per);
-  uint32_t ct = 0, cu = 0;
+  if (nblk <= kScanRows) {
+    uint32_t *h = a.bhist + a.items.hoff[it];
+    for (int b = tid; b < nb; b += 1024) {
+      uint32_t v[kScanRows], run = 0;
+#pragma unroll
+      for (int lb = 0; lb < kScanRows; lb++) v[lb] = lb < nblk ? h[(int64_t)lb * nb + b] : 0u;
+#pragma unroll
+      for (int lb = 0; lb < kScanRows; lb++) {
+        if (lb < nblk) h[(int64_t)lb * nb + b] = run;
+        run += v[lb];
+      }
+      a.count[b0 + b] = run;
+    }
+    __syncthreads();
+  }
+  // a contiguous run of bins per thread; tiles and units as one 64-bit sum
+  const int per = (nb + 1023) / 1024, lo = min(nb, tid * per), hi = min(nb, lo + per);
+  auto of = [&](uint32_t cnt) {
+    const uint32_t tb = bin_tiles(a.unit_tiles, cnt);
+    return (uint64_t)tb | (uint64_t)((tb + U - 1) / U) << 32;
+  };
+  uint64_t sum = 0, all;
+  for (int b = lo; b < hi; b++) sum += of(a.count[b0 + b]);
+  uint64_t run = block_scan<uint64_t>(sum, wsum, all);
   for (int b = lo; b < hi; b++) {
-    const uint32_t tb = bin_tiles(a.unit_tiles, a.count[b0 + b]);
-    ct += tb;
-    cu += (tb + U - 1) / U;
+    a.bin_tile[b0 + b] = (uint32_t)run;
+    a.bin_unit[b0 + b] = (uint32_t)(run >> 32);
+    run += of(a.count[b0 + b]);
   }
-  pt[threadIdx.x] = ct;
-  pu[threadIdx.x] = cu;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t rt = 0, ru = 0;
-    for (int i = 0; i < 256; i++) {
-      uint32_t y = pt[i], z = pu[i];
-      pt[i] = rt;
-      pu[i] = ru;
-      rt += y;
-      ru += z;
-    }
-    a.item_tiles[it + 1] = (rt + 3u) & ~3u;  // whole groups of 4 tiles per point
-    a.item_units[it + 1] = ru;
+  const uint32_t rt = (uint32_t)all, ru = (uint32_t)(all >> 32);
+  if (tid == 0) {
+    // whole groups of 4 tiles per point; read by another workgroup
+    __hip_atomic_store(&a.item_tiles[it + 1], (rt + 3u) & ~3u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&a.item_units[it + 1], ru, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t done = __hip_atomic_fetch_add(&a.ctl[kCtlScan], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    last_sh = done + 1 == (uint32_t)a.items.n_items;
   }
   __syncthreads();
-  uint32_t rt = pt[threadIdx.x], ru = pu[threadIdx.x];
-  for (int b = lo; b < hi; b++) {
-    const uint32_t tb = bin_tiles(a.unit_tiles, a.count[b0 + b]);
-    a.bin_tile[b0 + b] = rt;
-    a.bin_unit[b0 + b] = ru;
-    rt += tb;
-    ru += (tb + U - 1) / U;
-  }
-}
-
-// prefix of tiles over items (one thread); reset of the per-class counters
-template <typename R>
-__global__ void item_scan_kernel(MfmaArgsT<R> a) {
-  if (threadIdx.x == 0) {
-    uint32_t r = 0;
-    a.item_tiles[0] = 0;
-    for (int i = 0; i < a.items.n_items; i++) {
-      r += a.item_tiles[i + 1];
-      a.item_tiles[i + 1] = r;
-    }
-    a.ctl[0] = r;
-    for (int c = 0; c < kMaxClasses; c++) a.ctl[1 + c] = 0;
-    a.ctl[kCtlRefine] = 0;
-    uint32_t u = 0;
-    a.item_units[0] = 0;
-    for (int i = 0; i < a.items.n_items; i++) {
-      u += a.item_units[i + 1];
-      a.item_units[i + 1] = u;
-    }
-    // coefficient storage: K 2Mp 16 floats per tile of each point
-    int64_t c = 0;
-    for (int i = 0; i < a.items.n_items; i++) {
-      a.item_cop[i] = c;
+  if (!last_sh) return;
+  const int ni = a.items.n_items;
+  uint64_t ct = 0, cc = 0;  // tiles and units; coefficient storage: K 2Mp 16 values per tile of each point
+  for (int c0 = 0; c0 < ni; c0 += 1024) {
+    const int i = c0 + tid;
+    uint64_t t = 0, c = 0, tt, tc;
+    if (i < ni) {
+      const uint32_t nt = __hip_atomic_load(&a.item_tiles[i + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t nu = __hip_atomic_load(&a.item_units[i + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      t = (uint64_t)nt | (uint64_t)nu << 32;
       const PointDev &p = a.pts[a.items.point[i]];
-      c += (int64_t)(a.item_tiles[i + 1] - a.item_tiles[i]) * p.K * 2 * p.Mp * kTS;
+      c = (uint64_t)nt * (uint64_t)(p.K * 2 * p.Mp * kTS);
     }
+    const uint64_t xt = ct + block_scan<uint64_t>(t, wsum, tt) + t;
+    const uint64_t xc = cc + block_scan<uint64_t>(c, wsum, tc);
+    if (i < ni) {
+      a.item_tiles[i + 1] = (uint32_t)xt;
+      a.item_units[i + 1] = (uint32_t)(xt >> 32);
+      a.item_cop[i] = (int64_t)xc;
+    }
+    ct += tt;
+    cc += tc;
   }
+  if (tid == 0) {
+    a.item_tiles[0] = 0;
+    a.item_units[0] = 0;
+    a.ctl[0] = (uint32_t)ct;
+    a.ctl[kCtlRefine] = 0;
+  }
+  if (tid < kMaxClasses) a.ctl[1 + tid] = 0;
 }
 
-// ---- 3. scatter: one record per sample at its (padded) sorted slot ------------
+// ---- 3. one record per sample at its (padded) sorted slot; the tiles -----------
+// The first n_sort_blocks workgroups scatter their samples' records.  The
+// others take one tile per thread: its point and bin, the work unit it opens
+// (every unit_tiles-th tile of a bin opens one, for itself and the next ones),
+// and the padding slots (flag 0) that the scatter leaves: the rest of a bin's
+// last tiles and, past the last bin, the tiles that round the point up to
+// groups of 4.  The tile's bin is found by bisection of the point's tile
+// prefixes, so a bin that holds most of a call's samples (a proposal
+// concentrated on a source) costs no more than the same number of tiles in
+// many bins: one thread per bin took 877 us for 1e6 samples with half of them
+// in a few bins, one per tile 6 us.
 template <typename R>
-__global__ void __launch_bounds__(kSortThreads) scatter_kernel(MfmaArgsT<R> a) {
-  extern __shared__ uint32_t cur_l[];
-  const int it = block_item(a.items, blockIdx.x);
-  const int lb = blockIdx.x - a.items.blk0[it];
-  const int b0 = a.items.bin0[it], nb = a.items.bin0[it + 1] - b0;
-  const bool lds = nb <= kLdsBins;
-  uint32_t *cur = lds ? cur_l : a.bhist + a.items.hoff[it] + (int64_t)lb * nb;
-  if (lds) {
-    const uint32_t *row = a.bhist + a.items.hoff[it] + (int64_t)lb * nb;
-    for (int i = threadIdx.x; i < nb; i += kSortThreads) cur_l[i] = row[i];
-  }
-  __syncthreads();
-  const int64_t n = a.items.cnt[it];
-  const int64_t j0 = (int64_t)lb * kSortBlock, j1 = min(n, j0 + kSortBlock);
-  const uint32_t tbase = a.item_tiles[it];
-  // kSortBlock / kSortThreads samples per thread, their loads issued together
-  constexpr int U = kSortBlock / kSortThreads;
-  SampleRec rec[U];
-  uint32_t key[U];
-#pragma unroll
-  for (int u = 0; u < U; u++) {
-    const int64_t jj = j0 + threadIdx.x + (int64_t)u * kSortThreads, j = jj < j1 ? jj : j0;
-    const int64_t f = a.items.samp0[it] + j;
-    const int64_t col = a.items.off[it] + j;
-    key[u] = a.key[f];
-#pragma unroll
-    for (int d = 0; d < 7; d++) rec[u].th[d] = sizeof(R) == 4 ? (float)a.theta[d * a.stride + col] : 0.f;
-    rec[u].col = (int)col;
-    const uint2 nw = *(const uint2 *)(a.nsh + f * 4);
-    rec[u].n[0] = (int16_t)(nw.x & 0xffffu);
-    rec[u].n[1] = (int16_t)(nw.x >> 16);
-    rec[u].n[2] = (int16_t)(nw.y & 0xffffu);
-    rec[u].flag = (nw.y >> 16) ? 1 : 2;
-  }
-#pragma unroll
-  for (int u = 0; u < U; u++) {
-    if (j0 + threadIdx.x + (int64_t)u * kSortThreads >= j1) break;
-    const uint32_t r = atomicAdd(&cur[key[u]], 1u);
-    a.rec[kTS * (tbase + a.bin_tile[b0 + key[u]]) + r] = rec[u];
-  }
-}
-
-// One thread per tile: its point and bin, the work unit it opens (every unit_tiles-th tile
-// of a bin opens one, for itself and the next ones), and the padding slots
-// (flag 0) that the scatter leaves: the rest of a bin's last pair and, past
-// the last bin, the tiles that round the point up to groups of 4.  The tile's
-// bin is found by bisection of the point's tile prefixes, so a bin that holds
-// most of a call's samples (a proposal concentrated on a source) costs no more
-// than the same number of tiles in many bins: one thread per bin took 877 us
-// for 1e6 samples with half of them in a few bins, this form 6 us.
-template <typename R>
-__global__ void __launch_bounds__(64) tile_kernel(MfmaArgsT<R> a) {
-  const uint32_t t = blockIdx.x * 64u + threadIdx.x;
+__device__ __forceinline__ void tile_setup(const MfmaArgsT<R> &a, uint32_t t) {
   if (t >= a.ctl[0]) return;
   int lo = 0, hi = a.items.n_items;  // item_tiles[lo] <= t < item_tiles[hi]
   while (hi - lo > 1) {
@@ -337,6 +347,52 @@ __global__ void __launch_bounds__(64) tile_kernel(MfmaArgsT<R> a) {
   z.n[0] = z.n[1] = z.n[2] = 0;
   z.flag = 0;
   for (uint32_t q = used; q < (uint32_t)kTS; q++) a.rec[(int64_t)kTS * t + q] = z;
+}
+
+template <typename R, int TH, int U>
+__global__ void __launch_bounds__(TH) scatter_kernel(MfmaArgsT<R> a) {
+  extern __shared__ uint32_t cur_l[];
+  if ((int)blockIdx.x >= a.n_sort_blocks) {
+    tile_setup(a, (blockIdx.x - (uint32_t)a.n_sort_blocks) * TH + threadIdx.x);
+    return;
+  }
+  const int it = block_item(a.items, blockIdx.x);
+  const int lb = blockIdx.x - a.items.blk0[it];
+  const int b0 = a.items.bin0[it], nb = a.items.bin0[it + 1] - b0;
+  const bool lds = nb <= kLdsBins;
+  uint32_t *cur = lds ? cur_l : a.bhist + a.items.hoff[it] + (int64_t)lb * nb;
+  if (lds) {
+    const uint32_t *row = a.bhist + a.items.hoff[it] + (int64_t)lb * nb;
+    for (int i = threadIdx.x; i < nb; i += TH) cur_l[i] = row[i];
+  }
+  __syncthreads();
+  const int64_t n = a.items.cnt[it];
+  const int64_t j0 = (int64_t)lb * (TH * U), j1 = min(n, j0 + TH * U);
+  const uint32_t tbase = a.item_tiles[it];
+  // U samples per thread, their loads issued together
+  SampleRec rec[U];
+  uint32_t key[U];
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    const int64_t jj = j0 + threadIdx.x + (int64_t)u * TH, j = jj < j1 ? jj : j0;
+    const int64_t f = a.items.samp0[it] + j;
+    const int64_t col = a.items.off[it] + j;
+    key[u] = a.key[f];
+#pragma unroll
+    for (int d = 0; d < 7; d++) rec[u].th[d] = sizeof(R) == 4 ? (float)a.theta[d * a.stride + col] : 0.f;
+    rec[u].col = (int)col;
+    const uint2 nw = *(const uint2 *)(a.nsh + f * 4);
+    rec[u].n[0] = (int16_t)(nw.x & 0xffffu);
+    rec[u].n[1] = (int16_t)(nw.x >> 16);
+    rec[u].n[2] = (int16_t)(nw.y & 0xffffu);
+    rec[u].flag = (nw.y >> 16) ? 1 : 2;
+  }
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    if (j0 + threadIdx.x + (int64_t)u * TH >= j1) break;
+    const uint32_t r = atomicAdd(&cur[key[u]], 1u);
+    a.rec[kTS * (tbase + a.bin_tile[b0 + key[u]]) + r] = rec[u];
+  }
 }
 
 // ---- 4. per-sample coefficients (FP64), tile-major ---------------------------
@@ -497,17 +553,26 @@ __global__ void __launch_bounds__(64) coef_kernel(MfmaArgsT<R> a, int item_lo, i
   ct->flag[s] = valid ? 1 : (pad ? 0 : 2);
 }
 
+// the sort: sort blocks of TH U samples
+template <typename R, int TH, int U>
+static void sort_launch(const MfmaArgsT<R> &a, hipStream_t st) {
+  const size_t lds = sizeof(uint32_t) * (size_t)std::min(a.max_item_bins, kLdsBins);
+  hipLaunchKernelGGL((bin_kernel<R, TH, U>), dim3(a.n_sort_blocks), dim3(TH), lds, st, a);
+  if (a.max_item_blocks > kScanRows)
+    hipLaunchKernelGGL(colscan_kernel<R>,
+                       dim3((unsigned)((a.max_item_bins + kScanBins - 1) / kScanBins), std::min(a.items.n_items, 65535)),
+                       dim3(kScanRanges * kScanBins), 0, st, a);
+  hipLaunchKernelGGL(scan_kernel<R>, dim3(a.items.n_items), dim3(1024), 0, st, a);
+  hipLaunchKernelGGL((scatter_kernel<R, TH, U>), dim3((unsigned)(a.n_sort_blocks + (a.max_tiles + TH - 1) / TH)), dim3(TH),
+                     lds, st, a);
+}
+
 template <typename R>
 hipError_t mfma_prepare(const MfmaArgsT<R> &a, const int *mclass_M, const int *mclass_item0,
                         const int64_t *mclass_tiles, int n_mclasses, hipStream_t st) {
-  const size_t lds = sizeof(uint32_t) * (size_t)std::min(a.max_item_bins, kLdsBins);
-  hipLaunchKernelGGL(bin_kernel<R>, dim3(a.n_sort_blocks), dim3(kSortThreads), lds, st, a);
-  hipLaunchKernelGGL(colscan_kernel<R>, dim3((unsigned)((a.max_item_bins + kScanBins - 1) / kScanBins), std::min(a.items.n_items, 65535)),
-                     dim3(kScanRanges * kScanBins), 0, st, a);
-  hipLaunchKernelGGL(tilescan_kernel<R>, dim3(a.items.n_items), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(item_scan_kernel<R>, dim3(1), dim3(64), 0, st, a);
-  hipLaunchKernelGGL(scatter_kernel<R>, dim3(a.n_sort_blocks), dim3(kSortThreads), lds, st, a);
-  hipLaunchKernelGGL(tile_kernel<R>, dim3((unsigned)((a.max_tiles + 63) / 64)), dim3(64), 0, st, a);
+  if (a.sort_block == 256) sort_launch<R, 256, 1>(a, st);
+  else if (a.sort_block == 1024) sort_launch<R, 256, 4>(a, st);
+  else sort_launch<R, 1024, 4>(a, st);
   for (int c = 0; c < n_mclasses; c++) {
     const int lo = mclass_item0[c], hi = mclass_item0[c + 1];
     const dim3 grid((unsigned)(((int64_t)kTS * mclass_tiles[c] + 63) / 64));

@@ -581,8 +581,14 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   std::vector<int64_t> samp0(1, 0), mclass_tiles, hoff;
   std::vector<int> bin0(1, 0), blk0(1, 0), class_T, class_K, class_item0, mclass_M, mclass_item0;
   int64_t hist_total = 0, cop_floats = 0;
-  int max_item_bins = 1;
-  int64_t max_tiles = 0;
+  int max_item_bins = 1, max_item_blocks = 1;
+  int64_t max_tiles = 0, all = 0;
+  for (size_t i = 0; i < it.point.size(); i++) {
+    all += it.cnt[i];
+    max_item_bins = std::max(max_item_bins, h->hp[it.point[i]].n_bins_key);
+  }
+  // (the block histograms of very many bins are kept few)
+  const int sort_block = max_item_bins <= kLdsBins ? sort_block_of(all) : 4096;
   for (size_t i = 0; i < it.point.size(); i++) {
     const PointDev &p = h->hp[it.point[i]];
     const int T = p.Mp >> 1;
@@ -604,7 +610,8 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
     long long nb = (long long)bin0.back() + p.n_bins_key;
     if (nb > (1 << 28)) return fail(h, RIFT_E_SHAPE, "too many delay bins in one call");
     bin0.push_back((int)nb);
-    const int nblk = (int)((it.cnt[i] + kSortBlock - 1) / kSortBlock);
+    const int nblk = (int)((it.cnt[i] + sort_block - 1) / sort_block);
+    max_item_blocks = std::max(max_item_blocks, nblk);
     blk0.push_back(blk0.back() + nblk);
     hoff.push_back(hist_total);
     hist_total += (int64_t)nblk * p.n_bins_key;
@@ -637,6 +644,8 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   a.items.hoff = d_hoff;
   a.n_sort_blocks = blk0.back();
   a.max_item_bins = max_item_bins;
+  a.sort_block = sort_block;
+  a.max_item_blocks = max_item_blocks;
   a.items.point = d_point;
   a.items.off = d_off;
   a.items.cnt = d_cnt;
@@ -847,7 +856,7 @@ Items make_items(int n_items, const rift_ile_item *items) {
 bool use_sorted64(const rift_ile *h, const Items &it, int64_t stride, bool bwd) {
   if (h->dmarg && !bwd) return false;
   if (stride > (int64_t)INT32_MAX || plain_samples(h, 8, bwd) == 0) return false;
-  const double sort_work = bwd ? 1.2e7 : 6.0e7;
+  const double sort_work = bwd ? 3.0e7 : 4.0e7;
   double work = 0.0;
   for (size_t i = 0; i < it.point.size(); i++) {
     const PointDev &p = h->hp[it.point[i]];
