@@ -845,25 +845,28 @@ Items make_items(int n_items, const rift_ile_item *items) {
   return it;
 }
 
-// FP64 calls that go to the sorted matrix-core form: at least sort_work units
-// of K n_t (M + 4) per sample.  Below, the sort's launches cost more than the
-// plain kernel's one: 10007 samples at K = 2, M = 2, n_t = 410 (4.9e7) take 73
-// us there and 85 us sorted, 20000 at K = 3, M = 9 (3.2e8) 2583 and 314 us with
-// the gradient, 2e5 at K = 3, M = 21, n_t = 820 (1.2e10) 10.2 and 1.2 ms.  What the plain form refuses stays
+// FP64 calls that go to the sorted matrix-core form: by units of K n_t (M + 4)
+// per sample.  Below the line the sort's launches cost more than the plain
+// kernel's one: 10007 samples at K = 2, M = 2, n_t = 410 (4.9e7) take 73 us
+// there and 57 us sorted, 5 x 3226 at K = 3, M = 5, n_t = 128 (5.6e7) 71 and
+// 79 us; with the gradient 5 x 697 at K = 3, M = 12, n_t = 107 (1.8e7) 200 and
+// 231 us, 20000 at K = 3, M = 9 (3.2e8) 2586 and 291 us.  What the plain form refuses stays
 // refused; what it takes and the sorted form does not (more than 2^31 columns,
 // the bins of a very large pad) stays with it, and so does distance
 // marginalization.
 bool use_sorted64(const rift_ile *h, const Items &it, int64_t stride, bool bwd) {
   if (h->dmarg && !bwd) return false;
   if (stride > (int64_t)INT32_MAX || plain_samples(h, 8, bwd) == 0) return false;
-  const double sort_work = bwd ? 3.0e7 : 4.0e7;
   double work = 0.0;
+  int K = 1;
   for (size_t i = 0; i < it.point.size(); i++) {
     const PointDev &p = h->hp[it.point[i]];
     if (p.n_bins_key > (1 << 16)) return false;
     work += (double)it.cnt[i] * p.K * p.n_t * (p.M + 4);
+    K = std::max(K, p.K);
   }
-  return work >= sort_work;
+  // (three detectors have some four times the bins of two, and fuller tiles later)
+  return work >= (bwd ? 3.0e7 : K == 3 ? 6.0e7 : 4.0e7);
 }
 
 template <typename R>
