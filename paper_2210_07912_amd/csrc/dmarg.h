@@ -75,8 +75,10 @@ __device__ __forceinline__ double dm_log<double>(double v) { return log(v); }
 // The breakpoints are the ends and the stationary points clamped to the range
 // (missing ones repeat an end), so every loop has a fixed trip count and the
 // arrays stay in registers.
-template <typename F>
-__device__ inline void dm_interval(F A, F B, F t_lo, F t_hi, F T, int iters, F &ta, F &tb) {
+// SIDE 0: ta and tb; 1: the calling lane's side only (right: tb, else ta, the
+// other end left unset), for two lanes that share the work and exchange ends.
+template <typename F, int SIDE = 0>
+__device__ inline void dm_interval(F A, F B, F t_lo, F t_hi, F T, int iters, F &ta, F &tb, bool right = false) {
   auto E = [&](F t) {
     const F x = dm_exp<F>(t);
     return x * A - x * x * B - F(3) * t;
@@ -129,6 +131,39 @@ __device__ inline void dm_interval(F A, F B, F t_lo, F t_hi, F T, int iters, F &
         v = br[0];
       }
     }
+  }
+  if constexpr (SIDE == 1) {
+    // the last breakpoint at or above thr, or the crossing after it
+    F ur = t_hi, vr = t_hi;
+    bool doner = false, crossr = false;
+#pragma unroll
+    for (int i = 3; i >= 0; i--) {
+      if (!doner && Eb[i] >= thr) {
+        doner = true;
+        if (i < 3) {
+          ur = br[i];
+          vr = br[i + 1];
+          crossr = true;
+        } else {
+          ur = br[3];
+        }
+      }
+    }
+    // one bisection for either end: [u, v] with the inside at v (left) or u (right)
+    if (right) {
+      u = ur;
+      v = vr;
+      cross = crossr;
+    }
+    if (cross) {
+      for (int k = 0; k < iters; k++) {
+        const F m = F(0.5) * (u + v);
+        if ((E(m) >= thr) != right) v = m; else u = m;
+      }
+    }
+    ta = cross ? u : v;
+    tb = cross ? v : u;
+    return;
   }
   if (cross) {
     for (int k = 0; k < iters; k++) {

@@ -50,6 +50,8 @@ constexpr int kMaxT = kMaxModes / 2;  // MFMA steps of 4 elements per detector: 
 constexpr int kMaxClasses = 48;  // one persistent launch per distinct (T = Mp / 2, K)
 constexpr int kCtlRefine = 1 + kMaxClasses;  // ctl slot of the refinement count
 constexpr int kCtlScan = 2 + kMaxClasses;    // ctl slot of the points scanned so far
+constexpr int kCtlUnits2 = 3 + kMaxClasses;  // first of the unit counters of a call's second pass over its units
+constexpr int kCtlWords = kCtlUnits2 + kMaxClasses;
 constexpr int kNtBuckets = 17;   // autotuner key: floor(log2 n_t) of a class's longest window
 constexpr int kFeedConfigs = 7;  // launch configurations the autotuner measures per class
 
@@ -124,7 +126,8 @@ struct MfmaArgsT {
   WorkUnit *unit;         // [max_tiles] work units, bins in order, points in order
   uint32_t *bin_unit;     // [n_bins] first unit of the bin within its item
   uint32_t *item_units;   // [n_items + 1] unit prefix over items (filled on device)
-  uint32_t *ctl;          // [0]: number of tiles, [1 + c]: unit counter of class c, then kCtlRefine, kCtlScan
+  uint32_t *ctl;          // [0]: number of tiles, [1 + c]: unit counter of class c, then kCtlRefine, kCtlScan,
+                          // [kCtlUnits2 + c]: class c's of a second pass
   // adjoint (null in the forward pass)
   const R *gin;           // [stride] upstream d/d ln L_t, or null (= 1)
   R *grad;                // [7][stride] gradient of ln L_t (times gin)

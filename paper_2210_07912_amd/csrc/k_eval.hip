@@ -55,9 +55,10 @@ namespace rift {
 // the window values are the data terms A_j, base 2): MODE 1 writes each
 // slot's largest A_j; MODE 2 reads it back, places the slot's nodes x_i over
 // D (dmarg.h) and sums exp2(x_i (A_j - A_max)) per node over the window,
-// skipping window samples where even the smallest node's term is below
-// 2^-(T + 10) log2 e (their n_t terms together are far under the rule's
-// error), then combines the nodes in FP64.  Both passes recompute the same
+// leaving out a node's terms below 2^-(T + 10) log2 e (its sum is at least 1,
+// and n_t such terms together are far under the rule's error), eight nodes
+// and four window samples at a time, then combines the nodes in FP64, twelve
+// by each of the sample's two lanes.  Both passes recompute the same
 // window values bit for bit.
 // WPE: wavefronts per SIMD the register allocation must allow.  est_regs
 // counts the parts of the sample operands, the rows kept per detector (of one
@@ -116,7 +117,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
   for (;;) {
     __syncthreads();  // every wavefront is done with the previous unit
     if (threadIdx.x == 0) {
-      const uint32_t n = atomicAdd(&a.ctl[1 + cls], 1u);
+      const uint32_t n = atomicAdd(&a.ctl[(MODE == 2 ? kCtlUnits2 : 1) + cls], 1u);
       WorkUnit w;
       w.tile = 0xffffffffu;
       w.ntiles = 0;
@@ -291,25 +292,36 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
     constexpr int NN = MODE == 2 ? kDmGL : 1;
     float am = MODE == 1 ? -INFINITY : 0.f, skip = INFINITY;
     double ta = 0.0, hq = 0.0;  // the nodes' interval in t = ln x
+    constexpr float kNodeSkip = -(float)((DmRule<float>::T + 10.0) * kLog2e);
     float xs[NN], Sq[NN];
 #pragma unroll
     for (int q = 0; q < NN; q++) xs[q] = Sq[q] = 0.f;
     if constexpr (MODE == 2) {
       const float av = active ? a.amax[(int64_t)t * kTS + sc] : 0.f;
-      if (valid && isfinite(av)) {
+      const bool have = valid && isfinite(av);
+      // the interval is searched in FP32, one end by each of the sample's two
+      // lanes; an end at the prior's edge takes the edge's FP64 value, so a
+      // range much narrower than the FP32 spacing of t keeps its exact width
+      // (the rule's weights scale with it)
+      const double tlo = log(p.d_ref / a.dm_hi), thi = log(p.d_ref / a.dm_lo);
+      float taf = (float)tlo, tbf = (float)thi;
+      if (have)
+        dm_interval<float, 1>(av * kLn2f, Bf * kLn2f, (float)tlo, (float)thi, (float)DmRule<float>::T, 24, taf, tbf, h);
+      const float mine = h ? tbf : taf, other = __shfl_xor(mine, 32);
+      taf = h ? other : mine;
+      tbf = h ? mine : other;
+      if (!(tbf > taf)) {  // a single point (or a non-finite envelope): the whole range
+        taf = (float)tlo;
+        tbf = (float)thi;
+      }
+      if (have) {
         am = av;
-        // the interval is searched in FP32; an end at the prior's edge takes
-        // the edge's FP64 value, so a range much narrower than the FP32
-        // spacing of t keeps its exact width (the rule's weights scale with it)
-        const double tlo = log(p.d_ref / a.dm_hi), thi = log(p.d_ref / a.dm_lo);
-        float taf, tbf;
-        dm_interval<float>(av * kLn2f, Bf * kLn2f, (float)tlo, (float)thi, (float)DmRule<float>::T, 24, taf, tbf);
         ta = taf <= (float)tlo ? tlo : (double)taf;
         const double tb = tbf >= (float)thi ? thi : (double)tbf;
         hq = tb - ta;
 #pragma unroll
         for (int q = 0; q < NN; q++) xs[q] = expf((float)(ta + hq * (0.5 + 0.5 * dm_gl_node(q))));
-        skip = -(float)((DmRule<float>::T + 10.0) * kLog2e) / xs[0];
+        skip = kNodeSkip / xs[0];
       }
     }
     f16v acc[PL ? 1 : K];  // the last block's rows (8 (i / 4) + 4 h + i % 4 in register i)
@@ -353,17 +365,24 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
       } else if constexpr (MODE == 2) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; q4++) {
-          if (c4[q4] - am >= skip) {
+          const float dm = c4[q4] - am;
+          if (dm >= skip) {
             float d[4];
 #pragma unroll
             for (int i = 0; i < 4; i++) d[i] = ell[4 * q4 + i] - am;
+            // eight nodes at a time, ascending: past the first whose terms are
+            // all below 2^kNodeSkip (its sum is at least 1) none counts
 #pragma unroll
-            for (int q = 0; q < NN; q++) {
-              float e = 0.f;
+            for (int q0 = 0; q0 < NN; q0 += 8)
+              if (xs[q0] * dm >= kNodeSkip) {
 #pragma unroll
-              for (int i = 0; i < 4; i++) e += __builtin_amdgcn_exp2f(xs[q] * d[i]);
-              Sq[q] += e;
-            }
+                for (int q = q0; q < q0 + 8 && q < NN; q++) {
+                  float e = 0.f;
+#pragma unroll
+                  for (int i = 0; i < 4; i++) e += __builtin_amdgcn_exp2f(xs[q] * d[i]);
+                  Sq[q] += e;
+                }
+              }
           }
         }
       } else {
@@ -515,26 +534,24 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
       for (int q = 0; q < NN; q++) {
         Sq[q] += __shfl_xor(Sq[q], 32);
       }
+      // twelve nodes per lane
       float lt = NAN;
-      if (valid && h == 0 && hq > 0.0) {
-        const double A = (double)am * (double)kLn2f, Bv = (double)Bf * (double)kLn2f;
-        const double c = 3.0 * p.d_ref * p.d_ref * p.d_ref / (a.dm_hi * a.dm_hi * a.dm_hi - a.dm_lo * a.dm_lo * a.dm_lo);
-        const double lc = log(0.5 * hq * c);
-        double cmax = -INFINITY, acc = 0.0;
+      const double A = (double)am * (double)kLn2f, Bv = (double)Bf * (double)kLn2f;
+      const double c = 3.0 * p.d_ref * p.d_ref * p.d_ref / (a.dm_hi * a.dm_hi * a.dm_hi - a.dm_lo * a.dm_lo * a.dm_lo);
+      double ci[NN / 2 > 0 ? NN / 2 : 1], cmax = -INFINITY, sum = 0.0;
 #pragma unroll
-        for (int q = 0; q < NN; q++) {
-          const double tq = ta + hq * (0.5 + 0.5 * dm_gl_node(q));
-          const double xd = (double)xs[q];
-          const double ci = lc + log(dm_gl_weight(q)) - 3.0 * tq + xd * A - xd * xd * Bv + log((double)Sq[q]);
-          if (ci > cmax) {
-            acc = acc * exp(cmax - ci) + 1.0;
-            cmax = ci;
-          } else {
-            acc += exp(ci - cmax);
-          }
-        }
-        lt = (float)(cmax + log(acc) - log((double)NT));
+      for (int q = 0; q < NN / 2; q++) {
+        const double node = h ? dm_gl_node(q + NN / 2) : dm_gl_node(q), wt = h ? dm_gl_weight(q + NN / 2) : dm_gl_weight(q);
+        const double tq = ta + hq * (0.5 + 0.5 * node), xd = (double)(h ? xs[q + NN / 2] : xs[q]);
+        ci[q] = xd * A - xd * xd * Bv - 3.0 * tq + log(wt * (double)(h ? Sq[q + NN / 2] : Sq[q]));
+        cmax = fmax(cmax, ci[q]);
       }
+      const double co = __hiloint2double(__shfl_xor(__double2hiint(cmax), 32), __shfl_xor(__double2loint(cmax), 32));
+      cmax = fmax(cmax, co);
+#pragma unroll
+      for (int q = 0; q < NN / 2; q++) sum += exp(ci[q] - cmax);
+      sum += __hiloint2double(__shfl_xor(__double2hiint(sum), 32), __shfl_xor(__double2loint(sum), 32));
+      if (valid && hq > 0.0) lt = (float)(cmax + log(sum) + log(0.5 * hq * c) - log((double)NT));
       if (!isfinite(lt)) lt = NAN;
       if (flag != 0 && h == 0) {
         if (a.lnL) gpw(a.lnL)[col] = lt;
@@ -575,15 +592,26 @@ static void launch_tk(const MfmaArgs &a, int lo, int hi, int cls, hipStream_t st
   hipLaunchKernelGGL((mfma_kernel<G, K, D, MODE, WPE>), dim3(grid), dim3(256), 0, st, a, lo, hi, cls);
 }
 
+// The passes of distance marginalization run one wavefront per SIMD, with all
+// its registers, in calls of at most kOneWave samples per compute unit: those
+// have no second wavefront to share it (a workgroup takes 128 samples), and
+// the forms for two keep part of the nodes and sums in scratch memory.  3370
+// samples at K = 3, M = 9, n_t = 105 take 95 us, in the form for two 123; 64000
+// at K = 2, M = 5, n_t = 300 take 165 us, in the form for two 150.
+constexpr int kOneWave = 128;
+
 // pass: 0 ln L_t (staged or direct feed); 1, 2 the passes of distance
-// marginalization (staged feed)
+// marginalization (direct feed)
 template <int G, int K>
 static void launch_tkm(const MfmaArgs &a, bool direct, int pass, int lo, int hi, int cls, hipStream_t st, int res,
                        int wpe) {
   // a cap the class cannot meet without spilling runs the uncapped form
   constexpr int D3 = can_wpe(G, K, 3) ? 3 : base_wpe(G, K, 0, true), D4 = can_wpe(G, K, 4) ? 4 : base_wpe(G, K, 0, true);
   constexpr int S3 = can_wpe(G, K, 3) ? 3 : base_wpe(G, K, 0, false);
-  if (pass == 1) launch_tk<G, K, true, 1>(a, lo, hi, cls, st, res);
+  const bool one = a.total <= (int64_t)kOneWave * (a.grid / 4);
+  if (pass == 1 && one) launch_tk<G, K, true, 1, 1>(a, lo, hi, cls, st, res);
+  else if (pass == 1) launch_tk<G, K, true, 1>(a, lo, hi, cls, st, res);
+  else if (pass == 2 && one) launch_tk<G, K, true, 2, 1>(a, lo, hi, cls, st, res);
   else if (pass == 2) launch_tk<G, K, true, 2>(a, lo, hi, cls, st, res);
   else if (direct && wpe == 3) launch_tk<G, K, true, 0, D3>(a, lo, hi, cls, st, res);
   else if (wpe == 3) launch_tk<G, K, false, 0, S3>(a, lo, hi, cls, st, res);
@@ -693,13 +721,9 @@ hipError_t mfma_forward(const MfmaArgs &a, const int *class_T, const int *class_
       }
   if (ev0) (void)hipEventRecord(ev0, st);
   if (a.dmarg) {
-    // distance marginalization: every class's largest data terms, then (the
-    // work-unit counters cleared by a fill kernel) the integrals over D
+    // distance marginalization: every class's largest data terms, then (with
+    // unit counters of its own) the integrals over D
     for (int pass = 1; pass <= 2; pass++) {
-      if (pass == 2) {
-        e = fill_u32(a.ctl + 1, n_classes, 0u, st);
-        if (e != hipSuccess) return e;
-      }
       fan_fork(fo, st, n_classes);
       for (int c = 0; c < n_classes; c++) {
         e = launch_mode(a, class_T[c], class_K[c], false, class_item0[c], class_item0[c + 1], c,

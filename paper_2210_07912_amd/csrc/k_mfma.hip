@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(1024) scan_kernel(MfmaArgsT<R> a) {
     a.ctl[0] = (uint32_t)ct;
     a.ctl[kCtlRefine] = 0;
   }
-  if (tid < kMaxClasses) a.ctl[1 + tid] = 0;
+  if (tid < kMaxClasses) a.ctl[1 + tid] = a.ctl[kCtlUnits2 + tid] = 0;
 }
 
 // ---- 3. one record per sample at its (padded) sorted slot; the tiles -----------

@@ -711,7 +711,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   a.bin_unit = (uint32_t *)p;
   if ((s = ws_get(h, W_ITEMUNITS, 4 * (size_t)(ni + 1), &p)) != RIFT_OK) return s;
   a.item_units = (uint32_t *)p;
-  if ((s = ws_get(h, W_CTL, 4 * (1 + kMaxClasses) + 64, &p)) != RIFT_OK) return s;
+  if ((s = ws_get(h, W_CTL, 4 * kCtlWords, &p)) != RIFT_OK) return s;
   a.ctl = (uint32_t *)p;
   a.grid = h->n_cu * 4;
   hipEvent_t e0 = nullptr, e1 = nullptr;

@@ -134,6 +134,32 @@ def test_dmarg_full_size_sampled(ile, orc, which):
     h.close()
 
 
+@pytest.mark.parametrize("n_modes,n_det", [(3, 1), (5, 2), (9, 3), (21, 3)])
+def test_dmarg_small_and_large_calls(ile, n_modes, n_det):
+    """Calls of up to 128 samples per compute unit run forms of one wavefront
+    per SIMD, larger ones of two: the same samples give the same bits on
+    either side of the line, whole tiles or not."""
+    line = 128 * torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng([1700, n_modes])
+    d = dict(synth.make_point(synth.PointSpec(seed=synth.BASE_SEED + 1700, dets=("H1", "L1", "V1")[:n_det], n_modes=2,
+                                              n_t=77, snr=1.0, kernel="none")))
+    lm = [(l, m) for l in range(2, 5) for m in range(-l, l + 1)][:n_modes]
+    d["ell"], d["em"] = (np.array(v, dtype=np.int32) for v in zip(*lm))
+    G = rng.standard_normal((n_det, n_modes, n_modes + 2)) + 1j * rng.standard_normal((n_det, n_modes, n_modes + 2))
+    d["U"] = 100.0 * G @ G.conj().transpose(0, 2, 1) / (n_modes + 2)
+    Q = rng.standard_normal((2, n_det, d["Q"].shape[1], n_modes))
+    d["Q"] = 30.0 * (Q[0] + 1j * Q[1])
+    th = torch.tensor(_samples(d, 701, line + 1), dtype=torch.float32)
+    h = _handle(ile, [d], "fp32")
+    h.set_distance_marginalization(True)
+    _say(f"dmarg M={n_modes} K={n_det} n={line + 1}, {line}, 301")
+    out = h.lnL(th).cpu().numpy()
+    assert np.isfinite(out).any()
+    for lo, hi in ((1, line + 1), (17, 318)):
+        assert np.array_equal(h.lnL(th[:, lo:hi].contiguous()).cpu().numpy(), out[lo:hi], equal_nan=True)
+    h.close()
+
+
 def _oracle_marginalize_dm(orc, pts, seed, counts, rounds, mask, eps):
     """The oracle's adaptive run with distance marginalization: draws of the
     other six parameters (histograms over mask), ln w = ln L_tD + ln ratio,
