@@ -48,9 +48,8 @@ size_t plain_lds_bytes(int elem, int TS, int rows_cap, int nt_cap, bool bwd);
 // ---- FP32 MFMA path -------------------------------------------------------
 constexpr int kMaxT = kMaxModes / 2;  // MFMA steps of 4 elements per detector: M_p / 2
 constexpr int kMaxClasses = 48;  // one persistent launch per distinct (T = Mp / 2, K)
-constexpr int kCtlRefine = 1 + kMaxClasses;  // ctl slot of the refinement count
-constexpr int kCtlScan = 2 + kMaxClasses;    // ctl slot of the points scanned so far
-constexpr int kCtlUnits2 = 3 + kMaxClasses;  // first of the unit counters of a call's second pass over its units
+constexpr int kCtlScan = 1 + kMaxClasses;    // ctl slot of the points scanned so far
+constexpr int kCtlUnits2 = 2 + kMaxClasses;  // first of the unit counters of a call's second pass over its units
 constexpr int kCtlWords = kCtlUnits2 + kMaxClasses;
 constexpr int kNtBuckets = 17;   // autotuner key: floor(log2 n_t) of a class's longest window
 constexpr int kFeedConfigs = 7;  // launch configurations the autotuner measures per class
@@ -126,16 +125,16 @@ struct MfmaArgsT {
   WorkUnit *unit;         // [max_tiles] work units, bins in order, points in order
   uint32_t *bin_unit;     // [n_bins] first unit of the bin within its item
   uint32_t *item_units;   // [n_items + 1] unit prefix over items (filled on device)
-  uint32_t *ctl;          // [0]: number of tiles, [1 + c]: unit counter of class c, then kCtlRefine, kCtlScan,
+  uint32_t *ctl;          // [0]: number of tiles, [1 + c]: unit counter of class c, then kCtlScan,
                           // [kCtlUnits2 + c]: class c's of a second pass
   // adjoint (null in the forward pass)
   const R *gin;           // [stride] upstream d/d ln L_t, or null (= 1)
   R *grad;                // [7][stride] gradient of ln L_t (times gin)
   R *gop;                 // per point [tiles][K][2 Mp][16]: G_k = sum_r c_k[r] Q_k[r] (cop layout)
   R *hop;                 // [tiles][kMaxDet][16]: H_k = sum_j p_j Re(a^dag Qtilde'_k(j))
-  int *jrng;              // [16 max_tiles][4] or null: the samples to refine, appended in any order (count in
-                          // ctl[kCtlRefine]): sorted slot, then the window blocks whose maximum is within
-                          // kRefineNats of the sample's (b0 | b1 << 16, b2 | count << 16)
+  int *jrng;              // [16 max_tiles][2] or null: per sorted slot the window blocks whose maximum is within
+                          // kRefineNats of the sample's, b0 | b1 << 16, b2 | count << 16 (count 0: not refined;
+                          // padding slots are not written)
   // distance marginalization (forward only): a first pass writes each slot's
   // largest window data term, a second integrates over D
   int dmarg;
@@ -204,12 +203,15 @@ inline void fan_join(const Fanout &fo, hipStream_t st, int n_classes) {
 }
 // FP64 re-evaluation of the adjoint over the window blocks that hold each
 // sample's softmax mass (samples whose mass lies in at most kRefineBlocks
-// blocks of 16 window samples, anywhere in the window); overwrites grad and
-// lnL of those samples.  Launched after the
-// chain rule on the same stream.
+// blocks of 16 window samples, anywhere in the window); writes grad and lnL of
+// those samples of class (T, K), points item_lo..item_hi - 1 (tiles: a bound
+// of theirs).  Launched after
+// the FP32 sweep of the class on the same stream; the chain rule then leaves
+// those samples out.
 constexpr int kRefineBlocks = 3;
 constexpr float kRefineNats = 40.f;
-hipError_t refine_backward(const MfmaArgs &a, hipStream_t st);
+hipError_t refine_backward(const MfmaArgs &a, int T, int K, int item_lo, int item_hi, int64_t tiles,
+                           hipStream_t st);
 // the part all share: delay-bin sort, tile records, coefficient pass, work units
 template <typename R>
 hipError_t mfma_prepare(const MfmaArgsT<R> &a, const int *mclass_M, const int *mclass_item0,

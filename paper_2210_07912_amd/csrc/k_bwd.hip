@@ -349,13 +349,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
             const float thr = t1 - kRefD2;
             const int nb = (t2 >= thr ? (t3 >= thr ? 3 : 2) : 1);
             const bool ok = valid && t1 > -3.0e38f && rest < thr && i1 < 65536 && i2 < 65536 && i3 < 65536;
-            if (ok) {
-              const uint32_t r = atomicAdd(&a.ctl[kCtlRefine], 1u);
-              RIFT_GLOBAL int *jo = gpw(a.jrng) + 4 * (size_t)r;
-              jo[0] = (int)(t * kTS + s);
-              jo[1] = i1 | ((nb > 1 ? i2 : 0) << 16);
-              jo[2] = (nb > 2 ? i3 : 0) | (nb << 16);
-            }
+            RIFT_GLOBAL int *jo = gpw(a.jrng) + 2 * ((size_t)t * kTS + s);
+            jo[0] = i1 | ((nb > 1 ? i2 : 0) << 16);
+            jo[1] = ok ? (nb > 2 ? i3 : 0) | (nb << 16) : 0;
           }
           if (a.lnL) gpw(a.lnL)[col] = lt;
           if (a.lnw) gpw(a.lnw)[col] = lt + (a.ln_ratio ? gp(a.ln_ratio)[col] : 0.f);
@@ -382,6 +378,7 @@ __global__ void __launch_bounds__(64) chain_kernel(MfmaArgsT<R> a, int item_lo, 
   const int s = (int)(pos % kTS);
   const SampleRec rec = a.rec[pos];
   if (rec.flag == 0) return;  // padding
+  if (a.jrng && a.jrng[2 * pos + 1] != 0) return;  // refined (k_refine.hip)
   const int it = __builtin_amdgcn_readfirstlane(a.tile_item[t_blk]);
   const int pt = __builtin_amdgcn_readfirstlane(a.items.point[it]);
   const RIFT_CONST PointDev &p = *cp(a.pts + pt);
@@ -576,12 +573,15 @@ hipError_t mfma_backward(const MfmaArgs &a, const int *class_T, const int *class
 #undef RIFT_T_CASE
       default: return hipErrorInvalidValue;
     }
+    int64_t tiles = 0;  // of the runs that the class has points of
+    for (int m = 0; m < n_mclasses; m++)
+      if (mclass_item0[m] < hi && mclass_item0[m + 1] > lo) tiles += mclass_tiles[m];
+    e = refine_backward(a, class_T[c], K, lo, hi, tiles, sc);
+    if (e != hipSuccess) return e;
   }
   fan_join(fo, st, n_classes);
   if (ev1) (void)hipEventRecord(ev1, st);
-  e = chain_launch(a, mclass_M, mclass_item0, mclass_tiles, n_mclasses, st);
-  if (e != hipSuccess) return e;
-  return refine_backward(a, st);
+  return chain_launch(a, mclass_M, mclass_item0, mclass_tiles, n_mclasses, st);
 }
 
 }  // namespace rift

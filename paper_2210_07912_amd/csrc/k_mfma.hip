@@ -296,7 +296,6 @@ __global__ void __launch_bounds__(1024) scan_kernel(MfmaArgsT<R> a) {
     a.item_tiles[0] = 0;
     a.item_units[0] = 0;
     a.ctl[0] = (uint32_t)ct;
-    a.ctl[kCtlRefine] = 0;
   }
   if (tid < kMaxClasses) a.ctl[1 + tid] = a.ctl[kCtlUnits2 + tid] = 0;
 }

@@ -15,19 +15,30 @@
 // the maximum hold all but n_t e^-kRefineNats of the mass, and this kernel
 // redoes the sample over them in FP64 (coefficients, B, the contraction of
 // the rows the blocks need, ell_j, p_j, H_k, c_k, G_k and the chain rule),
-// overwriting its gradient and ln L_t.  Other samples keep the FP32 result:
+// writing its gradient and ln L_t.  Other samples keep the FP32 result:
 // their ell_j come within kRefineNats of the maximum in more than three
 // blocks, so the terms of their sums are comparatively small and so is the
 // rounding.
 //
-// The FP32 sweep appends the samples to refine to a list; one persistent
-// kernel takes them a wavefront per sample.  Lanes over the five angles for the
-// trigonometry, over detectors for the antenna patterns, over modes for the
-// harmonics, over (detector, mode) for a, U a, V a, G_k and the chain rule,
-// over (block, row) for the contraction z_k[r] = Re sum_m conj(a_km) Q_k[r][m]
-// and the transposed interpolation c_k, over (block, window sample) for
-// ell_j, p_j and H_k.  Q is read in the handle's plain layout (FP32 values,
-// exact in FP64).
+// A workgroup takes a tile of 16 sorted samples, a wavefront per detector (all
+// detectors in one wavefront need some 300 registers).  The samples share a
+// delay bin, so the blocks that one of them needs start at the same rows for
+// all, and they mostly need the same ones: the workgroup walks the union of
+// their blocks (2.8 for 12 in all, of 10.5 samples a tile, at the size below),
+// the contraction and G_k = Q_k^T c_k on the FP64 matrix cores as in the FP64
+// path (k_eval64.hip), with Q from the FP32 matrix-core layout (FP32 values,
+// exact in FP64); ell_j is summed over the detectors through LDS.  U and V enter as one real matrix per detector,
+//     W = [Ur + Vr, -Ui - Vi; Ui - Vi, Ur - Vr]   (rows, columns re / im),
+// for which B = 1/4 a^T W a and d ln L / d a = G - 1/2 W a: one more matrix
+// product per tile.  The chain rule is then three complex sums over the modes
+// per detector, sum conj(Y) v, sum conj(dY / d iota) v and sum conj(i m Y) v
+// with v = G - 1/2 W a, each lane over the elements it holds.
+//
+// A wavefront per sample (lanes over rows, modes and window samples, vector
+// FP64, the sums over the wavefront) took 574 us for 1e5 samples at K = 3,
+// M = 21, n_t = 820, by 1540 vector instructions and 87 loads a sample.  This
+// form takes 261 us: matrix products 70 us, vector instructions 77 us, the rest
+// latency at the three wavefronts per SIMD it is compiled for (at two 319 us).
 #include "common.h"
 #include "internal.h"
 #include "mfma_tile.h"
@@ -36,329 +47,406 @@
 
 namespace rift {
 
-constexpr int kRefWaves = 4;
-constexpr int kRefRowsB = kTS + 3;  // rows one window block needs
-static_assert(kRefineBlocks * kRefRowsB <= 64, "one (block, row) per lane");
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d4 __attribute__((ext_vector_type(4)));
 
-// Wave-wide sum / maximum of a double without LDS: butterflies within each
-// 16-lane row by DPP (xor 1, xor 2, half-row mirror, row mirror), then the
-// four row results through scalar registers.  All 64 lanes must be active.
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double lane_d(double x, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
-                          __builtin_amdgcn_readlane(__double2loint(x), l));
-}
-__device__ __forceinline__ double wsum(double v) {
-  v += dpp_d<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-  v += dpp_d<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-  v += dpp_d<0x141>(v);  // row_half_mirror
-  v += dpp_d<0x140>(v);  // row_mirror
-  return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
-}
-__device__ __forceinline__ double wmax(double v) {
-  v = fmax(v, dpp_d<0xB1>(v));
-  v = fmax(v, dpp_d<0x4E>(v));
-  v = fmax(v, dpp_d<0x141>(v));
-  v = fmax(v, dpp_d<0x140>(v));
-  return fmax(fmax(lane_d(v, 0), lane_d(v, 16)), fmax(lane_d(v, 32), lane_d(v, 48)));
+constexpr double kTiny = -60.0;  // nats below the reference where a term is zero
+
+__device__ __forceinline__ double shfl_xor_d(double v, int o) {
+  return __hiloint2double(__shfl_xor(__double2hiint(v), o), __shfl_xor(__double2loint(v), o));
 }
 
-// LDS of one wavefront
-struct RefineWave {
-  double a[kMaxDet * kMaxModes][2];   // a_km
-  double ua[kMaxDet * kMaxModes][2];  // (U a)_km
-  double va[kMaxDet * kMaxModes][2];  // (V a)_km
-  double y[kMaxModes][4];             // Y_m, dY_m / d iota
-  double f[kMaxDet][6];               // F+, Fx, dF/dalpha, dF/ddelta
-  double z[kMaxDet][64];              // z_k, then c_k, at lane (block, row)
-  double p[64];                       // p_j at lane (block, window sample)
-};
-
-// one listed sample: entry ent = (sorted slot, b0 | b1 << 16, b2 | count << 16)
-__device__ __forceinline__ void refine_one(const MfmaArgs &a, RefineWave &W, int lane, int4 ent) {
-  constexpr int MM = kMaxModes;
-  const int nb = ent.z >> 16;
-  if (nb < 1 || nb > kRefineBlocks) return;
-  const int blk[3] = {ent.y & 0xffff, ent.y >> 16, ent.z & 0xffff};
-  const int64_t pos = ent.x;
-  const SampleRec rec = a.rec[pos];
-  if (rec.flag != 1) return;
-  const int it = a.tile_item[pos / kTS];
-  const PointDev &p = a.pts[a.items.point[it]];
-  const int K = p.K, M = p.M, NT = p.n_t, P = p.pad;
-
+template <int T>
+__global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_eu(3))) refine_kernel(MfmaArgs a, int item_lo, int item_hi) {
+  constexpr int U = T / 2, OD = T & 1;   // pairs of instructions; an odd one
+  constexpr int E = 4 * T;               // elements per row
+  constexpr int MT = (E + 15) / 16;      // 16-element tiles of G
+  constexpr int ZB = 32 * kTS;
+  // per wavefront in turn: the rows of the last two blocks [row][sample], its
+  // detector's terms of the window samples, p of the last two blocks, its sums
+  __shared__ double buf_all[kMaxDet * ZB];
+  __shared__ double yt[2 * T][4][kTS];   // Y_m, dY_m / d iota (zero past M)
+  __shared__ double em_sh[2 * T];        // m
+  __shared__ double tg[5][2][kTS];       // sin, cos of alpha - gmst, delta, psi, iota / 2, phi
+  const int lane = threadIdx.x & 63, s = lane & 15, g = lane >> 4;
+  const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), K = blockDim.x >> 6;
+  double *const buf = buf_all + k * ZB;
+  // (one tile per workgroup: in a loop over tiles the compiler keeps the
+  // constants of the FP64 functions in some 100 registers)
+  const uint32_t t = a.item_tiles[item_lo] + blockIdx.x;
+  if (t >= a.item_tiles[item_hi]) return;
+  uint32_t key = __builtin_amdgcn_readfirstlane(a.tile_key[t]);
+  if (key == kNoBin) return;  // the tiles that round a point up to groups of 4
+  const SampleRec rec = a.rec[(size_t)t * kTS + s];
+  RIFT_GLOBAL int *const jr = gpw(a.jrng) + 2 * ((size_t)t * kTS + s);
+  int b01 = 0, b2n = 0;
+  if (rec.flag == 1) {
+    b01 = jr[0];
+    b2n = jr[1];
+  }
+  const int nb = b2n >> 16;
+  const bool on = nb >= 1 && nb <= kRefineBlocks;
+  if (!__any(on)) return;  // the same for the whole workgroup
+  const int it = __builtin_amdgcn_readfirstlane(a.tile_item[t]);
+  const int pt = __builtin_amdgcn_readfirstlane(a.items.point[it]);
+  const RIFT_CONST PointDev &p = *cp(a.pts + pt);
+  const int NT = p.n_t, P = p.pad, M = p.M;
+  const int JB = (NT + 15) >> 4, rem = NT - 16 * (JB - 1);
+  for (int i = 0; i < k; i++) key /= (uint32_t)p.nq;
+  const int lo = __builtin_amdgcn_readfirstlane((int)(key % (uint32_t)p.nq) * p.bin_w - P);
+  const RIFT_GLOBAL float *const qk = gp(p.Qm) + (size_t)(k * p.Lpad + P + lo) * E;
   double th[7];
 #pragma unroll
-  for (int d = 0; d < 7; d++) th[d] = (double)rec.th[d];
-  // sin / cos of alpha - gmst, delta, psi, iota / 2, phi: one lane each
-  double sv = 0.0, cv = 1.0;
-  {
-    const double arg = lane == 0 ? th[RIFT_ALPHA] - p.gmst
-                       : lane == 1 ? th[RIFT_DELTA]
-                       : lane == 2 ? th[RIFT_PSI]
-                       : lane == 3 ? 0.5 * th[RIFT_IOTA]
-                                   : th[RIFT_PHI];
-    if (lane < 5) sincos(arg, &sv, &cv);
-  }
-  SkyTrig tr;
-  tr.sh = lane_d(sv, 0);
-  tr.ch = lane_d(cv, 0);
-  tr.sd = lane_d(sv, 1);
-  tr.cd = lane_d(cv, 1);
-  tr.sp = lane_d(sv, 2);
-  tr.cp = lane_d(cv, 2);
-  const double si = lane_d(sv, 3), ci = lane_d(cv, 3), s1 = lane_d(sv, 4), c1 = lane_d(cv, 4);
-  const double x = p.d_ref / th[RIFT_DIST];
-  // integer row offsets and Catmull-Rom weights per detector (uniform)
-  int nk[kMaxDet];
-  double w[kMaxDet][4], wd[kMaxDet][4];
-  bool ok = isfinite(th[RIFT_TAU]);
-#pragma unroll
-  for (int k = 0; k < kMaxDet; k++) {
-    nk[k] = 0;
-    double mu = 0.0;
-    if (k < K) {
-      const double sk = (th[RIFT_TAU] + delay(p.rc[k], tr)) * p.f_s;
-      const double fl = floor(sk);
-      ok = ok && isfinite(sk) && fl >= -P && fl <= P;
-      nk[k] = ok ? (int)fl : 0;
-      mu = ok ? sk - fl : 0.0;
+  for (int d = 0; d < 7; d++) th[d] = rec.flag == 1 ? (double)rec.th[d] : (d == RIFT_DIST ? 1.0 : 0.0);
+  // an angle per lane group: the first four by the first wavefront, phi by the last
+  for (int i = k == 0 ? 0 : 4; i < (k == K - 1 ? 5 : 4); i += 4) {
+    const int d = i + g;
+    const double arg = d == 0   ? th[RIFT_ALPHA] - p.gmst
+                       : d == 1 ? th[RIFT_DELTA]
+                       : d == 2 ? th[RIFT_PSI]
+                       : d == 3 ? 0.5 * th[RIFT_IOTA]
+                                : th[RIFT_PHI];
+    double sv, cv;
+    sincos(arg, &sv, &cv);
+    if (d < 5) {
+      tg[d][0][s] = sv;
+      tg[d][1][s] = cv;
     }
-    cr_weights<double>(mu, w[k]);
-    cr_dweights<double>(mu, wd[k]);
   }
-  if (!ok) return;
+  __syncthreads();
+  auto trig = [&] {
+    SkyTrig tr;
+    tr.sh = tg[0][0][s];
+    tr.ch = tg[0][1][s];
+    tr.sd = tg[1][0][s];
+    tr.cd = tg[1][1][s];
+    tr.sp = tg[2][0][s];
+    tr.cp = tg[2][1][s];
+    return tr;
+  };
 
-  // ---- antenna patterns (lanes over detectors), harmonics (lanes over modes) ----
-  if (lane < K) {
-    double D[9];
+  // ---- harmonics: 4 K lanes per sample, one mode each --------------------------
+  {
+    const double si = tg[3][0][s], ci = tg[3][1][s], s1 = tg[4][0][s], c1 = tg[4][1][s];
+    const double u = ci * ci, hs = si * ci, hc = 0.5 * (ci * ci - si * si);
+#pragma unroll 1
+    for (int m = 4 * k + g; m < 2 * T; m += 4 * K) {
+      // Y = s^par P(u) e^{i m phi}, s = sin(iota) / 2, u = cos^2(iota / 2)
+      // (the whole row of coefficients, zero past the degree, in one go)
+      const int mc = min(m, M - 1), par = p.hpar[mc], em = p.em[mc];
+      double h[kMaxHDeg + 1], P1 = 0.0, dP = 0.0, cr, cim;
 #pragma unroll
-    for (int i = 0; i < 9; i++) D[i] = p.D[lane][i];
-    double Fp, Fc, dFa[2], dFd[2];
-    antenna(D, tr, Fp, Fc, dFa, dFd);
-    W.f[lane][0] = Fp;
-    W.f[lane][1] = Fc;
-    W.f[lane][2] = dFa[0];
-    W.f[lane][3] = dFa[1];
-    W.f[lane][4] = dFd[0];
-    W.f[lane][5] = dFd[1];
-  }
-  const double u = ci * ci, hs = si * ci, hc = 0.5 * (ci * ci - si * si);
-  for (int m = lane; m < M; m += 64) {
-    // Y = s^par P(u) e^{i m phi}, s = sin(iota) / 2, u = cos^2(iota / 2)
-    const int deg = p.hdeg[m];
-    double Pv = p.hpoly[m][deg], dP = 0.0;
-    for (int j = deg - 1; j >= 0; j--) {
-      dP = fma(dP, u, Pv);
-      Pv = fma(Pv, u, p.hpoly[m][j]);
+      for (int j = 0; j <= kMaxHDeg; j++) h[j] = p.hpoly[mc][j];
+#pragma unroll
+      for (int j = kMaxHDeg; j >= 0; j--) {
+        dP = fma(dP, u, P1);
+        P1 = fma(P1, u, h[j]);
+      }
+      double y = par ? hs * P1 : P1, dy = par ? hc * P1 - hs * hs * dP : -hs * dP;
+      if (m >= M) y = dy = 0.0;
+      phase_m(em, c1, s1, cr, cim);
+      yt[m][0][s] = y * cr;
+      yt[m][1][s] = y * cim;
+      yt[m][2][s] = dy * cr;
+      yt[m][3][s] = dy * cim;
+      if (s == 0) em_sh[m] = (double)em;
     }
-    double y, dy;
-    if (p.hpar[m]) {
-      y = hs * Pv;
-      dy = hc * Pv - hs * hs * dP;
-    } else {
-      y = Pv;
-      dy = -hs * dP;
-    }
-    const int em = p.em[m], am = em < 0 ? -em : em;
-    double cr = 1.0, cim = 0.0;
-    for (int q = 0; q < am; q++) {
-      const double nr = cr * c1 - cim * s1;
-      cim = cr * s1 + cim * c1;
-      cr = nr;
-    }
-    if (em < 0) cim = -cim;
-    W.y[m][0] = y * cr;
-    W.y[m][1] = y * cim;
-    W.y[m][2] = dy * cr;
-    W.y[m][3] = dy * cim;
   }
-  wave_sync();
-  // ---- a_km = x F_k Y_m ----
-  for (int l = lane; l < K * M; l += 64) {
-    const int k = l / M, m = l - k * M;
-    const double Fp = W.f[k][0], Fc = W.f[k][1], yr = W.y[m][0], yi = W.y[m][1];
-    W.a[k * MM + m][0] = x * (Fp * yr - Fc * yi);
-    W.a[k * MM + m][1] = x * (Fp * yi + Fc * yr);
+  double D[9], rc[3];
+#pragma unroll
+  for (int i = 0; i < 9; i++) D[i] = p.D[k][i];
+#pragma unroll
+  for (int i = 0; i < 3; i++) rc[i] = p.rc[k][i];
+  double xr, xi;
+  {
+    double Fp, Fc;
+    antenna(D, trig(), Fp, Fc);
+    const double x = on ? p.d_ref / th[RIFT_DIST] : 0.0;
+    xr = x * Fp;
+    xi = x * Fc;
   }
-  wave_sync();
-  // ---- (U a)_km, (V a)_km and B = 1/4 sum_k [a^dag U a + Re(a^T V a)] ----
-  double bpart = 0.0;
-  for (int l = lane; l < K * M; l += 64) {
-    const int k = l / M, m = l - k * M;
-    const double *U = p.U + ((size_t)k * M + m) * M * 2;
-    double ur = 0.0, ui = 0.0, vr = 0.0, vi = 0.0;
-    for (int mp = 0; mp < M; mp++) {
-      const double br = W.a[k * MM + mp][0], bi = W.a[k * MM + mp][1];
-      ur = fma(U[2 * mp], br, fma(-U[2 * mp + 1], bi, ur));
-      ui = fma(U[2 * mp], bi, fma(U[2 * mp + 1], br, ui));
+  const int n = on ? (int)gp(a.rec)[(size_t)t * kTS + s].n[k] : lo;
+  double w[4], wd[4];
+  {
+    const double mu = on ? (th[RIFT_TAU] + delay(rc, trig())) * p.f_s - (double)n : 0.0;
+    cr_weights<double>(mu, w);
+    cr_dweights<double>(mu, wd);
+  }
+  const int sh = min(max(n - lo, 0), kBinW - 1);  // a tile's samples are of its bin
+  __syncthreads();  // the harmonics
+
+  // sum over the elements of a row operand times a_km = x F_k Y_m:
+  // instructions 2 u + i take element 8 u + 2 g + i, the odd last one 8 U + g
+  auto contract = [&](auto even, auto odd_last) {
+    d4 c = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const double yr = yt[4 * u + g][0][s], yi = yt[4 * u + g][1][s];
+      double qr, qi;
+      even(u, qr, qi);
+      c = __builtin_amdgcn_mfma_f64_16x16x4f64(qr, fma(xr, yr, -xi * yi), c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f64_16x16x4f64(qi, fma(xr, yi, xi * yr), c, 0, 0, 0);
+    }
+    if constexpr (OD) {
+      const double yr = yt[4 * U + (g >> 1)][0][s], yi = yt[4 * U + (g >> 1)][1][s];
+      c = __builtin_amdgcn_mfma_f64_16x16x4f64(odd_last(), (g & 1) ? fma(xr, yi, xi * yr) : fma(xr, yr, -xi * yi), c,
+                                               0, 0, 0);
+    }
+    return c;
+  };
+  const int arow = s * E + 2 * g, atail = s * E + 8 * U + g;
+  f2 A[U > 0 ? U : 1];
+  float At = 0.f;
+  auto rows = [&](int b) {  // row block b's operands
+    const RIFT_GLOBAL float *q = qk + (size_t)(16 * b) * E;
+#pragma unroll
+    for (int u = 0; u < U; u++) A[u] = *(const RIFT_GLOBAL f2 *)(q + 8 * u + arow);
+    if constexpr (OD) At = q[atail];
+  };
+  auto product = [&] {
+    return contract(
+        [&](int u, double &qr, double &qi) {
+          qr = (double)A[u][0];
+          qi = (double)A[u][1];
+        },
+        [&] { return (double)At; });
+  };
+  auto put = [&](const d4 &z, int row) {  // register i of lane group g: row 4 i + g
+#pragma unroll
+    for (int i = 0; i < 4; i++) buf[16 * (row + 4 * i + g) + s] = z[i];
+  };
+
+  // ---- the blocks that any of the samples needs, in ascending order -----------
+  d4 acc = {0.0, 0.0, 0.0, 0.0}, gacc[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; mt++) gacc[mt] = d4{0.0, 0.0, 0.0, 0.0};
+  double m_ref = 0.0, s_run = 0.0, hsum = 0.0, pp[4] = {0.0, 0.0, 0.0, 0.0};
+  // G_k += Q_k^T c_k over row block rb, with p of window blocks rb - 1 (pa)
+  // and rb (pb).  Instruction q takes rows 4 g + q, element 16 mt + s (past
+  // the last element: the next row's, of results that are not used).
+  float qv[4][MT];
+  auto grows = [&](int rb) {
+    const RIFT_GLOBAL float *qr = qk + (size_t)(16 * rb + 4 * g) * E + s;
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+#pragma unroll
+      for (int mt = 0; mt < MT; mt++) qv[q][mt] = qr[q * E + 16 * mt];
+  };
+  auto gproduct = [&](const double (&pa)[4], const double (&pb)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      buf[16 * (4 * g + i) + s] = pa[i];
+      buf[16 * (16 + 4 * g + i) + s] = pb[i];
+    }
+    wave_sync();
+    const double *pr = buf + 16 * (13 + 4 * g - sh) + s;  // p of row 16 rb + 4 g, tap 3
+    double pv[7], c[4];
+#pragma unroll
+    for (int o = 0; o < 7; o++) pv[o] = pr[16 * o];
+#pragma unroll
+    for (int q = 0; q < 4; q++) c[q] = w[0] * pv[q + 3] + w[1] * pv[q + 2] + w[2] * pv[q + 1] + w[3] * pv[q];
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+#pragma unroll
+      for (int mt = 0; mt < MT; mt++)
+        gacc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qv[q][mt], c[q], gacc[mt], 0, 0, 0);
+    wave_sync();
+  };
+  const double none[4] = {0.0, 0.0, 0.0, 0.0};
+  int cand = 0x7fffffff;
+  if (on && g < nb) cand = g == 0 ? b01 & 0xffff : g == 1 ? (int)((uint32_t)b01 >> 16) : b2n & 0xffff;
+  int last = -2;
+  for (;;) {
+    const int c = __builtin_amdgcn_readfirstlane(wave_min(cand > last ? cand : 0x7fffffff));
+    if (c >= JB) break;  // no further one
+    if (c != last + 1) {
+      rows(c);
+      if (last >= 0) {
+        grows(last + 1);
+        gproduct(pp, none);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; i++) pp[i] = 0.0;
+      acc = product();
+    }
+    rows(c + 1);
+    put(acc, 0);
+    acc = product();
+    put(acc, 16);
+    grows(c);
+    wave_sync();
+    double z[7], ell[4], zd[4];
+#pragma unroll
+    for (int o = 0; o < 7; o++) z[o] = buf[16 * (4 * g + sh + o) + s];
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      buf[64 * i + lane] = w[0] * z[i] + w[1] * z[i + 1] + w[2] * z[i + 2] + w[3] * z[i + 3];
+      zd[i] = wd[0] * z[i] + wd[1] * z[i + 1] + wd[2] * z[i + 2] + wd[3] * z[i + 3];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; i++) ell[i] = -m_ref;
+#pragma unroll
+    for (int kk = 0; kk < kMaxDet; kk++)
+      if (kk < K)
+#pragma unroll
+        for (int i = 0; i < 4; i++) ell[i] += buf_all[kk * ZB + 64 * i + lane];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      if (!on || (c == JB - 1 && 4 * g + i >= rem)) ell[i] = -INFINITY;
+    // the reference of a sample: moved when a block exceeds it by 64
+    double cmax = fmax(fmax(ell[0], ell[1]), fmax(ell[2], ell[3]));
+    cmax = fmax(cmax, shfl_xor_d(cmax, 16));
+    cmax = fmax(cmax, shfl_xor_d(cmax, 32));
+    if ((last < 0 || cmax > 64.0) && cmax > -INFINITY) {
+      const double f = last < 0 ? 0.0 : exp(-cmax);
+      s_run *= f;
+      hsum *= f;
+#pragma unroll
+      for (int i = 0; i < 4; i++) pp[i] *= f;
+#pragma unroll
+      for (int mt = 0; mt < MT; mt++) gacc[mt] *= f;
+      m_ref += cmax;
+#pragma unroll
+      for (int i = 0; i < 4; i++) ell[i] -= cmax;
+    }
+    double pj[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) pj[i] = ell[i] <= kTiny ? 0.0 : exp(ell[i]);  // (a NaN reaches the sums)
+    s_run += (pj[0] + pj[1]) + (pj[2] + pj[3]);
+#pragma unroll
+    for (int i = 0; i < 4; i++) hsum = fma(pj[i], zd[i], hsum);
+    gproduct(pp, pj);
+#pragma unroll
+    for (int i = 0; i < 4; i++) pp[i] = pj[i];
+    last = c;
+  }
+  if (last >= 0) {
+    grows(last + 1);
+    gproduct(pp, none);
+  }
+  s_run += shfl_xor_d(s_run, 16);
+  s_run += shfl_xor_d(s_run, 32);
+  const double inv = 1.0 / s_run;
+
+  // ---- v = G - 1/2 W a, the sums of the chain rule -----------------------------
+  double s0r = 0.0, s0i = 0.0, s1r = 0.0, s1i = 0.0, s2r = 0.0, s2i = 0.0, sbr = 0.0, sbi = 0.0;
+#pragma unroll
+  for (int mt = 0; mt < MT; mt++) {
+    // W a of elements 16 mt + ...: this lane's row of W is 16 mt + s, its
+    // columns the two of the instructions' modes (a is zero past M, and
+    // results past 2 M are not used: indices are clamped)
+    const bool odd = (s & 1) != 0;
+    const size_t urow = ((size_t)k * M + min(8 * mt + (s >> 1), M - 1)) * M;
+    wave_sync();  // (the harmonics read again for each tile of rows, not kept)
+    __builtin_amdgcn_sched_barrier(0);
+    d2 W[U + OD];
+    auto mode = [&](int u) { return min(u < U ? 4 * u + g : 4 * U + (g >> 1), M - 1); };
+#pragma unroll
+    for (int u = 0; u < U + OD; u++) {
+      const d2 v = *(const RIFT_GLOBAL d2 *)(gp(p.U) + 2 * (urow + mode(u)));
+      W[u] = odd ? d2{v[1], v[0]} : d2{v[0], -v[1]};
     }
     if (p.V) {
-      const double *V = p.V + ((size_t)k * M + m) * M * 2;
-      for (int mp = 0; mp < M; mp++) {
-        const double br = W.a[k * MM + mp][0], bi = W.a[k * MM + mp][1];
-        vr = fma(V[2 * mp], br, fma(-V[2 * mp + 1], bi, vr));
-        vi = fma(V[2 * mp], bi, fma(V[2 * mp + 1], br, vi));
-      }
-    }
-    W.ua[k * MM + m][0] = ur;
-    W.ua[k * MM + m][1] = ui;
-    W.va[k * MM + m][0] = vr;
-    W.va[k * MM + m][1] = vi;
-    const double ar = W.a[k * MM + m][0], ai = W.a[k * MM + m][1];
-    bpart += ar * ur + ai * ui + ar * vr - ai * vi;
-  }
-  const double B = 0.25 * wsum(bpart);
-
-  // ---- z_k at lane (block i, row r): Q row P + 16 blk[i] + n_k + r ----
-  const float *Qf = (const float *)p.Q;
-  const int ib = lane / kRefRowsB, rr = lane - ib * kRefRowsB;
-  const bool row_on = ib < nb;
-  const int row0 = row_on ? P + kTS * blk[ib < 3 ? ib : 0] + rr : 0;
 #pragma unroll
-  for (int k = 0; k < kMaxDet; k++) {
-    if (k < K) {
-      double z = 0.0;
-      if (row_on) {
-        const float *q = Qf + ((size_t)k * p.Lpad + (row0 + nk[k])) * M * 2;
-        for (int m = 0; m < M; m++)
-          z = fma(W.a[k * MM + m][0], (double)q[2 * m], fma(W.a[k * MM + m][1], (double)q[2 * m + 1], z));
+      for (int u = 0; u < U + OD; u++) {
+        const d2 v = *(const RIFT_GLOBAL d2 *)(gp(p.V) + 2 * (urow + mode(u)));
+        W[u] -= odd ? d2{v[1], v[0]} : d2{-v[0], v[1]};
       }
-      W.z[k][lane] = z;
+    }
+    const d4 wa = contract(
+        [&](int u, double &wre, double &wim) {
+          wre = W[u][0];
+          wim = W[u][1];
+        },
+        [&] { return (g & 1) ? W[U + OD - 1][1] : W[U + OD - 1][0]; });
+    wave_sync();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      if (16 * mt + 4 * i >= E) continue;
+      const int m = 8 * mt + 2 * i + (g >> 1);  // element 16 mt + 4 i + g
+      const double v = gacc[mt][i] * inv - 0.5 * wa[i];
+      // v (even g) or i v (odd g) times conj(Y): (p, q) = (Yr, -Yi) or (Yi, Yr)
+      const double yr = yt[m][0][s], yi = yt[m][1][s], dr = yt[m][2][s], di = yt[m][3][s];
+      const double yp = (g & 1) ? yi : yr, yq = (g & 1) ? yr : -yi;
+      const double dp = (g & 1) ? di : dr, dq = (g & 1) ? dr : -di;
+      const double em = em_sh[m];
+      s0r = fma(yp, v, s0r);
+      s0i = fma(yq, v, s0i);
+      s1r = fma(dp, v, s1r);
+      s1i = fma(dq, v, s1i);
+      s2r = fma(em * yq, v, s2r);  // conj(i m Y) = -i m conj(Y)
+      s2i = fma(-em * yp, v, s2i);
+      sbr = fma(yp, wa[i], sbr);
+      sbi = fma(yq, wa[i], sbi);
     }
   }
+  // this detector's parts: Re(conj(x F) S), F = Fp + i Fc; B in out[7]
+  // (the distance and the angles read again, not kept through the blocks)
   wave_sync();
-
-  // ---- ell_j, p_j, ln L_t, H_k at lane (block i, window sample jj) ----
-  const int jb = lane >> 4, jj = lane & 15;
-  const int jw = jb < nb ? kTS * blk[jb < 3 ? jb : 0] + jj : NT;  // window index
-  const bool win_on = jb < nb && jw < NT;
-  double ell = -INFINITY, dk[kMaxDet] = {0.0, 0.0, 0.0};
-  if (win_on) {
-    ell = -B;
-#pragma unroll
-    for (int k = 0; k < kMaxDet; k++) {
-      if (k < K) {
-        const double *z = &W.z[k][jb * kRefRowsB + jj];
-        ell += w[k][0] * z[0] + w[k][1] * z[1] + w[k][2] * z[2] + w[k][3] * z[3];
-        dk[k] = wd[k][0] * z[0] + wd[k][1] * z[1] + wd[k][2] * z[2] + wd[k][3] * z[3];
-      }
-    }
-  }
-  const double mx = wmax(ell);
-  const double e = win_on ? exp(ell - mx) : 0.0;
-  const double S = wsum(e);
-  const double pj = e / S;
-  const double lnLt = mx + log(S) - log((double)NT);
-  double Hk[kMaxDet];
-#pragma unroll
-  for (int k = 0; k < kMaxDet; k++) Hk[k] = k < K ? wsum(pj * dk[k]) : 0.0;
-  W.p[lane] = pj;
-  wave_sync();
-  // ---- c_k at lane (block i, row r) = sum_q w_q p_(i, r - q) (overwrites z) ----
-#pragma unroll
-  for (int k = 0; k < kMaxDet; k++) {
-    if (k < K) {
-      double c = 0.0;
-      if (row_on) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const int j = rr - q;
-          if (j >= 0 && j < kTS) c = fma(w[k][q], W.p[ib * kTS + j], c);
-        }
-      }
-      W.z[k][lane] = c;
-    }
-  }
-  wave_sync();
-
-  // ---- G_km = sum over (block, row) c_k Q_k[row][m], then the chain rule ----
-  double out[7] = {0, 0, 0, 0, 0, 0, 0};
-  for (int l = lane; l < K * M; l += 64) {
-    const int k = l / M, m = l - k * M;
-    const int nkk = k == 0 ? nk[0] : k == 1 ? nk[1] : nk[2];
-    double Gr = 0.0, Gi = 0.0;
-    for (int i = 0; i < nb; i++) {
-      const int bi = i == 0 ? blk[0] : i == 1 ? blk[1] : blk[2];
-      const float *q = Qf + ((size_t)k * p.Lpad + (P + kTS * bi + nkk)) * M * 2 + 2 * m;
-      for (int r = 0; r < kRefRowsB; r++) {
-        const double c = W.z[k][i * kRefRowsB + r];
-        Gr = fma(c, (double)q[(size_t)r * M * 2], Gr);
-        Gi = fma(c, (double)q[(size_t)r * M * 2 + 1], Gi);
-      }
-    }
-    const double Fp = W.f[k][0], Fc = W.f[k][1];
-    const double dFa0 = W.f[k][2], dFa1 = W.f[k][3], dFd0 = W.f[k][4], dFd1 = W.f[k][5];
-    const double yr = W.y[m][0], yi = W.y[m][1], dyr = W.y[m][2], dyi = W.y[m][3];
-    const double er = Gr - 0.5 * W.ua[k * MM + m][0], ei = Gi - 0.5 * W.ua[k * MM + m][1];
-    const double var = W.va[k * MM + m][0], vai = W.va[k * MM + m][1];
-    auto contrib = [&](double dar, double dai) { return dar * er + dai * ei - 0.5 * (dar * var - dai * vai); };
-    out[RIFT_ALPHA] += contrib(x * (dFa0 * yr - dFa1 * yi), x * (dFa0 * yi + dFa1 * yr));
-    out[RIFT_DELTA] += contrib(x * (dFd0 * yr - dFd1 * yi), x * (dFd0 * yi + dFd1 * yr));
-    const double Fpr = 2.0 * Fc, Fpi = -2.0 * Fp;  // dF / dpsi = -2 i F
-    out[RIFT_PSI] += contrib(x * (Fpr * yr - Fpi * yi), x * (Fpr * yi + Fpi * yr));
-    out[RIFT_IOTA] += contrib(x * (Fp * dyr - Fc * dyi), x * (Fp * dyi + Fc * dyr));
-    const double iyr = -p.em[m] * yi, iyi = p.em[m] * yr;
-    out[RIFT_PHI] += contrib(x * (Fp * iyr - Fc * iyi), x * (Fp * iyi + Fc * iyr));
-    const double ar = W.a[k * MM + m][0], ai = W.a[k * MM + m][1];
-    out[RIFT_DIST] += contrib(-ar / th[RIFT_DIST], -ai / th[RIFT_DIST]);
-  }
-#pragma unroll
-  for (int d = 0; d < 6; d++) out[d] = wsum(out[d]);
+  const double dist = rec.flag == 1 ? (double)gp(a.rec)[(size_t)t * kTS + s].th[RIFT_DIST] : 1.0, x = p.d_ref / dist;
+  const SkyTrig tr = trig();
+  double out[8], Fp, Fc, dFa[2], dFd[2];
+  antenna(D, tr, Fp, Fc, dFa, dFd);
+  auto re = [&](double fr, double fi, double sr, double s_i) { return x * (fr * sr + fi * s_i); };
   // arrival times: f_s H_k d(dt_k) / d(alpha, delta) and f_s H_k for tau
-  const double dn_a[3] = {-tr.cd * tr.sh, tr.cd * tr.ch, 0.0};
-  const double dn_d[3] = {-tr.sd * tr.ch, -tr.sd * tr.sh, tr.cd};
+  const double H = hsum * inv * p.f_s;
+  out[RIFT_ALPHA] = re(dFa[0], dFa[1], s0r, s0i) - H * (rc[0] * (-tr.cd * tr.sh) + rc[1] * (tr.cd * tr.ch));
+  out[RIFT_DELTA] =
+      re(dFd[0], dFd[1], s0r, s0i) - H * (rc[0] * (-tr.sd * tr.ch) + rc[1] * (-tr.sd * tr.sh) + rc[2] * tr.cd);
+  out[RIFT_PSI] = re(2.0 * Fc, -2.0 * Fp, s0r, s0i);  // dF / dpsi = -2 i F
+  out[RIFT_IOTA] = re(Fp, Fc, s1r, s1i);
+  out[RIFT_PHI] = re(Fp, Fc, s2r, s2i);
+  out[RIFT_DIST] = -re(Fp, Fc, s0r, s0i) / dist;
+  out[RIFT_TAU] = H;
+  out[7] = 0.25 * re(Fp, Fc, sbr, sbi);
 #pragma unroll
-  for (int k = 0; k < kMaxDet; k++) {
-    if (k < K) {
-      const double ddt_a = -(p.rc[k][0] * dn_a[0] + p.rc[k][1] * dn_a[1] + p.rc[k][2] * dn_a[2]);
-      const double ddt_d = -(p.rc[k][0] * dn_d[0] + p.rc[k][1] * dn_d[1] + p.rc[k][2] * dn_d[2]);
-      out[RIFT_ALPHA] += Hk[k] * p.f_s * ddt_a;
-      out[RIFT_DELTA] += Hk[k] * p.f_s * ddt_d;
-      out[RIFT_TAU] += Hk[k] * p.f_s;
+  for (int d = 0; d < 8; d++) {
+    out[d] += shfl_xor_d(out[d], 16);
+    out[d] += shfl_xor_d(out[d], 32);
+    if (g == 0) buf[16 * d + s] = out[d];
+  }
+  __syncthreads();
+  if (k == 0 && on && g == 0) {
+#pragma unroll
+    for (int d = 0; d < 8; d++) {
+      out[d] = buf_all[16 * d + s];
+      if (K > 1) out[d] += buf_all[ZB + 16 * d + s];
+      if (K > 2) out[d] += buf_all[2 * ZB + 16 * d + s];
+    }
+    const double lt = m_ref + log(s_run) - log((double)NT) - out[7];
+    if (isfinite(lt)) {
+      const int64_t col = rec.col;
+      const double gi = a.gin ? (double)gp(a.gin)[col] : 1.0;
+#pragma unroll
+      for (int d = 0; d < 7; d++) gpw(a.grad)[d * a.stride + col] = (float)(gi * out[d]);
+      if (a.lnL) gpw(a.lnL)[col] = (float)lt;
+    } else {
+      jr[1] = 0;  // left to the chain rule of the FP32 sweep
     }
   }
-  if (lane == 0 && isfinite(lnLt)) {
-    const int64_t col = rec.col;
-    const double gi = a.gin ? (double)a.gin[col] : 1.0;
-#pragma unroll
-    for (int d = 0; d < 7; d++) a.grad[d * a.stride + col] = (float)(gi * out[d]);
-    if (a.lnL) a.lnL[col] = (float)lnLt;
-  }
 }
 
-// persistent: wavefront w takes list entries w, w + (all wavefronts), ...
-__global__ void __launch_bounds__(64 * kRefWaves) refine_bwd_kernel(MfmaArgs a) {
-  __shared__ RefineWave sw[kRefWaves];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t n = a.ctl[kCtlRefine];
-  const uint32_t stride = gridDim.x * kRefWaves;
-  for (uint32_t i = blockIdx.x * kRefWaves + wave; i < n; i += stride) {
-    const int4 e = ((const int4 *)a.jrng)[i];
-    refine_one(a, sw[wave], lane, e);
-    wave_sync();  // the next entry reuses the wavefront's LDS
-  }
+template <int T>
+static void launch_refine(const MfmaArgs &a, int K, int lo, int hi, int64_t tiles, hipStream_t st) {
+  hipLaunchKernelGGL((refine_kernel<T>), dim3((unsigned)tiles), dim3(64 * K), 0, st, a, lo, hi);
 }
 
-hipError_t refine_backward(const MfmaArgs &a, hipStream_t st) {
-  if (a.total <= 0 || !a.jrng) return hipSuccess;
-  static int per_cu = 0;
-  if (per_cu == 0) {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, refine_bwd_kernel, 64 * kRefWaves, 0) != hipSuccess || nb < 1)
-      nb = 1;
-    per_cu = nb;
+hipError_t refine_backward(const MfmaArgs &a, int T, int K, int lo, int hi, int64_t tiles, hipStream_t st) {
+  if (a.total <= 0 || tiles <= 0 || !a.jrng) return hipSuccess;
+  switch (T) {
+#define RIFT_T_CASE(TT) \
+  case TT: launch_refine<TT>(a, K, lo, hi, tiles, st); break;
+    RIFT_T_CASE(1) RIFT_T_CASE(2) RIFT_T_CASE(3) RIFT_T_CASE(4) RIFT_T_CASE(5) RIFT_T_CASE(6) RIFT_T_CASE(7)
+    RIFT_T_CASE(8) RIFT_T_CASE(9) RIFT_T_CASE(10) RIFT_T_CASE(11) RIFT_T_CASE(12) RIFT_T_CASE(13)
+    RIFT_T_CASE(14) RIFT_T_CASE(15) RIFT_T_CASE(16)
+#undef RIFT_T_CASE
+    default: return hipErrorInvalidValue;
   }
-  // a.grid is 4 workgroups per compute unit
-  const int64_t slots = (int64_t)a.max_tiles * kTS;
-  const int64_t want = (slots + kRefWaves - 1) / kRefWaves;
-  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)(a.grid / 4) * per_cu)));
-  hipLaunchKernelGGL(refine_bwd_kernel, grid, dim3(64 * kRefWaves), 0, st, a);
   return hipGetLastError();
 }
 

@@ -688,7 +688,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
     if ((s = ws_get(h, W_HOP, sizeof(R) * kMaxDet * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
     a.hop = (R *)p;
     if (h->refine && sizeof(R) == 4) {
-      if ((s = ws_get(h, W_JRNG, 4 * sizeof(int) * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
+      if ((s = ws_get(h, W_JRNG, 2 * sizeof(int) * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
       a.jrng = (int *)p;
     }
     a.gin = gin;

@@ -763,6 +763,54 @@ def test_lnL_with_V(ile, orc):
             assert np.all(np.abs(out - ref) <= 1e-9 * (1 + np.abs(ref)))
 
 
+@pytest.mark.parametrize("M,K,n_t,n,v", [
+    (1, 1, 1, 1, False), (2, 3, 16, 17, True), (3, 2, 17, 40, False), (4, 1, 32, 16, True), (6, 3, 33, 100, False),
+    (7, 2, 47, 33, True), (9, 3, 48, 300, False), (11, 1, 48, 65, False), (13, 3, 40, 64, True), (15, 2, 31, 90, False),
+    (17, 3, 48, 130, False), (20, 1, 45, 31, True), (21, 3, 48, 200, True), (23, 2, 16, 50, False),
+    (25, 3, 48, 70, False), (28, 2, 37, 48, True), (30, 3, 48, 80, False), (32, 3, 48, 60, True), (21, 3, 400, 120, False)])
+def test_refined_adjoint_shapes(ile, orc, M, K, n_t, n, v):
+    """The FP64 refinement of the FP32 adjoint at every group count of the
+    modes, with and without V: windows of at most three blocks of 16 (every
+    sample is refined, over one to three neighbouring blocks), and a long one
+    with a loud spike 200 samples after another (blocks far apart).  Refined
+    results differ from FP64 by their rounding to FP32: 2^-24 of each
+    component, taken here as 5e-7 of the sample's largest one."""
+    rng = np.random.default_rng([93, M, K, n_t])
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1500 + M, dets=("H1", "L1", "V1")[:K], n_modes=2, n_t=n_t, snr=1.0,
+                           kernel="none")
+    d = dict(synth.make_point(spec))
+    lm = [(l, m) for l in range(2, 9) for m in range(-l, l + 1)]
+    pick = rng.choice(len(lm), M, replace=False)
+    d["ell"] = np.array([lm[i][0] for i in pick], dtype=np.int32)
+    d["em"] = np.array([lm[i][1] for i in pick], dtype=np.int32)
+    L = d["Q"].shape[1]
+    G = rng.standard_normal((K, M, M + 2)) + 1j * rng.standard_normal((K, M, M + 2))
+    d["U"] = 100.0 * G @ G.conj().transpose(0, 2, 1) / (M + 2)
+    d["Q"] = 30.0 * (rng.standard_normal((K, L, M)) + 1j * rng.standard_normal((K, L, M)))
+    if n_t > 48:
+        c = np.arange(L) - L // 2
+        d["Q"] = d["Q"] * (0.01 + 20.0 * (np.exp(-0.02 * (c + 100.0) ** 2) + np.exp(-0.02 * (c - 100.0) ** 2)))[None, :, None]
+    if v:
+        V = rng.standard_normal((K, M, M)) + 1j * rng.standard_normal((K, M, M))
+        d["V"] = 5.0 * (V + V.transpose(0, 2, 1))
+    th = synth.mixed_samples(d, 34, n).astype(np.float32).astype(np.float64)
+    p = orc.Point.from_dict(d, complex64=True)
+    lt, g = orc.grad(p, th)
+    h = _handle(ile, [d], "fp32")
+    _say(f"refined adjoint M={M} K={K} n_t={n_t} n={n} V={v}")
+    gg, lg = h.backward(torch.tensor(th, dtype=torch.float32), want_lnL=True)
+    gg, lg = gg.cpu().numpy().astype(np.float64), lg.cpu().numpy().astype(np.float64)
+    h.close()
+    ug, ur = _consistent(gg, th, spec.f_s), _consistent(g, th, spec.f_s)
+    rel = (np.abs(ug - ur) / np.abs(ur).max(axis=0)).max(axis=0)
+    if n_t <= 48:
+        assert rel.max() <= 5e-7, rel.max()
+        assert np.all(np.abs(lg - lt) <= 1e-7 * (1 + np.abs(lt)))
+    else:
+        assert (rel <= 5e-7).mean() > 0.5, np.sort(rel)
+        assert rel.max() <= GRAD_REL
+
+
 def test_high_l_modes(ile, orc):
     """Modes up to the largest degree the library accepts (l = 8), through the
     coefficient pass and chain rule (polynomial harmonic tables): ln L_t for
