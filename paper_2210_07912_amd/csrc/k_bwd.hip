@@ -190,6 +190,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
     // scaled by 2^(m_ref - m_new).  At the end all of them are divided by the
     // sum of p, which also gives ln L_t.
     float s_run = 0.f;
+    // A block whose maximum is kNoMass (base 2) below the reference of every
+    // sample of the tile has no part in the sums, which are at least 1: no
+    // exponentials and, with the block before it, no second product (n_t terms
+    // of 2^-60 are far under an FP32 rounding)
+    constexpr float kNoMass = -60.f;
+    bool any_prev = false;
     // Where the window's mass lies (for the FP64 refinement): the three
     // largest block maxima (t1 >= t2 >= t3, blocks i1, i2, i3) and the
     // largest maximum of every other block (rest)
@@ -282,21 +288,27 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
             m_ref += cmax;
 #pragma unroll
             for (int i = 0; i < 4; i++) ell[i] -= cmax;
+            cmax = 0.f;
           }
-          float pj[4];
+          // (a NaN window value, of an overflowing sample, must reach the sums)
+          const bool any = __any(!(cmax <= kNoMass));
+          float pj[4] = {0.f, 0.f, 0.f, 0.f};
+          if (any) {
 #pragma unroll
-          for (int i = 0; i < 4; i++) pj[i] = __builtin_amdgcn_exp2f(ell[i]);
+            for (int i = 0; i < 4; i++) pj[i] = __builtin_amdgcn_exp2f(ell[i]);
 #pragma unroll
-          for (int i = 0; i < 4; i++) s_run += pj[i];
+            for (int i = 0; i < 4; i++) s_run += pj[i];
 #pragma unroll
-          for (int k = 0; k < K; k++)
+            for (int k = 0; k < K; k++)
 #pragma unroll
-            for (int i = 0; i < 4; i++) hsum[k] = fmaf(pj[i], zd[k][i], hsum[k]);
+              for (int i = 0; i < 4; i++) hsum[k] = fmaf(pj[i], zd[k][i], hsum[k]);
+          }
           float *pw = pr + 16 * (c & 1) + 4 * g;
           *(f4 *)pw = f4{pj[0], pj[1], pj[2], pj[3]};
           if ((c & 1) == 0) *(f4 *)(pw + 32) = f4{pj[0], pj[1], pj[2], pj[3]};
           wave_sync();
-          gproduct(c);
+          if (any || any_prev) gproduct(c);
+          any_prev = any;
         }
       }
       stage_store((b + 1) % 3);
@@ -320,7 +332,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
       *(f4 *)pw = f4{0.f, 0.f, 0.f, 0.f};
       if ((JB & 1) == 0) *(f4 *)(pw + 32) = f4{0.f, 0.f, 0.f, 0.f};
       wave_sync();
-      gproduct(JB);
+      if (any_prev) gproduct(JB);
       // H_k: the 4 lanes of a sample; z is in base-2 units (times log2 e)
       if (flag != 0) {
         RIFT_GLOBAL float *ho = gpw(a.hop + (size_t)t * (kMaxDet * kTS));

@@ -27,7 +27,8 @@
 // their blocks (2.8 for 12 in all, of 10.5 samples a tile, at the size below),
 // the contraction and G_k = Q_k^T c_k on the FP64 matrix cores as in the FP64
 // path (k_eval64.hip), with Q from the FP32 matrix-core layout (FP32 values,
-// exact in FP64); ell_j is summed over the detectors through LDS.  U and V enter as one real matrix per detector,
+// exact in FP64); ell_j is summed over the detectors through LDS.  U and V
+// enter as one real matrix per detector,
 //     W = [Ur + Vr, -Ui - Vi; Ui - Vi, Ur - Vr]   (rows, columns re / im),
 // for which B = 1/4 a^T W a and d ln L / d a = G - 1/2 W a: one more matrix
 // product per tile.  The chain rule is then three complex sums over the modes

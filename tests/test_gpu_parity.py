@@ -811,6 +811,31 @@ def test_refined_adjoint_shapes(ile, orc, M, K, n_t, n, v):
         assert rel.max() <= GRAD_REL
 
 
+@pytest.mark.parametrize("sign", [1, -1])
+def test_adjoint_mass_far_below_zero(ile, orc, sign):
+    """A data term that falls (or rises) by 0.3 per window sample from (to)
+    -100: the mass spreads over the first (last) blocks, which lie far below
+    the sums' initial reference, too many of them to be refined, and the
+    blocks at the other end have no part in the sums.  FP32 gradient and
+    ln L_t against the oracle."""
+    tw = 1 / 4096
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1650, dets=("H1", "L1", "V1"), n_modes=5, n_t=500, snr=1.0, kernel="none")
+    d = dict(synth.make_point(spec))
+    th = synth.mixed_samples(d, 35, 50, tau_width=tw)
+    th[:6] = th[:6, :1]
+    a = np.asarray(orc.coeffs(orc.Point.from_dict(d), th[:, 0])[0])
+    r = np.arange(d["Q"].shape[1]) - d["Q"].shape[1] // 2
+    ramp = -100.0 - 0.3 * (sign * r + 250.0)
+    d["Q"] = ramp[None, :, None] * (a / (np.abs(a) ** 2).sum())[:, None, :]
+    p = orc.Point.from_dict(d, complex64=True)
+    lt, g = orc.grad(p, th)
+    h = _handle(ile, [d], "fp32", tau_width=tw)
+    _say(f"adjoint, mass far below zero, sign {sign}")
+    gg, lg = h.backward(torch.tensor(th), want_lnL=True)
+    _grad_check(gg.cpu().numpy(), lg.cpu().numpy(), g, lt, th, "far below zero", f_s=spec.f_s, own_top=False, op=p)
+    h.close()
+
+
 def test_high_l_modes(ile, orc):
     """Modes up to the largest degree the library accepts (l = 8), through the
     coefficient pass and chain rule (polynomial harmonic tables): ln L_t for
