@@ -39,7 +39,10 @@
 // FP64, the sums over the wavefront) took 574 us for 1e5 samples at K = 3,
 // M = 21, n_t = 820, by 1540 vector instructions and 87 loads a sample.  This
 // form takes 261 us: matrix products 70 us, vector instructions 77 us, the rest
-// latency at the three wavefronts per SIMD it is compiled for (at two 319 us).
+// latency at the three wavefronts per SIMD it is compiled for (at two 319 us)
+// and about 10 ns a workgroup to start one.  Of prior draws of a loud point
+// (four samples a tile to refine, mostly in different blocks) it takes 305 us
+// where a wavefront per sample took 232.
 #include "common.h"
 #include "internal.h"
 #include "mfma_tile.h"
@@ -81,12 +84,8 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
   if (key == kNoBin) return;  // the tiles that round a point up to groups of 4
   const SampleRec rec = a.rec[(size_t)t * kTS + s];
   RIFT_GLOBAL int *const jr = gpw(a.jrng) + 2 * ((size_t)t * kTS + s);
-  int b01 = 0, b2n = 0;
-  if (rec.flag == 1) {
-    b01 = jr[0];
-    b2n = jr[1];
-  }
-  const int nb = b2n >> 16;
+  const int b01 = jr[0], b2n = jr[1];
+  const int nb = rec.flag == 1 ? b2n >> 16 : 0;  // (unset in padding slots)
   const bool on = nb >= 1 && nb <= kRefineBlocks;
   if (!__any(on)) return;  // the same for the whole workgroup
   const int it = __builtin_amdgcn_readfirstlane(a.tile_item[t]);
@@ -247,11 +246,14 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
     for (int o = 0; o < 7; o++) pv[o] = pr[16 * o];
 #pragma unroll
     for (int q = 0; q < 4; q++) c[q] = w[0] * pv[q + 3] + w[1] * pv[q + 2] + w[2] * pv[q + 1] + w[3] * pv[q];
+    // (a narrow peak often has no weight in one of the two row blocks; a NaN counts)
+    if (__any(c[0] != 0.0 || c[1] != 0.0 || c[2] != 0.0 || c[3] != 0.0)) {
 #pragma unroll
-    for (int q = 0; q < 4; q++)
+      for (int q = 0; q < 4; q++)
 #pragma unroll
-      for (int mt = 0; mt < MT; mt++)
-        gacc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qv[q][mt], c[q], gacc[mt], 0, 0, 0);
+        for (int mt = 0; mt < MT; mt++)
+          gacc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qv[q][mt], c[q], gacc[mt], 0, 0, 0);
+    }
     wave_sync();
   };
   const double none[4] = {0.0, 0.0, 0.0, 0.0};
