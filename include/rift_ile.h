@@ -247,13 +247,13 @@ typedef struct {
  *   Q[k][r][m] = <h_m(. + t_r)|d>_k = 2 sum_i df/S e^{2 pi i f_i t_r} conj(h~_m) d~_k,
  *                t_r = (row0 + r) / f_s for r < n_rows (rows wrap modulo N),
  *   U[k][m][m'] = <h_m|h_m'>_k,   V[k][m][m'] = <h*_m|h_m'>_k = 2 sum_i df/S h~_m(-f_i) h~_m'(f_i).
- * Q is an unnormalized inverse DFT of the weighted product (one batched
- * complex FFT over detectors and modes, hipFFT), U and V fixed-order FP64
- * sums per entry.  Outputs are caller-owned host arrays, complex
+ * Q is an unnormalized inverse DFT of the weighted product (the requested
+ * rows only, in two steps; a batched hipFFT over detectors and modes where
+ * that is less work), U and V fixed-order FP64 sums per entry.  Outputs are caller-owned host arrays, complex
  * interleaved FP64: Q [K][n_rows][M][2] (the row layout of
  * rift_ile_point.Q; NULL allowed when n_rows == 0), U and V [K][M][M][2].
  * Runs on the current device and blocks; it allocates and frees its own
- * device buffers (inputs, a K M N scratch, outputs) and FFT plan.  Errors:
+ * device buffers (inputs, scratch, outputs) and, if used, the FFT plan.  Errors:
  * RIFT_E_INVALID (NULL array, df or f_low invalid), RIFT_E_SHAPE (K, M, N or
  * n_rows out of range), RIFT_E_NONFINITE (non-finite input, or a PSD value
  * <= 0 in band), RIFT_E_OOM, RIFT_E_DEVICE (HIP or FFT failure). */
@@ -336,19 +336,19 @@ rift_status rift_ile_set_grad_refine(rift_ile *h, int enable);
 /* Per-class launch configuration of the FP32 evaluation (batching: every
  * (T, K) class of points, T = ceil(M / 2) MFMA steps and K detectors, is one
  * persistent launch).  Two forms of the same kernel exist: "staged" (each
- * workgroup copies the rows of Q its unit needs into LDS, one barrier per two
- * 16-row blocks) and "direct" (each wavefront loads its own operands from
- * global memory one block ahead, no barrier, less LDS and more resident
- * workgroups); each runs with as many workgroups as the device keeps resident
+ * workgroup copies the rows of Q its unit needs into LDS, one barrier per
+ * 32-row block) and "direct" (each wavefront loads its own operands from
+ * global memory ahead of their use, no barrier, less LDS); each runs with as many workgroups as the device keeps resident
  * or with half as many per compute unit; the direct form also comes compiled
  * with its registers capped so that three or four wavefronts fit on a SIMD,
  * the staged form capped for three (more resident workgroups where LDS allows
  * them).  The seven configurations are numbered 1 staged, 2 direct, 3 staged
  * at half residency, 4 direct at half residency, 5 direct capped for three
  * wavefronts per SIMD, 6 direct capped for four, 7 staged capped for three;
- * their results are bit-identical.  mode 1 (the default): the first
+ * their results are bit-identical.  A cap that does not fit a class's
+ * registers runs the uncapped form, and is not measured.  mode 1 (the default): the first
  * evaluation of a class on the handle, for each n_t bucket (floor(log2) of
- * the class's longest window), runs all seven twice on that call's data,
+ * the class's longest window), runs them twice each on that call's data,
  * timed with events (that call waits for them), and later calls use the
  * fastest by the better of its two runs (configuration 1 unless another is
  * at least 3 % faster).  mode 0: every
