@@ -288,10 +288,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
             m_ref += cmax;
 #pragma unroll
             for (int i = 0; i < 4; i++) ell[i] -= cmax;
-            cmax = 0.f;
           }
-          // (a NaN window value, of an overflowing sample, must reach the sums)
-          const bool any = __any(!(cmax <= kNoMass));
+          // (of the values, not of their maximum, which leaves a NaN out: a
+          // NaN window value, of an overflowing sample, must reach the sums)
+          const bool any = __any(!(ell[0] <= kNoMass && ell[1] <= kNoMass && ell[2] <= kNoMass && ell[3] <= kNoMass));
           float pj[4] = {0.f, 0.f, 0.f, 0.f};
           if (any) {
 #pragma unroll

@@ -235,10 +235,10 @@ __global__ void __launch_bounds__(256) eval64_kernel(MfmaArgsT<double> a, int it
         m_ref += cmax;
 #pragma unroll
         for (int i = 0; i < 4; i++) ell[i] -= cmax;
-        cmax = 0.0;
       }
-      // (a NaN window value, of an overflowing sample, must reach the sums)
-      const bool any = __any(!(cmax <= kTiny));
+      // (of the values, not of their maximum, which leaves a NaN out: a NaN
+      // window value, of an overflowing sample, must reach the sums)
+      const bool any = __any(!(ell[0] <= kTiny && ell[1] <= kTiny && ell[2] <= kTiny && ell[3] <= kTiny));
       double pj[4] = {0.0, 0.0, 0.0, 0.0};
       if (any) {
 #pragma unroll

@@ -1,0 +1,65 @@
+"""GPU parity at the edges of what the sorted matrix-core forms take: window
+values that overflow, results that may not depend on a sample's neighbours,
+calls of very many delay bins, grids of the precompute with long sums."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from test_gpu_parity import _handle, _say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ile():
+    from paper_2210_07912_amd import ile as m
+    m.lib()
+    return m
+
+
+@pytest.mark.parametrize("prec,big", [("fp32", 3e38), ("fp64", 1.7e308)])
+def test_overflow_far_below_the_peak(ile, orc, prec, big):
+    """A row of Q that overflows the near samples' window values (one detector
+    at the geocentre, whose interpolation weights are 0, 1, 0, 0: -inf and NaN,
+    no +inf), 1900 nats below their peak: ln L_t and gradient of those samples
+    are NaN in every form, also where the sorted forms leave blocks without
+    mass out; the others, 20 times as far away, do not overflow and agree with
+    the oracle."""
+    n_t, n = 200, 40000
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1700, dets=("H1",), n_modes=2, n_t=n_t, snr=1.0, kernel="none")
+    d = dict(synth.make_point(spec))
+    d["det_pos"] = np.zeros((1, 3))
+    th = synth.mixed_samples(d, 37, 4)[:, :1]
+    th[6], th[5] = 0.0, 100.0
+    a = np.asarray(orc.coeffs(orc.Point.from_dict(d), th[:, 0])[0])[0]
+    th[5] = np.float32(100.0 * np.abs(a).max() / 3.0)  # the largest coefficient is 3
+    a *= 3.0 / np.abs(a).max()
+    m = int(np.argmax(np.abs(a)))
+    L = d["Q"].shape[1]
+    row = L - (n_t + 3)  # first row of the window is (L - n_t - 3) / 2 + 1
+    row //= 2
+    d["U"] = 1e-3 * np.eye(2)[None].astype(complex)
+    d["Q"] = np.zeros((1, L, 2), dtype=complex)
+    d["Q"][0, row + 9] = 2000.0 * a / (np.abs(a) ** 2).sum()
+    bad = row + 151
+    part = np.array([a[m].real, a[m].imag])
+    q = -0.9 * big * (part / np.abs(part).max())
+    d["Q"][0, bad, m] = q[0] + 1j * q[1]
+    ths = np.repeat(th, n, axis=1)
+    near = np.arange(n) % 2 == 0
+    ths[5, ~near] = np.float32(20.0 * th[5, 0])
+    ths = ths.astype(np.float32).astype(np.float64)
+    far = orc.lnL_t(orc.Point.from_dict(d, complex64=(prec == "fp32")), ths[:, 1:2])[0]
+    h = _handle(ile, [d], prec)
+    _say(f"overflow far below the peak {prec}: far samples {far}")
+    t = torch.tensor(ths)
+    out = h.lnL(t).cpu().numpy()
+    g, lg = h.backward(t, want_lnL=True)
+    small = h.lnL(t[:, :64]).cpu().numpy()
+    h.close()
+    for v in (small, out, lg.cpu().numpy()):
+        assert np.isnan(v[near[:v.size]]).all()
+        assert np.abs(v[~near[:v.size]] - far).max() <= 2e-5 * abs(far)  # (FP32: the data term of 100)
+    g = g.cpu().numpy()
+    assert np.isnan(g[:, near]).all() and np.isfinite(g[:, ~near]).all()
