@@ -190,10 +190,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
     // scaled by 2^(m_ref - m_new).  At the end all of them are divided by the
     // sum of p, which also gives ln L_t.
     float s_run = 0.f;
-    // A block whose maximum is kNoMass (base 2) below the reference of every
-    // sample of the tile has no part in the sums, which are at least 1: no
-    // exponentials and, with the block before it, no second product (n_t terms
-    // of 2^-60 are far under an FP32 rounding)
+    // A term kNoMass (base 2) below the reference is zero: the sums are at
+    // least 1, and n_t terms of 2^-60 are far under an FP32 rounding.  A block
+    // without larger ones in any sample of the tile takes no exponentials and,
+    // with the block before it, no second product.
     constexpr float kNoMass = -60.f;
     bool any_prev = false;
     // Where the window's mass lies (for the FP64 refinement): the three
@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
           float pj[4] = {0.f, 0.f, 0.f, 0.f};
           if (any) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) pj[i] = __builtin_amdgcn_exp2f(ell[i]);
+            for (int i = 0; i < 4; i++) pj[i] = ell[i] <= kNoMass ? 0.f : __builtin_amdgcn_exp2f(ell[i]);
 #pragma unroll
             for (int i = 0; i < 4; i++) s_run += pj[i];
 #pragma unroll

@@ -257,11 +257,15 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
     wave_sync();
   };
   const double none[4] = {0.0, 0.0, 0.0, 0.0};
-  int cand = 0x7fffffff;
-  if (on && g < nb) cand = g == 0 ? b01 & 0xffff : g == 1 ? (int)((uint32_t)b01 >> 16) : b2n & 0xffff;
+  // (a sample takes part in its own blocks only: what it gets does not depend
+  // on the samples that share its tile)
+  constexpr int kNone = 0x7fffffff;
+  const int c0 = on ? b01 & 0xffff : kNone, c1 = on && nb > 1 ? (int)((uint32_t)b01 >> 16) : kNone,
+            c2 = on && nb > 2 ? b2n & 0xffff : kNone;
   int last = -2;
   for (;;) {
-    const int c = __builtin_amdgcn_readfirstlane(wave_min(cand > last ? cand : 0x7fffffff));
+    const int own = min(min(c0 > last ? c0 : kNone, c1 > last ? c1 : kNone), c2 > last ? c2 : kNone);
+    const int c = __builtin_amdgcn_readfirstlane(wave_min(own));
     if (c >= JB) break;  // no further one
     if (c != last + 1) {
       rows(c);
@@ -299,13 +303,15 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; i++)
-      if (!on || (c == JB - 1 && 4 * g + i >= rem)) ell[i] = -INFINITY;
-    // the reference of a sample: moved when a block exceeds it by 64
+      if (own != c || (c == JB - 1 && 4 * g + i >= rem)) ell[i] = -INFINITY;
+    // the reference of a sample: its first block's maximum, moved when a block
+    // exceeds it by 64
+    const bool first = c == min(min(c0, c1), c2);
     double cmax = fmax(fmax(ell[0], ell[1]), fmax(ell[2], ell[3]));
     cmax = fmax(cmax, shfl_xor_d(cmax, 16));
     cmax = fmax(cmax, shfl_xor_d(cmax, 32));
-    if ((last < 0 || cmax > 64.0) && cmax > -INFINITY) {
-      const double f = last < 0 ? 0.0 : exp(-cmax);
+    if ((first || cmax > 64.0) && cmax > -INFINITY) {
+      const double f = first ? 0.0 : exp(-cmax);
       s_run *= f;
       hsum *= f;
 #pragma unroll

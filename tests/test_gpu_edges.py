@@ -63,3 +63,40 @@ def test_overflow_far_below_the_peak(ile, orc, prec, big):
         assert np.abs(v[~near[:v.size]] - far).max() <= 2e-5 * abs(far)  # (FP32: the data term of 100)
     g = g.cpu().numpy()
     assert np.isnan(g[:, near]).all() and np.isfinite(g[:, ~near]).all()
+
+
+def test_gradient_does_not_depend_on_the_neighbours(ile, orc):
+    """Two peaks, the later one higher: within 40 nats of each other for the
+    far samples, 60 and more apart for the near ones, so that samples of one
+    tile need different blocks.  The peaks are symmetric about a row (one
+    detector, at the geocentre), so that the derivative in tau is zero but for
+    the rounding of its terms, which shows the order and the references of every
+    sum: it and all else of the near samples are the same, bit for bit, alone
+    and among the far ones, in any order."""
+    n = 96
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1701, dets=("H1",), n_modes=2, n_t=160, snr=1.0, kernel="none")
+    d = dict(synth.make_point(spec))
+    d["ell"], d["em"] = d["ell"][:1], d["em"][:1]
+    d["U"] = 1e-3 * np.ones((1, 1, 1), dtype=complex)
+    d["det_pos"] = np.zeros((1, 3))
+    th = synth.mixed_samples(d, 38, 4)[:, 3:]
+    th[6], th[5] = 0.0, 200.0
+    d["Q"] = np.zeros((1, d["Q"].shape[1], 1), dtype=complex)
+    a = np.asarray(orc.coeffs(orc.Point.from_dict(d), th[:, 0])[0])[0]
+    r = np.arange(d["Q"].shape[1]) - d["Q"].shape[1] // 2
+    peaks = 970.0 * np.maximum(0, 1 - ((r + 40) / 20) ** 2) + 1000.0 * np.maximum(0, 1 - ((r - 40) / 20) ** 2)
+    d["Q"][0] = (peaks[:, None] * (a / (np.abs(a) ** 2).sum())[None, :])
+    ths = np.repeat(th, n, axis=1)
+    near = np.arange(n) % 3 != 0
+    ths[5, near] = 95.0 - 0.1 * np.arange(near.sum())
+    ths[5, ~near] = 200.0 + np.arange((~near).sum())
+    h = _handle(ile, [d], "fp32")
+    _say("gradient beside other samples")
+    g, l = (x.cpu().numpy() for x in h.backward(torch.tensor(ths), want_lnL=True))
+    perm = np.random.default_rng(3).permutation(n)
+    gp, lp = (x.cpu().numpy() for x in h.backward(torch.tensor(ths[:, perm]), want_lnL=True))
+    ga, la = (x.cpu().numpy() for x in h.backward(torch.tensor(ths[:, near]), want_lnL=True))
+    h.close()
+    assert np.isfinite(g).all() and np.abs(g[6]).max() < 1e-6 and (g[6, near] != 0.0).any()
+    assert np.array_equal(g[:, near], ga) and np.array_equal(l[near], la)
+    assert np.array_equal(g[:, perm], gp) and np.array_equal(l[perm], lp)
