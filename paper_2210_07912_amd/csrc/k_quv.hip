@@ -61,6 +61,13 @@ __global__ void __launch_bounds__(256) quv_gather_kernel(int M, int64_t N, int64
 // destroy; the whole call 16.4 -> 0.97 ms, most of it the copies.
 constexpr int kMaxA = 64;
 constexpr int kBT = 64;  // b per workgroup of the first step
+// Both steps add in runs of eight terms, the second its N / A / 8 runs with
+// Kahan's compensation: the error of one long sum grows with its length, the
+// FFT's with log N.  Largest error over the largest |Q| of a steep spectrum at N
+// = 4096, 32749 (prime: one step of N terms) and 2^18: by the FFT library
+// 3.5e-16, 1.7e-15 and 1.5e-15; as long sums 2.4e-15, 1.1e-14 and 5.3e-14; in
+// runs 2.4e-16, 4.9e-16 and 9.8e-16 (the call 2 % slower at the size above).
+constexpr int kSub = 8;
 
 // S[series][c][b]; x = w conj(h) d is formed here.  A workgroup takes 64 b of
 // one series; each of its four wavefronts a quarter of the c, eight at a time.
@@ -97,15 +104,25 @@ __global__ void __launch_bounds__(256) quv_step1_kernel(int M, int64_t N, int A,
       acc[q] = double2{0.0, 0.0};
       ph[q] = 0;
     }
-    for (int a = 0; a < A; a++) {
-      const double2 v = x[a][lane];
+    for (int a0 = 0; a0 < A; a0 += kSub) {
+      double2 sub[8];
+#pragma unroll
+      for (int q = 0; q < 8; q++) sub[q] = double2{0.0, 0.0};
+      for (int a = a0; a < min(A, a0 + kSub); a++) {
+        const double2 v = x[a][lane];
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+          const double2 t = tw[ph[q]];
+          sub[q].x = fma(v.x, t.x, fma(-v.y, t.y, sub[q].x));
+          sub[q].y = fma(v.x, t.y, fma(v.y, t.x, sub[q].y));
+          ph[q] += c0 + q;  // a (c0 + q) mod A, below 2 kMaxA before
+          while (ph[q] >= A) ph[q] -= A;
+        }
+      }
 #pragma unroll
       for (int q = 0; q < 8; q++) {
-        const double2 t = tw[ph[q]];
-        acc[q].x = fma(v.x, t.x, fma(-v.y, t.y, acc[q].x));
-        acc[q].y = fma(v.x, t.y, fma(v.y, t.x, acc[q].y));
-        ph[q] += c0 + q;  // a (c0 + q) mod A, below 2 kMaxA before
-        while (ph[q] >= A) ph[q] -= A;
+        acc[q].x += sub[q].x;
+        acc[q].y += sub[q].y;
       }
     }
     if (b < B) {
@@ -129,7 +146,12 @@ __global__ void __launch_bounds__(256) quv_step2_kernel(int M, int64_t N, int A,
   const int64_t r = r0 + (int64_t)A * (8 * (int64_t)blockIdx.x + row);
   if (r0 + (int64_t)A * 8 * blockIdx.x >= n_rows) return;  // the whole workgroup
   const int64_t n = ((row0 + r) % N + N) % N;
-  double qr = 0.0, qi = 0.0;
+  double qr = 0.0, qi = 0.0, er = 0.0, ei = 0.0;  // the sums and what their roundings have added
+  auto add = [](double &sum, double &err, double v) {
+    const double y = v - err, t = sum + y;
+    err = (t - sum) - y;
+    sum = t;
+  };
   for (int64_t b0 = 0; b0 < B; b0 += 32) {
     __syncthreads();
     for (int e = threadIdx.x; e < 32 * M; e += 256) {
@@ -142,11 +164,16 @@ __global__ void __launch_bounds__(256) quv_step2_kernel(int M, int64_t N, int A,
     }
     __syncthreads();
     if (m < M)
-#pragma unroll 8
-      for (int j = 0; j < 32; j++) {
-        const double2 v = sx[j][m], t = w[row][j];
-        qr = fma(v.x, t.x, fma(-v.y, t.y, qr));
-        qi = fma(v.x, t.y, fma(v.y, t.x, qi));
+      for (int j0 = 0; j0 < 32; j0 += kSub) {
+        double sr = 0.0, si = 0.0;
+#pragma unroll
+        for (int j = 0; j < kSub; j++) {
+          const double2 v = sx[j0 + j][m], t = w[row][j0 + j];
+          sr = fma(v.x, t.x, fma(-v.y, t.y, sr));
+          si = fma(v.x, t.y, fma(v.y, t.x, si));
+        }
+        add(qr, er, sr);
+        add(qi, ei, si);
       }
   }
   if (m < M && r < n_rows) Q[((size_t)k * n_rows + r) * M + m] = double2{qr, qi};
@@ -190,14 +217,20 @@ __global__ void __launch_bounds__(256) quv_gram_kernel(int M, int64_t N, double 
       const int e = threadIdx.x + 256 * q;
       if (e < M * M) {
         const int m = e / M, mp = e % M;
+        // (the tile's sum, then the chunk's: one long sum rounds more)
+        double2 su = {0.0, 0.0}, sv = {0.0, 0.0};
 #pragma unroll 4
         for (int j = 0; j < kGT; j++) {
           const double2 a = h[m][j], an = hn[m][j], b = wh[mp][j];
-          u[q].x = fma(a.x, b.x, fma(a.y, b.y, u[q].x));
-          u[q].y = fma(a.x, b.y, fma(-a.y, b.x, u[q].y));
-          v[q].x = fma(an.x, b.x, fma(-an.y, b.y, v[q].x));
-          v[q].y = fma(an.x, b.y, fma(an.y, b.x, v[q].y));
+          su.x = fma(a.x, b.x, fma(a.y, b.y, su.x));
+          su.y = fma(a.x, b.y, fma(-a.y, b.x, su.y));
+          sv.x = fma(an.x, b.x, fma(-an.y, b.y, sv.x));
+          sv.y = fma(an.x, b.y, fma(an.y, b.x, sv.y));
         }
+        u[q].x += su.x;
+        u[q].y += su.y;
+        v[q].x += sv.x;
+        v[q].y += sv.y;
       }
     }
   }

@@ -100,3 +100,32 @@ def test_gradient_does_not_depend_on_the_neighbours(ile, orc):
     assert np.isfinite(g).all() and np.abs(g[6]).max() < 1e-6 and (g[6, near] != 0.0).any()
     assert np.array_equal(g[:, near], ga) and np.array_equal(l[near], la)
     assert np.array_equal(g[:, perm], gp) and np.array_equal(l[perm], lp)
+
+
+def _row_sum_bound(N):
+    """Largest error of Q over its largest value: an FFT's, of log2 N levels
+    that round each value once by 2^-53 in quadrature, four times over."""
+    return 4.0 * 2.0 ** -53 * np.sqrt(np.log2(N))
+
+
+@pytest.mark.parametrize("N", [4096, 9600, 32749, 131071, 2 ** 18])
+def test_precompute_long_sums(ile, N):
+    """Rows of Q against sums in extended precision, on grids with many and
+    (32749 and 131071 are prime) no divisors: the error does not grow with the
+    number of terms of a row."""
+    M, R = 2, 24
+    data, psd, modes, f = synth.fd_inputs(90 + N, n_det=1, n_modes=M, N=N, df=0.25, f_low=0.3)
+    row0 = N // 3
+    Q, _, _ = ile.precompute(data, psd, modes, 0.25, 0.3, row0, R)
+    ld = np.longdouble
+    w = np.where(np.abs(f) > 0.3, 2.0 * ld(0.25) / psd[0].astype(ld), ld(0))
+    i = np.arange(N, dtype=np.int64)
+    err = big = 0.0
+    for r in range(R):
+        ph = 2 * ld("3.14159265358979323846264338327950288") * ((i * (row0 + r)) % N).astype(ld) / ld(N)
+        x = (np.cos(ph) + 1j * np.sin(ph)) * w * data[0].astype(np.clongdouble)
+        for m in range(M):
+            ref = (np.conj(modes[m].astype(np.clongdouble)) * x).sum()
+            err, big = max(err, float(abs(Q[0, r, m] - ref))), max(big, float(abs(ref)))
+    _say(f"precompute sums N={N}: {err / big:.2e}, bound {_row_sum_bound(N):.2e}")
+    assert err <= _row_sum_bound(N) * big
