@@ -1332,6 +1332,7 @@ rift_status rift_ile_precompute(const rift_ile_fd_point *in, int64_t row0, int64
                 (long long)n_rows);
   if (!(in->df > 0.0) || !std::isfinite(in->df) || !(in->f_low >= 0.0) || !std::isfinite(in->f_low))
     return fail(nullptr, RIFT_E_INVALID, "precompute: df or f_low invalid");
+  row0 = (row0 % N + N) % N;  // (any row0: the kernels form differences with it)
   const size_t nd = 2 * (size_t)K * N, np_ = (size_t)K * N, nm = 2 * (size_t)M * N;
   const size_t nx = n_rows > 0 ? 2 * (size_t)K * M * N : 0, nq = 2 * (size_t)K * n_rows * M, nu = 2 * (size_t)K * M * M;
   const size_t ng = 2 * nu * (size_t)quv_part_chunks(N);

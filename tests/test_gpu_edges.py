@@ -129,3 +129,14 @@ def test_precompute_long_sums(ile, N):
             err, big = max(err, float(abs(Q[0, r, m] - ref))), max(big, float(abs(ref)))
     _say(f"precompute sums N={N}: {err / big:.2e}, bound {_row_sum_bound(N):.2e}")
     assert err <= _row_sum_bound(N) * big
+
+
+def test_precompute_rows_at_the_ends_of_int64(ile):
+    """Rows wrap modulo N from any first row, also the smallest and largest
+    64-bit ones (N = 4095, whose divisors are odd)."""
+    data, psd, modes, f = synth.fd_inputs(92, n_det=2, n_modes=3, N=4095, df=0.25, f_low=0.3)
+    for row0 in (-2 ** 63, -2 ** 63 + 5, 2 ** 63 - 70):
+        a = ile.precompute(data, psd, modes, 0.25, 0.3, row0, 65)
+        b = ile.precompute(data, psd, modes, 0.25, 0.3, row0 % 4095, 65)
+        _say(f"precompute row0 = {row0}")
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
