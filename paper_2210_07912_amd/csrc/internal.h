@@ -346,7 +346,8 @@ hipError_t fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st);
 // Q/U/V of Eq. (QUV) from frequency-domain inputs, all pointers device
 // memory: data [K][N] and modes [M][N] complex (interleaved), psd [K][N];
 // X [K][M][N] complex scratch; part [quv_part_chunks(N)][K][2][M][M] complex
-// scratch; Q [K][n_rows][M], U and V [K][M][M] complex.
+// scratch, written after X was read (they may share memory); Q [K][n_rows][M],
+// U and V [K][M][M] complex.
 // Ordered on st; returns hipErrorUnknown when the FFT library fails.
 hipError_t quv_device(int K, int M, int64_t N, double df, double f_low, const double *data, const double *psd,
                       const double *modes, int64_t row0, int64_t n_rows, double *X, double *part, double *Q, double *U,

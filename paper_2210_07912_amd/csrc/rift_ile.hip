@@ -1349,7 +1349,8 @@ rift_status rift_ile_precompute(const rift_ile_fd_point *in, int64_t row0, int64
     at += (n + 31) & ~(size_t)31;
     return p;
   };
-  const size_t od = part(nd), op = part(np_), om = part(nm), ox = part(nx), og = part(ng), oq = part(nq), ou = part(nu),
+  // (the Gram sums' partials follow Q in the same scratch as its transform)
+  const size_t od = part(nd), op = part(np_), om = part(nm), ox = part(std::max(nx, ng)), oq = part(nq), ou = part(nu),
                ov = part(nu), ob = part(2);
   void *mem = nullptr;
   if (hipMalloc(&mem, sizeof(double) * at) != hipSuccess) {
@@ -1373,7 +1374,7 @@ rift_status rift_ile_precompute(const rift_ile_fd_point *in, int64_t row0, int64
   if (e == hipSuccess)
     e = quv_check(K, M, N, in->df, in->f_low, w + od, w + op, w + om, (unsigned long long *)(w + ob), nullptr);
   if (e == hipSuccess)
-    e = quv_device(K, M, N, in->df, in->f_low, w + od, w + op, w + om, row0, n_rows, w + ox, w + og, w + oq, w + ou,
+    e = quv_device(K, M, N, in->df, in->f_low, w + od, w + op, w + om, row0, n_rows, w + ox, w + ox, w + oq, w + ou,
                    w + ov, nullptr);
   if (e == hipSuccess) e = hipMemcpy(bad, w + ob, sizeof bad, hipMemcpyDeviceToHost);
   if (e == hipSuccess && bad[0] == 0 && bad[1] == ~0ull) {
