@@ -573,6 +573,26 @@ rift_status launch_graph(rift_ile *h, const MfmaArgs &a, const std::vector<int> 
   return join();
 }
 
+// Tiles of cnt samples of a point, at most: its bins are padded to whole tiles,
+// those of the FP32 evaluation to whole pairs of them, the point to groups of 4.
+template <typename R>
+int64_t tile_bound(const PointDev &p, int64_t cnt, bool grad) {
+  const int64_t pad = grad || sizeof(R) == 8 ? 1 : 2;
+  return (cnt + 15) / 16 + pad * std::min<int64_t>(p.n_bins_key, cnt) + 4;
+}
+
+// Workspace that run_mfma_group takes for them, bytes (hist: sort blocks of 4096).
+template <typename R>
+double group_bytes(const rift_ile *h, const PointDev &p, int64_t cnt, bool grad) {
+  const double operands = (double)p.K * 2 * p.Mp * 16 * sizeof(R);
+  const double tile = 16.0 * sizeof(SampleRec) + 8.0 + sizeof(CoefTileT<R>) + sizeof(WorkUnit) + operands +
+                      (grad ? operands + kMaxDet * 16.0 * sizeof(R) + (sizeof(R) == 4 ? 128.0 : 0.0) : 0.0) +
+                      (h->dmarg ? 64.0 : 0.0);
+  return 12.0 * cnt + tile * tile_bound<R>(p, cnt, grad) + p.n_bins_key * (12.0 + 4.0 * ((cnt + 4095) / 4096));
+}
+
+constexpr int64_t kMaxTiles = (int64_t)1 << 26, kMaxBins = (int64_t)1 << 28;  // of a group
+
 // One group of points (already in evaluation order) through the sort, the
 // coefficient pass and the persistent MFMA launches.
 template <typename R>
@@ -597,8 +617,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
       class_K.push_back(p.K);
       class_item0.push_back((int)i);
     }
-    // bins are padded to whole pairs of tiles, a point to whole groups of 4
-    const int64_t tiles_i = (it.cnt[i] + 15) / 16 + 2 * std::min<int64_t>(p.n_bins_key, it.cnt[i]) + 4;
+    const int64_t tiles_i = tile_bound<R>(p, it.cnt[i], grad != nullptr);
     const int mkey = p.Vpk ? -p.M : p.M;  // V tables: the general coefficient kernel
     if (mclass_M.empty() || mclass_M.back() != mkey) {
       mclass_M.push_back(mkey);
@@ -608,7 +627,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
     mclass_tiles.back() += tiles_i;
     samp0.push_back(samp0.back() + it.cnt[i]);
     long long nb = (long long)bin0.back() + p.n_bins_key;
-    if (nb > (1 << 28)) return fail(h, RIFT_E_SHAPE, "too many delay bins in one call");
+    if (nb > kMaxBins) return fail(h, RIFT_E_SHAPE, "too many delay bins in one call");
     bin0.push_back((int)nb);
     const int nblk = (int)((it.cnt[i] + sort_block - 1) / sort_block);
     max_item_blocks = std::max(max_item_blocks, nblk);
@@ -625,7 +644,7 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   const int64_t total = samp0.back();
   if (ni == 0) return RIFT_OK;
   if (total == 0) return RIFT_OK;
-  if (total >= (int64_t)1 << 31 || max_tiles >= (int64_t)1 << 26)
+  if (total >= (int64_t)1 << 31 || max_tiles >= kMaxTiles)
     return fail(h, RIFT_E_SHAPE, "more than 2^31 samples in one call");
   MfmaArgsT<R> a;
   std::memset(&a, 0, sizeof(a));
@@ -783,7 +802,9 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
 
 // Points grouped by MFMA step count T (one persistent launch per group),
 // then mode count, costliest first: the kernels take tiles in this order.
-// The points are evaluated in runs whose workspace stays under a budget.
+// The points are evaluated in runs whose workspace stays under a budget: the
+// samples' part of it, and one and a half times it with the padding of their
+// bins (many points of few samples: mostly padding), within a run's limits.
 template <typename R>
 rift_status run_mfma(rift_ile *h, const Items &it_in, int64_t stride, const R *theta, R *lnL, R *lnw,
                      const R *ln_ratio, const R *gin = nullptr, R *grad = nullptr) {
@@ -804,8 +825,10 @@ rift_status run_mfma(rift_ile *h, const Items &it_in, int64_t stride, const R *t
     return cost(a) > cost(b);
   });
   const double budget = h->ws_budget;  // bytes of per-sample workspace per run
+  const bool bwd = grad != nullptr;
   Items grp;
-  double used = 0.0;
+  double used = 0.0, bytes = 0.0;
+  int64_t tiles = 0, bins = 0;
   for (int oi : order) {
     if (it_in.cnt[oi] == 0) continue;
     const PointDev &p = h->hp[it_in.point[oi]];
@@ -814,19 +837,29 @@ rift_status run_mfma(rift_ile *h, const Items &it_in, int64_t stride, const R *t
       const double per = 4.0 + 8.0 + 44.0 + 10.0 * sizeof(R) +
                          (double)p.K * 2 * p.Mp * sizeof(R) * 1.1 * (grad ? 2.0 : 1.0) + (h->dmarg ? 4.4 : 0.0);
       int64_t take = remaining;
-      if (used + per * take > budget) {
+      // (also of the samples after others in the group)
+      auto over = [&](int64_t n) {
+        return used + per * n > budget || bytes + group_bytes<R>(h, p, n, bwd) > 1.5 * budget ||
+               tiles + tile_bound<R>(p, n, bwd) >= kMaxTiles;
+      };
+      if (over(take) || bins + p.n_bins_key > kMaxBins) {
         if (!grp.point.empty()) {
           rift_status s = run_mfma_group<R>(h, grp, stride, theta, lnL, lnw, ln_ratio, gin, grad);
           if (s != RIFT_OK) return s;
           grp = Items();
-          used = 0.0;
+          used = bytes = 0.0;
+          tiles = bins = 0;
         }
         take = std::min<int64_t>(remaining, std::max<int64_t>(4096, (int64_t)(budget / per)));
+        while (take > 4096 && over(take)) take = std::max<int64_t>(4096, take - take / 16);
       }
       grp.point.push_back(it_in.point[oi]);
       grp.off.push_back(off);
       grp.cnt.push_back(take);
       used += per * take;
+      bytes += group_bytes<R>(h, p, take, bwd);
+      tiles += tile_bound<R>(p, take, bwd);
+      bins += p.n_bins_key;
       off += take;
       remaining -= take;
     }
@@ -873,7 +906,7 @@ template <typename R>
 rift_status eval(rift_ile *h, const Items &it, int64_t stride, const R *theta, R *lnL, R *lnw, const R *ln_ratio) {
   if (sizeof(R) == 4 ? !(h->flags & 1u) : use_sorted64(h, it, stride, false)) {
     const rift_status s = run_mfma<R>(h, it, stride, theta, lnL, lnw, ln_ratio);
-    if (sizeof(R) == 4 || s != RIFT_E_OOM) return s;  // FP64: the plain form needs no workspace
+    if (sizeof(R) == 4 || (s != RIFT_E_OOM && s != RIFT_E_SHAPE)) return s;  // FP64: the plain form needs no workspace
   }
   return run_plain<R>(h, it, stride, theta, lnL, lnw, ln_ratio, nullptr, nullptr, false);
 }
@@ -884,7 +917,7 @@ template <typename R>
 rift_status eval_grad(rift_ile *h, const Items &it, int64_t stride, const R *theta, R *lnL, const R *gin, R *grad) {
   if (sizeof(R) == 4 ? !(h->flags & 1u) : use_sorted64(h, it, stride, true)) {
     const rift_status s = run_mfma<R>(h, it, stride, theta, lnL, nullptr, nullptr, gin, grad);
-    if (sizeof(R) == 4 || s != RIFT_E_OOM) return s;
+    if (sizeof(R) == 4 || (s != RIFT_E_OOM && s != RIFT_E_SHAPE)) return s;
   }
   return run_plain<R>(h, it, stride, theta, lnL, nullptr, nullptr, gin, grad, true);
 }

@@ -140,3 +140,73 @@ def test_precompute_rows_at_the_ends_of_int64(ile):
         b = ile.precompute(data, psd, modes, 0.25, 0.3, row0 % 4095, 65)
         _say(f"precompute row0 = {row0}")
         assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+def _wide(key, K=2, n_modes=2, n_t=16, bins_per_det=256):
+    """A point whose pad gives bins_per_det delay bins (of 14 rows) per detector."""
+    spec = synth.PointSpec(seed=synth.BASE_SEED + key, dets=("H1", "L1", "V1")[:K], n_modes=n_modes, n_t=n_t, snr=1.0,
+                           kernel="none")
+    d = dict(synth.make_point(spec))
+    pad = (14 * bins_per_det - 1) // 2
+    g = np.random.default_rng(key)
+    L = n_t + 2 * pad + 3
+    d["pad"] = pad
+    d["Q"] = g.standard_normal((K, L, n_modes)) + 1j * g.standard_normal((K, L, n_modes))
+    return d
+
+
+def test_fp64_items_of_very_many_bins(ile, orc):
+    """More delay bins in one FP64 call (4200 items of 65536) than one sort
+    takes: evaluated, not refused, as every call of the plain form."""
+    d = _wide(1710, n_t=64)
+    n, per = 4200, 32
+    th = synth.mixed_samples(d, 40, n * per)
+    items = [(0, per * i, per) for i in range(n)]
+    h = _handle(ile, [d], "fp64")
+    _say(f"{n} items of {h.meta[0]}, 65536 bins each")
+    out = h.lnL(torch.tensor(th), items).cpu().numpy()
+    sub = np.arange(0, n * per, 1311)
+    ref = orc.lnL_t(orc.Point.from_dict(d), th[:, sub])
+    h.close()
+    assert np.all(np.abs(out[sub] - ref) <= 1e-9 * (1 + np.abs(ref)))
+
+
+def test_fp32_tiles_beyond_one_group(ile, orc):
+    """3.4e7 samples in 520 items of 65536 delay bins, most of them alone in
+    theirs: more tiles, padded to pairs, than one group holds (2^26); such a
+    call is evaluated in several (of some 100 GB of workspace)."""
+    d = _wide(1711, n_t=4)
+    n, per = 520, 65536
+    base = torch.tensor(synth.mixed_samples(d, 41, per, tau_width=2.0 * (d["pad"] / 4096.0 - 0.03)), dtype=torch.float32)
+    th = base.cuda().repeat(1, n)
+    h = _handle(ile, [d], "fp32", plain=False)
+    _say(f"{n} items of {per} samples, 65536 bins each")
+    out = h.lnL(th, [(0, per * i, per) for i in range(n)]).reshape(n, per)
+    one = h.lnL(base)
+    h.close()
+    assert torch.isfinite(one).all()
+    assert (out == one[None]).all()
+
+
+def test_workspace_of_many_small_points(ile):
+    """The adjoint pads a bin to one tile: 200 items of 2000 samples, 2197 bins
+    each, take no more device memory than those tiles do, a quarter more (the
+    growth) and half of that again (the rest of the arrays)."""
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1712, dets=("H1", "L1", "V1"), n_modes=21, n_t=16, snr=1.0,
+                           kernel="none")
+    d = synth.make_point(spec)
+    n, per = 200, 2000
+    th = torch.tensor(synth.mixed_samples(d, 42, n * per), dtype=torch.float32).cuda()
+    h = _handle(ile, [d], "fp32")
+    h.lnL(th[:, :64])
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    out = torch.empty_like(th)
+    g = h.backward(th, items=[(0, per * i, per) for i in range(n)])
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    tiles = n * (per / 16 + per + 4)
+    bound = 1.25 * 1.5 * tiles * (2 * 3 * 2 * 22 * 16 * 4)
+    _say(f"workspace {used / 1e9:.2f} GB, bound {bound / 1e9:.2f} GB")
+    h.close()
+    assert torch.isfinite(g).all() and used <= bound + out.numel() * 8
