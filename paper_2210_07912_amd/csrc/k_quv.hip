@@ -315,7 +315,7 @@ static int quv_split(int K, int M, int64_t N, int64_t n_rows) {
       cost = c;
     }
   }
-  // 32-bit grids: 8 rows of a residue per workgroup
+  // (the second step's phases b n are products below N^2, in 64 bits)
   return cost * K * M <= 5.0e10 && (double)N * (double)N < 9.0e18 ? best : 0;
 }
 

@@ -210,3 +210,56 @@ def test_workspace_of_many_small_points(ile):
     _say(f"workspace {used / 1e9:.2f} GB, bound {bound / 1e9:.2f} GB")
     h.close()
     assert torch.isfinite(g).all() and used <= bound + out.numel() * 8
+
+
+@pytest.mark.parametrize("M,K,n_t", [(1, 1, 16), (2, 3, 16), (3, 2, 17), (5, 3, 15), (12, 3, 47), (15, 1, 64),
+                                     (21, 3, 48), (28, 2, 33), (32, 3, 33)])
+def test_fp64_sorted_and_plain_forward(ile, orc, M, K, n_t):
+    """One FP64 call of 2e8 units of work (K n_t (M + 4) per sample), far above
+    the size rule of the sorted form, against the same samples in calls of 1e7,
+    far below it.  ln L_t agrees to the rounding of its terms, and not bit for
+    bit: both forms have run."""
+    rng = np.random.default_rng([94, M, K, n_t])
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1720 + M, dets=("H1", "L1", "V1")[:K], n_modes=2, n_t=n_t, snr=1.0,
+                           kernel="none")
+    d = dict(synth.make_point(spec))
+    lm = [(l, m) for l in range(2, 9) for m in range(-l, l + 1)]
+    pick = rng.choice(len(lm), M, replace=False)
+    d["ell"] = np.array([lm[i][0] for i in pick], dtype=np.int32)
+    d["em"] = np.array([lm[i][1] for i in pick], dtype=np.int32)
+    L = d["Q"].shape[1]
+    G = rng.standard_normal((K, M, M + 2)) + 1j * rng.standard_normal((K, M, M + 2))
+    d["U"] = 100.0 * G @ G.conj().transpose(0, 2, 1) / (M + 2)
+    d["Q"] = 30.0 * (rng.standard_normal((K, L, M)) + 1j * rng.standard_normal((K, L, M)))
+    unit = K * n_t * (M + 4)
+    n, part = int(2e8 / unit) + 1, int(1e7 / unit)
+    th = torch.tensor(synth.mixed_samples(d, 43, n))
+    h = _handle(ile, [d], "fp64")
+    _say(f"fp64 sorted and plain M={M} K={K} n_t={n_t} n={n}")
+    out = h.lnL(th).cpu().numpy()
+    cut = np.arange(0, n, max(part, n // 4))[:4]
+    small = np.concatenate([h.lnL(th[:, a:a + part]).cpu().numpy() for a in cut])
+    h.close()
+    same = np.concatenate([out[a:a + part] for a in cut])
+    assert np.isfinite(out).all() and np.allclose(same, small, rtol=1e-11, atol=1e-9)
+    assert (same != small).any()
+    cols = rng.choice(n, 40, replace=False)
+    ref = orc.lnL_t(orc.Point.from_dict(d), th.numpy()[:, cols])
+    assert np.all(np.abs(out[cols] - ref) <= 1e-9 * (1 + np.abs(ref)))
+
+
+def test_precompute_by_the_fft(ile):
+    """A precompute of more products than the pruned transform takes (a prime
+    grid, 40000 rows, ten series): the rows come from the FFT, and agree with
+    extended-precision sums as closely as those of a call of a few rows, which
+    does not take it."""
+    N, K, M, R, row0 = 131071, 2, 5, 40000, 100000
+    data, psd, modes, f = synth.fd_inputs(93, n_det=K, n_modes=M, N=N, df=0.25, f_low=0.3)
+    Q, U, V = ile.precompute(data, psd, modes, 0.25, 0.3, row0, R)
+    big = np.abs(Q).max()
+    for r in (0, 7001, 31070, R - 8):
+        q, u, v = ile.precompute(data, psd, modes, 0.25, 0.3, row0 + r, 8)
+        err = np.abs(Q[:, r:r + 8] - q).max() / big
+        _say(f"precompute by the FFT, rows {row0 + r}...: {err:.2e}")
+        assert 0.0 < err <= 8.0 * _row_sum_bound(N)  # (a prime grid: three transforms of twice the length and more)
+        assert np.array_equal(u, U) and np.array_equal(v, V)
