@@ -51,7 +51,7 @@ struct rift_ile {
   int n_cu = 0;
   int lds_max = 65536;
   // grow-only workspace, indexed by name
-  DevBuf ws[48];
+  DevBuf ws[32];
   // side streams for concurrent class kernels, and the workspace budget
   Fanout fan{};
   // captured evaluation runs: key (launch arguments and class layout) -> graph
@@ -90,12 +90,11 @@ struct rift_ile {
 namespace {
 
 enum WsId {
-  W_ITEM_POINT, W_ITEM_OFF, W_ITEM_CNT, W_ITEM_TILE0, W_ITEM_SAMP0, W_ITEM_BIN0,
-  W_KEY, W_NSH, W_COUNT, W_CURSOR, W_COP, W_BINTILE, W_ITEMTILES, W_PERM, W_TILES, W_CTL, W_CTILE,
-  W_PARTIALS, W_ROUND, W_ACCUM, W_RESULT, W_HIST, W_THETA, W_LNW, W_AUX, W_RATIO, W_BINS, W_ITEM_BLK0,
-  W_ITEM_HOFF, W_ITEM_COP, W_SEG_OFF, W_SEG_CNT, W_ASC, W_AHIST, W_UNIT, W_BINUNIT, W_ITEMUNITS, W_GOP, W_HOP, W_SEG_BLK, W_UBUF, W_EMPART, W_EMPART2, W_GMMFIT, W_EMWT, W_JRNG, W_AMAX, W_COUNT_IDS
+  W_ITEM_POINT, W_ITEM_OFF, W_ITEM_CNT, W_ITEM_TILE0, W_RUN,
+  W_PARTIALS, W_ROUND, W_ACCUM, W_RESULT, W_HIST, W_THETA, W_LNW, W_AUX, W_RATIO, W_BINS, W_SEG_OFF, W_SEG_CNT,
+  W_ASC, W_AHIST, W_SEG_BLK, W_UBUF, W_EMPART, W_EMPART2, W_GMMFIT, W_EMWT, W_COUNT_IDS
 };
-static_assert(W_COUNT_IDS <= 48, "workspace table too small");
+static_assert(W_COUNT_IDS <= 32, "workspace table too small");
 
 // Scratch of rift_ile_reduce_noalloc, for callers that cannot allocate:
 // the partial FP64 tuples of the reduction, the segment's offset and count,
@@ -649,28 +648,11 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   MfmaArgsT<R> a;
   std::memset(&a, 0, sizeof(a));
   rift_status s;
-  int *d_point, *d_bin0, *d_blk0;
-  int64_t *d_off, *d_cnt, *d_samp0, *d_hoff;
-  if ((s = upload(h, W_ITEM_POINT, it.point, &d_point)) != RIFT_OK) return s;
-  if ((s = upload(h, W_ITEM_OFF, it.off, &d_off)) != RIFT_OK) return s;
-  if ((s = upload(h, W_ITEM_CNT, it.cnt, &d_cnt)) != RIFT_OK) return s;
-  if ((s = upload(h, W_ITEM_SAMP0, samp0, &d_samp0)) != RIFT_OK) return s;
-  if ((s = upload(h, W_ITEM_BIN0, bin0, &d_bin0)) != RIFT_OK) return s;
-  if ((s = upload(h, W_ITEM_BLK0, blk0, &d_blk0)) != RIFT_OK) return s;
-  if ((s = upload(h, W_ITEM_HOFF, hoff, &d_hoff)) != RIFT_OK) return s;
   a.pts = h->d_pts;
-  a.items.blk0 = d_blk0;
-  a.items.hoff = d_hoff;
   a.n_sort_blocks = blk0.back();
   a.max_item_bins = max_item_bins;
   a.sort_block = sort_block;
   a.max_item_blocks = max_item_blocks;
-  a.items.point = d_point;
-  a.items.off = d_off;
-  a.items.cnt = d_cnt;
-  a.items.samp0 = d_samp0;
-  a.items.bin0 = d_bin0;
-  a.items.tile0 = nullptr;
   a.items.n_items = ni;
   a.stride = stride;
   a.total = total;
@@ -681,57 +663,69 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   a.n_bins = bin0.back();
   a.max_tiles = (int)max_tiles;
   a.unit_tiles = grad || sizeof(R) == 8 ? 4 : 8;
-  void *p;
-  if ((s = ws_get(h, W_KEY, 4 * total, &p)) != RIFT_OK) return s;
-  a.key = (uint32_t *)p;
-  if ((s = ws_get(h, W_NSH, 8 * total, &p)) != RIFT_OK) return s;
-  a.nsh = (int16_t *)p;
-  if ((s = ws_get(h, W_COUNT, 4 * (size_t)a.n_bins, &p)) != RIFT_OK) return s;
-  a.count = (uint32_t *)p;
-  if ((s = ws_get(h, W_CURSOR, 4 * (size_t)std::max<int64_t>(hist_total, 1), &p)) != RIFT_OK) return s;
-  a.bhist = (uint32_t *)p;
-  if ((s = ws_get(h, W_BINTILE, 4 * (size_t)a.n_bins, &p)) != RIFT_OK) return s;
-  a.bin_tile = (uint32_t *)p;
-  if ((s = ws_get(h, W_ITEMTILES, 4 * (size_t)(ni + 1), &p)) != RIFT_OK) return s;
-  a.item_tiles = (uint32_t *)p;
-  if ((s = ws_get(h, W_PERM, sizeof(SampleRec) * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-  a.rec = (SampleRec *)p;
-  if ((s = ws_get(h, W_TILES, 8 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-  a.tile_item = (int *)p;
-  a.tile_key = (uint32_t *)p + max_tiles;
-  if ((s = ws_get(h, W_COP, sizeof(R) * (size_t)cop_floats, &p)) != RIFT_OK) return s;
-  a.cop = (R *)p;
+  // The item arrays go up in one copy and share one allocation with the
+  // workspace: the first call on a handle spent most of its time in 7 copies and
+  // 23 allocations (10007 FP64 samples at K = 2, M = 2, first call: 190 us so,
+  // 150 in one piece, 145 in the plain form, whose GPU time is 30 us longer;
+  // three pieces, small enough for the runtime's own pool, took up to 230).
+  std::vector<char> packed;
+  std::vector<std::pair<void *, size_t>> places;  // pointers to set, their offsets
+  auto pack = [&](const auto &v, auto **dst) {
+    places.emplace_back((void *)dst, packed.size());
+    packed.insert(packed.end(), (const char *)v.data(), (const char *)(v.data() + v.size()));
+    packed.resize((packed.size() + 15) & ~(size_t)15);
+  };
+  pack(it.point, &a.items.point);
+  pack(it.off, &a.items.off);
+  pack(it.cnt, &a.items.cnt);
+  pack(samp0, &a.items.samp0);
+  pack(bin0, &a.items.bin0);
+  pack(blk0, &a.items.blk0);
+  pack(hoff, &a.items.hoff);
+  packed.resize((packed.size() + 255) & ~(size_t)255);
+  size_t bytes = packed.size();  // (at the head: what follows never overwrites the arrays last sent)
+  auto take = [&](auto **dst, size_t n) {
+    places.emplace_back((void *)dst, bytes);
+    bytes += (n * sizeof(**dst) + 255) & ~(size_t)255;
+  };
+  const size_t mt = (size_t)max_tiles, nb = (size_t)a.n_bins;
+  take(&a.key, total);
+  take(&a.nsh, 4 * total);
+  take(&a.count, nb);
+  take(&a.bhist, hist_total);
+  take(&a.bin_tile, nb);
+  take(&a.bin_unit, nb);
+  take(&a.item_tiles, ni + 1);
+  take(&a.item_units, ni + 1);
+  take(&a.item_cop, ni);
+  take(&a.tile_item, mt);
+  take(&a.tile_key, mt);
+  take(&a.unit, mt);
+  take(&a.ctl, kCtlWords);
+  take(&a.rec, 16 * mt);
+  take(&a.ctile, mt);
+  take(&a.cop, cop_floats);
   if (grad) {  // the adjoint's per-tile G_k (cop layout) and H_k
-    if ((s = ws_get(h, W_GOP, sizeof(R) * (size_t)cop_floats, &p)) != RIFT_OK) return s;
-    a.gop = (R *)p;
-    if ((s = ws_get(h, W_HOP, sizeof(R) * kMaxDet * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-    a.hop = (R *)p;
-    if (h->refine && sizeof(R) == 4) {
-      if ((s = ws_get(h, W_JRNG, 2 * sizeof(int) * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-      a.jrng = (int *)p;
-    }
+    take(&a.gop, cop_floats);
+    take(&a.hop, kMaxDet * 16 * mt);
+    if (h->refine && sizeof(R) == 4) take(&a.jrng, 2 * 16 * mt);
     a.gin = gin;
     a.grad = grad;
   }
   if (h->dmarg && !grad) {  // distance marginalization: each slot's largest data term
-    if ((s = ws_get(h, W_AMAX, sizeof(float) * 16 * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-    a.amax = (float *)p;
+    take(&a.amax, 16 * mt);
     a.dmarg = 1;
     a.dm_lo = h->d_min;
     a.dm_hi = h->d_max;
   }
-  if ((s = ws_get(h, W_ITEM_COP, sizeof(int64_t) * (size_t)ni, &p)) != RIFT_OK) return s;
-  a.item_cop = (int64_t *)p;
-  if ((s = ws_get(h, W_CTILE, sizeof(CoefTileT<R>) * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-  a.ctile = (CoefTileT<R> *)p;
-  if ((s = ws_get(h, W_UNIT, sizeof(WorkUnit) * (size_t)max_tiles, &p)) != RIFT_OK) return s;
-  a.unit = (WorkUnit *)p;
-  if ((s = ws_get(h, W_BINUNIT, 4 * (size_t)a.n_bins, &p)) != RIFT_OK) return s;
-  a.bin_unit = (uint32_t *)p;
-  if ((s = ws_get(h, W_ITEMUNITS, 4 * (size_t)(ni + 1), &p)) != RIFT_OK) return s;
-  a.item_units = (uint32_t *)p;
-  if ((s = ws_get(h, W_CTL, 4 * kCtlWords, &p)) != RIFT_OK) return s;
-  a.ctl = (uint32_t *)p;
+  void *base;
+  char *head;
+  if ((s = ws_get(h, W_RUN, bytes, &base)) != RIFT_OK) return s;
+  if ((s = upload(h, W_RUN, packed, &head)) != RIFT_OK) return s;
+  for (const auto &x : places) {
+    char *q = head + x.second;
+    std::memcpy(x.first, &q, sizeof q);
+  }
   a.grid = h->n_cu * 4;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (h->prof) {

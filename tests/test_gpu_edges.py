@@ -263,3 +263,36 @@ def test_precompute_by_the_fft(ile):
         _say(f"precompute by the FFT, rows {row0 + r}...: {err:.2e}")
         assert 0.0 < err <= 8.0 * _row_sum_bound(N)  # (a prime grid: three transforms of twice the length and more)
         assert np.array_equal(u, U) and np.array_equal(v, V)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_calls_of_many_shapes_on_one_handle(ile, prec):
+    """Forward and adjoint calls, of one item and of several, large and small,
+    in turn on one handle (graph replay on, in FP32): each gives what it gives
+    alone on a handle of its own, the first time and again, whatever the calls
+    before it left in the shared workspace."""
+    pts = [synth.make_point(synth.PointSpec(seed=synth.BASE_SEED + 1750 + i, dets=("H1", "L1", "V1")[:2 + i],
+                                            n_modes=(5, 9)[i], n_t=60, snr=1.0, kernel="none")) for i in range(2)]
+    th = torch.tensor(synth.mixed_samples(pts[0], 44, 60000))
+    calls = [(60000, [(0, 0, 60000)]), (50000, [(1, 20000, 30000), (0, 0, 20000)]), (500, [(1, 0, 200), (0, 200, 300)]),
+             (60000, [(1, 0, 60000)]), (50000, [(0, 20000, 30000), (1, 0, 20000)])]
+
+    def run(h, c, grad):
+        n, items = c
+        if not grad:
+            return [h.lnL(th[:, :n], items).cpu().numpy()]
+        return [x.cpu().numpy() for x in h.backward(th[:, :n], items=items, want_lnL=True)]
+
+    alone = {}
+    for i, c in enumerate(calls):
+        for grad in (False, True):
+            h = _handle(ile, pts, prec)
+            alone[i, grad] = run(h, c, grad)
+            h.close()
+    h = _handle(ile, pts, prec)
+    h.set_graph(True)
+    _say(f"calls of many shapes {prec}")
+    for i, grad in [(i, g) for _ in range(3) for g in (False, True) for i in range(len(calls))] + [(1, False), (4, False)]:
+        for a, b in zip(run(h, calls[i], grad), alone[i, grad]):
+            assert np.array_equal(a, b, equal_nan=True), (i, grad)
+    h.close()
