@@ -34,9 +34,12 @@ def _hipcc():
 # per-file extra flags: the coefficient pass and the adjoint are scheduled for
 # instruction-level parallelism (the coefficient pass of 1e6 samples at 21 modes
 # 149 us against 165, results bit-identical); the evaluation kernel sets its own
-# order and is 3 % faster at 3 detectors x 21 modes without it (756 against 781 us)
+# order and is 3 % faster at 3 detectors x 21 modes without it (756 against 781 us);
+# the refinement keeps no constants of the FP64 functions in registers through its
+# loop over blocks (22 spilled at 3 detectors x 21 modes with them, none without)
 EXTRA = {"k_mfma.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-         "k_bwd.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+         "k_bwd.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+         "k_refine.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def _compile(src):

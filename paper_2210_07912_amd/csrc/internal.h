@@ -96,6 +96,13 @@ struct WorkUnit {
   uint32_t key;     // the bin, within its point
 };
 
+// Up to 16 samples of one delay bin whose gradient is refined: entries first ..
+// first + n - 1 of MfmaArgs::rslot; their point and bin.
+struct __align__(16) RefineTile {
+  int first, n, point;
+  uint32_t key;
+};
+
 // R: the bulk precision (float, or double for FP64 handles).  A record's theta
 // is FP32: FP64 passes after the sort read a sample's theta at its column.
 template <typename R>
@@ -135,6 +142,9 @@ struct MfmaArgsT {
   int *jrng;              // [16 max_tiles][2] or null: per sorted slot the window blocks whose maximum is within
                           // kRefineNats of the sample's, b0 | b1 << 16, b2 | count << 16 (count 0: not refined;
                           // padding slots are not written)
+  RefineTile *rtile;      // [max_tiles] tiles to refine, each class's from its first tile on (ctl[kCtlUnits2 + c]
+                          // of class c)
+  int *rslot;             // [16 max_tiles] their sorted slots, each work unit's from its first slot on
   // distance marginalization (forward only): a first pass writes each slot's
   // largest window data term, a second integrates over D
   int dmarg;
@@ -204,14 +214,13 @@ inline void fan_join(const Fanout &fo, hipStream_t st, int n_classes) {
 // FP64 re-evaluation of the adjoint over the window blocks that hold each
 // sample's softmax mass (samples whose mass lies in at most kRefineBlocks
 // blocks of 16 window samples, anywhere in the window); writes grad and lnL of
-// those samples of class (T, K), points item_lo..item_hi - 1 (tiles: a bound
-// of theirs).  Launched after
-// the FP32 sweep of the class on the same stream; the chain rule then leaves
-// those samples out.
+// those samples of class cls, (T, K), points item_lo.. (tiles: a bound of
+// theirs).  Launched after the FP32 sweep of the class, which lists them in
+// tiles of one bin, on the same stream; the chain rule then leaves those samples
+// out.
 constexpr int kRefineBlocks = 3;
 constexpr float kRefineNats = 40.f;
-hipError_t refine_backward(const MfmaArgs &a, int T, int K, int item_lo, int item_hi, int64_t tiles,
-                           hipStream_t st);
+hipError_t refine_backward(const MfmaArgs &a, int T, int K, int item_lo, int cls, int64_t tiles, hipStream_t st);
 // the part all share: delay-bin sort, tile records, coefficient pass, work units
 template <typename R>
 hipError_t mfma_prepare(const MfmaArgsT<R> &a, const int *mclass_M, const int *mclass_item0,

@@ -42,18 +42,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
   __shared__ __align__(16) float pring_all[kWaves * kTS * kRP];
   __shared__ __align__(16) float stage[3 * SF];  // block b in buffer b % 3
   __shared__ WorkUnit unit_sh;
+  __shared__ int refine_sh;  // samples of the unit to refine, so far
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   float *ring = ring_all + wave * (K * kTS * kRZ);  // [det][sample][kRZ]
   float *pring = pring_all + wave * (kTS * kRP);     // [sample][kRP]
   const int s = lane & 15, g = lane >> 4;
-  const uint32_t u_lo = a.item_units[item_lo], u_hi = a.item_units[item_hi];
+  const uint32_t u_lo = a.item_units[item_lo], u_hi = a.item_units[item_hi], t_lo = a.item_tiles[item_lo];
   const int tid = threadIdx.x;
   const bool st_on = tid < 16 * T;
   const uint32_t st_goff = 16u * (uint32_t)tid;
   const int st_loff = (tid / T) * ES + 4 * (tid % T);
 
+  RefineTile prev = {0, 0, 0, 0u};  // the last unit's slots, point and bin
+  if (tid == 0) refine_sh = 0;
   for (;;) {
     if (tid == 0) {
+      // the last unit's samples to refine, in tiles of 16 (one counter's answer
+      // is waited for with the other's)
+      const int n = refine_sh;
+      uint32_t at = 0;
+      if (n > 0) at = atomicAdd(&a.ctl[kCtlUnits2 + cls], (uint32_t)((n + kTS - 1) / kTS));
       const uint32_t u = u_lo + atomicAdd(&a.ctl[1 + cls], 1u);
       WorkUnit w;
       if (u < u_hi) {
@@ -64,6 +72,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
         w.key = 0;
       }
       unit_sh = w;
+      refine_sh = 0;
+      for (int i = 0; i < n; i += kTS)
+        a.rtile[t_lo + at + i / kTS] = RefineTile{prev.first + i, min(kTS, n - i), prev.point, prev.key};
     }
     __syncthreads();
     const uint32_t t0 = __builtin_amdgcn_readfirstlane(unit_sh.tile);
@@ -73,7 +84,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
     const bool active = wave < ntiles;
     const uint32_t t = t0 + (active ? wave : 0);
     const int it = __builtin_amdgcn_readfirstlane(a.tile_item[t0]);
-    const PointDev &p = a.pts[a.items.point[it]];
+    const int pt = __builtin_amdgcn_readfirstlane(a.items.point[it]);
+    const PointDev &p = a.pts[pt];
     const int NT = p.n_t, P = p.pad, Lpad = p.Lpad;
     const RIFT_GLOBAL float *qk[K];
     int lo_k[K];
@@ -361,14 +373,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) m
             const float thr = t1 - kRefD2;
             const int nb = (t2 >= thr ? (t3 >= thr ? 3 : 2) : 1);
             const bool ok = valid && t1 > -3.0e38f && rest < thr && i1 < 65536 && i2 < 65536 && i3 < 65536;
-            RIFT_GLOBAL int *jo = gpw(a.jrng) + 2 * ((size_t)t * kTS + s);
+            const size_t slot = (size_t)t * kTS + s;
+            RIFT_GLOBAL int *jo = gpw(a.jrng) + 2 * slot;
             jo[0] = i1 | ((nb > 1 ? i2 : 0) << 16);
             jo[1] = ok ? (nb > 2 ? i3 : 0) | (nb << 16) : 0;
+            // (lanes 0..15: one count per wavefront)
+            const uint32_t listed = (uint32_t)__ballot(ok);
+            int first = 0;
+            if (listed != 0u && s == __builtin_ctz(listed)) first = atomicAdd(&refine_sh, __builtin_popcount(listed));
+            first = __shfl(first, listed != 0u ? __builtin_ctz(listed) : 0);
+            if (ok) gpw(a.rslot)[(size_t)t0 * kTS + first + __builtin_popcount(listed & ((1u << s) - 1u))] = (int)slot;
           }
           if (a.lnL) gpw(a.lnL)[col] = lt;
           if (a.lnw) gpw(a.lnw)[col] = lt + (a.ln_ratio ? gp(a.ln_ratio)[col] : 0.f);
         }
       }
+    }
+    if (a.jrng) {
+      prev = RefineTile{(int)(t0 * kTS), 0, pt, unit_sh.key};
+      __syncthreads();  // every wavefront has listed its samples
     }
   }
 }
@@ -588,7 +611,7 @@ hipError_t mfma_backward(const MfmaArgs &a, const int *class_T, const int *class
     int64_t tiles = 0;  // of the runs that the class has points of
     for (int m = 0; m < n_mclasses; m++)
       if (mclass_item0[m] < hi && mclass_item0[m + 1] > lo) tiles += mclass_tiles[m];
-    e = refine_backward(a, class_T[c], K, lo, hi, tiles, sc);
+    e = refine_backward(a, class_T[c], K, lo, c, tiles, sc);
     if (e != hipSuccess) return e;
   }
   fan_join(fo, st, n_classes);

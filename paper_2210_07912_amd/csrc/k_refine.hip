@@ -20,11 +20,14 @@
 // blocks, so the terms of their sums are comparatively small and so is the
 // rounding.
 //
-// A workgroup takes a tile of 16 sorted samples, a wavefront per detector (all
-// detectors in one wavefront need some 300 registers).  The samples share a
+// A workgroup takes up to 16 samples of one delay bin, a wavefront per detector
+// (all detectors in one wavefront need some 300 registers).  The sweep lists
+// the samples to refine of each of its work units (up to 64 slots of a bin), so
+// that these tiles are full however few of a sorted tile's samples need it,
+// and none is started in vain.  The samples of a tile share their
 // delay bin, so the blocks that one of them needs start at the same rows for
 // all, and they mostly need the same ones: the workgroup walks the union of
-// their blocks (2.8 for 12 in all, of 10.5 samples a tile, at the size below),
+// their blocks (2.8 for the 12 of 10.5 samples, at the size below),
 // the contraction and G_k = Q_k^T c_k on the FP64 matrix cores as in the FP64
 // path (k_eval64.hip), with Q from the FP32 matrix-core layout (FP32 values,
 // exact in FP64); ell_j is summed over the detectors through LDS.  U and V
@@ -37,12 +40,11 @@
 //
 // A wavefront per sample (lanes over rows, modes and window samples, vector
 // FP64, the sums over the wavefront) took 574 us for 1e5 samples at K = 3,
-// M = 21, n_t = 820, by 1540 vector instructions and 87 loads a sample.  This
-// form takes 261 us: matrix products 70 us, vector instructions 77 us, the rest
-// latency at the three wavefronts per SIMD it is compiled for (at two 319 us)
-// and about 10 ns a workgroup to start one.  Of prior draws of a loud point
-// (four samples a tile to refine, mostly in different blocks) it takes 305 us
-// where a wavefront per sample took 232.
+// M = 21, n_t = 820, half of them near the source, and 231 us for prior draws,
+// by 1540 vector instructions and 87 loads a sample.
+// The sorted tiles themselves took 261 and 294 us: of prior draws four samples a
+// tile, and a workgroup for every tile (some 10 ns each).  This form takes 202
+// and 176 us.
 #include "common.h"
 #include "internal.h"
 #include "mfma_tile.h"
@@ -62,7 +64,7 @@ __device__ __forceinline__ double shfl_xor_d(double v, int o) {
 }
 
 template <int T>
-__global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_eu(3))) refine_kernel(MfmaArgs a, int item_lo, int item_hi) {
+__global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_eu(3))) refine_kernel(MfmaArgs a, int item_lo, int cls) {
   constexpr int U = T / 2, OD = T & 1;   // pairs of instructions; an odd one
   constexpr int E = 4 * T;               // elements per row
   constexpr int MT = (E + 15) / 16;      // 16-element tiles of G
@@ -78,18 +80,15 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
   double *const buf = buf_all + k * ZB;
   // (one tile per workgroup: in a loop over tiles the compiler keeps the
   // constants of the FP64 functions in some 100 registers)
-  const uint32_t t = a.item_tiles[item_lo] + blockIdx.x;
-  if (t >= a.item_tiles[item_hi]) return;
-  uint32_t key = __builtin_amdgcn_readfirstlane(a.tile_key[t]);
-  if (key == kNoBin) return;  // the tiles that round a point up to groups of 4
-  const SampleRec rec = a.rec[(size_t)t * kTS + s];
-  RIFT_GLOBAL int *const jr = gpw(a.jrng) + 2 * ((size_t)t * kTS + s);
-  const int b01 = jr[0], b2n = jr[1];
-  const int nb = rec.flag == 1 ? b2n >> 16 : 0;  // (unset in padding slots)
-  const bool on = nb >= 1 && nb <= kRefineBlocks;
-  if (!__any(on)) return;  // the same for the whole workgroup
-  const int it = __builtin_amdgcn_readfirstlane(a.tile_item[t]);
-  const int pt = __builtin_amdgcn_readfirstlane(a.items.point[it]);
+  if (blockIdx.x >= *cp(a.ctl + kCtlUnits2 + cls)) return;
+  const RIFT_CONST RefineTile &rt = *cp(a.rtile + *cp(a.item_tiles + item_lo) + blockIdx.x);
+  const bool on = s < rt.n;
+  const uint32_t slot = (uint32_t)gp(a.rslot)[rt.first + (on ? s : 0)];
+  const SampleRec rec = a.rec[slot];
+  RIFT_GLOBAL int *const jr = gpw(a.jrng) + 2 * (size_t)slot;
+  const int b01 = jr[0], b2n = jr[1], nb = b2n >> 16;
+  uint32_t key = rt.key;
+  const int pt = rt.point;
   const RIFT_CONST PointDev &p = *cp(a.pts + pt);
   const int NT = p.n_t, P = p.pad, M = p.M;
   const int JB = (NT + 15) >> 4, rem = NT - 16 * (JB - 1);
@@ -98,7 +97,7 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
   const RIFT_GLOBAL float *const qk = gp(p.Qm) + (size_t)(k * p.Lpad + P + lo) * E;
   double th[7];
 #pragma unroll
-  for (int d = 0; d < 7; d++) th[d] = rec.flag == 1 ? (double)rec.th[d] : (d == RIFT_DIST ? 1.0 : 0.0);
+  for (int d = 0; d < 7; d++) th[d] = (double)rec.th[d];
   // an angle per lane group: the first four by the first wavefront, phi by the last
   for (int i = k == 0 ? 0 : 4; i < (k == K - 1 ? 5 : 4); i += 4) {
     const int d = i + g;
@@ -166,7 +165,7 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
     xr = x * Fp;
     xi = x * Fc;
   }
-  const int n = on ? (int)gp(a.rec)[(size_t)t * kTS + s].n[k] : lo;
+  const int n = on ? (int)gp(a.rec)[slot].n[k] : lo;
   double w[4], wd[4];
   {
     const double mu = on ? (th[RIFT_TAU] + delay(rc, trig())) * p.f_s - (double)n : 0.0;
@@ -397,7 +396,7 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
   // this detector's parts: Re(conj(x F) S), F = Fp + i Fc; B in out[7]
   // (the distance and the angles read again, not kept through the blocks)
   wave_sync();
-  const double dist = rec.flag == 1 ? (double)gp(a.rec)[(size_t)t * kTS + s].th[RIFT_DIST] : 1.0, x = p.d_ref / dist;
+  const double dist = (double)gp(a.rec)[slot].th[RIFT_DIST], x = p.d_ref / dist;
   const SkyTrig tr = trig();
   double out[8], Fp, Fc, dFa[2], dFd[2];
   antenna(D, tr, Fp, Fc, dFa, dFd);
@@ -441,15 +440,15 @@ __global__ void __launch_bounds__(64 * kMaxDet) __attribute__((amdgpu_waves_per_
 }
 
 template <int T>
-static void launch_refine(const MfmaArgs &a, int K, int lo, int hi, int64_t tiles, hipStream_t st) {
-  hipLaunchKernelGGL((refine_kernel<T>), dim3((unsigned)tiles), dim3(64 * K), 0, st, a, lo, hi);
+static void launch_refine(const MfmaArgs &a, int K, int lo, int cls, int64_t tiles, hipStream_t st) {
+  hipLaunchKernelGGL((refine_kernel<T>), dim3((unsigned)tiles), dim3(64 * K), 0, st, a, lo, cls);
 }
 
-hipError_t refine_backward(const MfmaArgs &a, int T, int K, int lo, int hi, int64_t tiles, hipStream_t st) {
+hipError_t refine_backward(const MfmaArgs &a, int T, int K, int lo, int cls, int64_t tiles, hipStream_t st) {
   if (a.total <= 0 || tiles <= 0 || !a.jrng) return hipSuccess;
   switch (T) {
 #define RIFT_T_CASE(TT) \
-  case TT: launch_refine<TT>(a, K, lo, hi, tiles, st); break;
+  case TT: launch_refine<TT>(a, K, lo, cls, tiles, st); break;
     RIFT_T_CASE(1) RIFT_T_CASE(2) RIFT_T_CASE(3) RIFT_T_CASE(4) RIFT_T_CASE(5) RIFT_T_CASE(6) RIFT_T_CASE(7)
     RIFT_T_CASE(8) RIFT_T_CASE(9) RIFT_T_CASE(10) RIFT_T_CASE(11) RIFT_T_CASE(12) RIFT_T_CASE(13)
     RIFT_T_CASE(14) RIFT_T_CASE(15) RIFT_T_CASE(16)

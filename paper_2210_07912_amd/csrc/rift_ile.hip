@@ -585,7 +585,7 @@ template <typename R>
 double group_bytes(const rift_ile *h, const PointDev &p, int64_t cnt, bool grad) {
   const double operands = (double)p.K * 2 * p.Mp * 16 * sizeof(R);
   const double tile = 16.0 * sizeof(SampleRec) + 8.0 + sizeof(CoefTileT<R>) + sizeof(WorkUnit) + operands +
-                      (grad ? operands + kMaxDet * 16.0 * sizeof(R) + (sizeof(R) == 4 ? 128.0 : 0.0) : 0.0) +
+                      (grad ? operands + kMaxDet * 16.0 * sizeof(R) + (sizeof(R) == 4 ? 200.0 : 0.0) : 0.0) +
                       (h->dmarg ? 64.0 : 0.0);
   return 12.0 * cnt + tile * tile_bound<R>(p, cnt, grad) + p.n_bins_key * (12.0 + 4.0 * ((cnt + 4095) / 4096));
 }
@@ -670,6 +670,8 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   // three pieces, small enough for the runtime's own pool, took up to 230).
   std::vector<char> packed;
   std::vector<std::pair<void *, size_t>> places;  // pointers to set, their offsets
+  packed.reserve(64 * (size_t)ni + 512);
+  places.reserve(32);
   auto pack = [&](const auto &v, auto **dst) {
     places.emplace_back((void *)dst, packed.size());
     packed.insert(packed.end(), (const char *)v.data(), (const char *)(v.data() + v.size()));
@@ -708,7 +710,11 @@ rift_status run_mfma_group(rift_ile *h, const Items &it, int64_t stride, const R
   if (grad) {  // the adjoint's per-tile G_k (cop layout) and H_k
     take(&a.gop, cop_floats);
     take(&a.hop, kMaxDet * 16 * mt);
-    if (h->refine && sizeof(R) == 4) take(&a.jrng, 2 * 16 * mt);
+    if (h->refine && sizeof(R) == 4) {
+      take(&a.jrng, 2 * 16 * mt);
+      take(&a.rslot, 16 * mt);
+      take(&a.rtile, mt);
+    }
     a.gin = gin;
     a.grad = grad;
   }

@@ -296,3 +296,31 @@ def test_calls_of_many_shapes_on_one_handle(ile, prec):
         for a, b in zip(run(h, calls[i], grad), alone[i, grad]):
             assert np.array_equal(a, b, equal_nan=True), (i, grad)
     h.close()
+
+
+def test_gradient_of_partly_refined_units(ile):
+    """One delay bin, of which every third sample's mass lies in one block and
+    the others' in all ten: work units of 64 slots with 0 to 22 samples to
+    refine, around the tiles of 16 they are gathered in.  Every sample gets what
+    it gets alone, refined or not."""
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1702, dets=("H1",), n_modes=2, n_t=160, snr=1.0, kernel="none")
+    d = dict(synth.make_point(spec))
+    d["det_pos"] = np.zeros((1, 3))
+    th = synth.mixed_samples(d, 45, 200)
+    th[6] = 0.0
+    th[5] = np.where(np.arange(200) % 3 == 0, 20.0, 4000.0) + 0.25 * np.arange(200)
+    r = np.arange(d["Q"].shape[1]) - d["Q"].shape[1] // 2
+    g = np.random.default_rng(46)
+    d["Q"] = 30.0 * (g.standard_normal((1, r.size, 2)) + 1j * g.standard_normal((1, r.size, 2)))
+    d["Q"] *= (0.01 + 30.0 * np.exp(-0.5 * ((r - 5) / 3.0) ** 2))[None, :, None]
+    t = torch.tensor(th.astype(np.float32))
+    h = _handle(ile, [d], "fp32")
+    alone = np.concatenate([h.backward(t[:, i:i + 1]).cpu().numpy() for i in range(200)], axis=1)
+    h.set_grad_refine(False)
+    changed = (h.backward(t).cpu().numpy() != alone).any(axis=0)
+    h.set_grad_refine(True)
+    _say(f"partly refined units: {changed[::3].sum()} of {changed[::3].size} near samples refined")
+    assert changed[::3].mean() > 0.5
+    for n in (1, 3, 46, 48, 49, 64, 65, 97, 128, 145, 200):
+        assert np.array_equal(h.backward(t[:, :n]).cpu().numpy(), alone[:, :n]), n
+    h.close()
