@@ -595,9 +595,11 @@ static void launch_tk(const MfmaArgs &a, int lo, int hi, int cls, hipStream_t st
 // The passes of distance marginalization run one wavefront per SIMD, with all
 // its registers, in calls of at most kOneWave samples per compute unit: those
 // have no second wavefront to share it (a workgroup takes 128 samples), and
-// the forms for two keep part of the nodes and sums in scratch memory.  3370
-// samples at K = 3, M = 9, n_t = 105 take 95 us, in the form for two 123; 64000
-// at K = 2, M = 5, n_t = 300 take 165 us, in the form for two 150.
+// the forms for two keep part of the nodes and sums in scratch memory.  Of
+// twelve shapes (K = 1..3, M = 2..21, n_t = 105..820) the form for one takes 0.65
+// to 0.99 of the other's time at 8 samples per compute unit (one shape 1.06),
+// 0.88 to 1.08 at 128 (K = 3, M = 9, n_t = 105: 138 and 147 us; n_t = 500: 263 and
+// 249) and 1.00 to 1.19 at 400 (but for M = 21 at K = 3, where they are alike).
 constexpr int kOneWave = 128;
 
 // pass: 0 ln L_t (staged or direct feed); 1, 2 the passes of distance

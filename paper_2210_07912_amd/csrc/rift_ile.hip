@@ -878,28 +878,55 @@ Items make_items(int n_items, const rift_ile_item *items) {
   return it;
 }
 
-// FP64 calls that go to the sorted matrix-core form: by units of K n_t (M + 4)
-// per sample.  Below the line the sort's launches cost more than the plain
-// kernel's one: 10007 samples at K = 2, M = 2, n_t = 410 (4.9e7) take 73 us
-// there and 57 us sorted, 5 x 3226 at K = 3, M = 5, n_t = 128 (5.6e7) 71 and
-// 79 us; with the gradient 5 x 697 at K = 3, M = 12, n_t = 107 (1.8e7) 200 and
-// 231 us, 20000 at K = 3, M = 9 (3.2e8) 2586 and 291 us.  What the plain form refuses stays
-// refused; what it takes and the sorted form does not (more than 2^31 columns,
-// the bins of a very large pad) stays with it, and so does distance
-// marginalization.
+// FP64 calls that go to the sorted matrix-core form, by units of work, K n_t
+// (M + 4) a sample.  What the plain form refuses stays refused; what it takes and
+// the sorted form does not (more than 2^31 columns, the bins of a very large
+// pad) stays with it, and so does distance marginalization.
+//
+// With the gradient: from 3e7 units on.  Of 170 calls (K = 1..3, M = 2..21, n_t =
+// 100..820, 1..16 points, 3e6 to 2e8 units) none above the line was slower
+// sorted than plain, a call of 2e8 units up to 11 times as fast; below it most
+// would be too, by up to three times.
+//
+// Forward: from 4e7 units (three detectors: 6e7) on, where the sorted form's
+// time is the shorter one by a model of both (us, fitted to 170 calls of 1e7 to
+// 4e8 units; half of the errors within 6 and 9 %): the sort, a wavefront's walk over
+// the blocks of the longest window, and the tiles, of which every bin that
+// delays reach has one that is not full; the plain kernel's units and window
+// samples.  The tile's walk is what costs at many modes and long windows: 1000
+// samples of one point at K = 3, M = 21, n_t = 800 (6e7 units) take 87 us in the
+// plain kernel and 236 sorted, 3333 of them 239 and 237, 10^4 samples at M = 2,
+// K = 2 (4.9e7) 73 and 57.  Where one of the 170 went to the slower form it lost
+// 20 % at most, one per cent on average (by units alone 59 %).
 bool use_sorted64(const rift_ile *h, const Items &it, int64_t stride, bool bwd) {
   if (h->dmarg && !bwd) return false;
   if (stride > (int64_t)INT32_MAX || plain_samples(h, 8, bwd) == 0) return false;
-  double work = 0.0;
+  double work = 0.0, window = 0.0, tiles = 0.0, walk = 0.0, walk_p = 0.0;
   int K = 1;
   for (size_t i = 0; i < it.point.size(); i++) {
     const PointDev &p = h->hp[it.point[i]];
     if (p.n_bins_key > (1 << 16)) return false;
-    work += (double)it.cnt[i] * p.K * p.n_t * (p.M + 4);
+    const double n = (double)it.cnt[i], unit = (double)p.K * p.n_t * (p.M + 4);
+    work += n * unit;
+    if (bwd || n == 0.0) continue;
+    // bins along a detector's delays, and those that delays of one source and
+    // window offset reach together
+    double r = 0.0;
+    for (int k = 0; k < p.K; k++)
+      r = std::max(r, std::sqrt(p.rc[k][0] * p.rc[k][0] + p.rc[k][1] * p.rc[k][1] + p.rc[k][2] * p.rc[k][2]));
+    const double nl = 2.0 * r * p.f_s / p.bin_w + 1.0, spread = 1.0 + h->tau_width * p.f_s / p.bin_w;
+    const double bins = std::min<double>(p.n_bins_key, spread * (p.K == 1 ? nl : (p.K == 2 ? 0.45 : 1.6) * nl * nl));
+    const double blocks = p.n_t / 16.0 + 1.0;
+    window += n * p.n_t;
+    tiles += unit * (n + 16.0 * std::min(n, bins));
+    walk = std::max(walk, blocks * (0.28 + 0.039 * p.K * (p.Mp >> 1)));
+    walk_p = std::max(walk_p, blocks * p.K);
     K = std::max(K, p.K);
   }
-  // (three detectors have some four times the bins of two, and fuller tiles later)
-  return work >= (bwd ? 3.0e7 : K == 3 ? 6.0e7 : 4.0e7);
+  if (bwd) return work >= 3.0e7;
+  const double sorted = 53.0 + 5.0 * K + walk + 1.4e-7 * tiles;
+  const double plain = 31.0 + 0.93e-6 * work + 5.0e-6 * window + 0.1 * walk_p;
+  return work >= (K == 3 ? 6.0e7 : 4.0e7) && sorted < plain;
 }
 
 template <typename R>

@@ -324,3 +324,25 @@ def test_gradient_of_partly_refined_units(ile):
     for n in (1, 3, 46, 48, 49, 64, 65, 97, 128, 145, 200):
         assert np.array_equal(h.backward(t[:, :n]).cpu().numpy(), alone[:, :n]), n
     h.close()
+
+
+@pytest.mark.parametrize("K,M,n_t,n,sorted_form", [(3, 21, 800, 1020, False), (2, 21, 800, 1100, False), (3, 9, 400, 3900, False),
+                                                   (2, 2, 410, 10007, True), (3, 21, 800, 20000, True)])
+def test_fp64_form_by_size(ile, K, M, n_t, n, sorted_form):
+    """Which form an FP64 forward call takes: at long windows and many modes
+    the sorted form pays later than its units of work say (1000 samples at K =
+    3, M = 21, n_t = 800 are 2.7 times as fast in the plain form).  Small parts
+    of the call, plain by their size, agree with it bit for bit only where
+    the whole call is plain, too."""
+    spec = synth.PointSpec(seed=synth.BASE_SEED + 1760 + M, dets=("H1", "L1", "V1")[:K], n_modes=M, n_t=n_t, snr=1.0,
+                           kernel="none")
+    d = synth.make_point(spec)
+    th = torch.tensor(synth.mixed_samples(d, 47, n))
+    h = _handle(ile, [d], "fp64")
+    _say(f"fp64 form K={K} M={M} n_t={n_t} n={n}")
+    out = h.lnL(th).cpu().numpy()
+    part = n // 40
+    parts = np.concatenate([h.lnL(th[:, a:a + part]).cpu().numpy() for a in range(0, n, part)])
+    h.close()
+    assert np.array_equal(out, parts) != sorted_form
+    assert np.allclose(out, parts, rtol=1e-12, atol=1e-11)
