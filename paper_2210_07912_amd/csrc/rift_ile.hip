@@ -878,55 +878,64 @@ Items make_items(int n_items, const rift_ile_item *items) {
   return it;
 }
 
-// FP64 calls that go to the sorted matrix-core form, by units of work, K n_t
-// (M + 4) a sample.  What the plain form refuses stays refused; what it takes and
-// the sorted form does not (more than 2^31 columns, the bins of a very large
-// pad) stays with it, and so does distance marginalization.
+// FP64 calls that go to the sorted matrix-core form.  What the plain form
+// refuses stays refused; what it takes and the sorted form does not (more than
+// 2^31 columns, the bins of a very large pad) stays with it, and so does
+// distance marginalization.
 //
-// With the gradient: from 3e7 units on.  Of 170 calls (K = 1..3, M = 2..21, n_t =
-// 100..820, 1..16 points, 3e6 to 2e8 units) none above the line was slower
-// sorted than plain, a call of 2e8 units up to 11 times as fast; below it most
-// would be too, by up to three times.
+// With the gradient: from 3e7 units of work, K n_t (M + 4) a sample.  Of 170
+// calls (K = 1..3, M = 2..21, n_t = 100..820, 1..16 points, 3e6 to 2e8 units)
+// none above the line was slower sorted than plain, a call of 2e8 units up to
+// 11 times as fast; below it most would be too, by up to three times.
 //
-// Forward: from 4e7 units (three detectors: 6e7) on, where the sorted form's
-// time is the shorter one by a model of both (us, fitted to 170 calls of 1e7 to
-// 4e8 units; half of the errors within 6 and 9 %): the sort, a wavefront's walk over
-// the blocks of the longest window, and the tiles, of which every bin that
-// delays reach has one that is not full; the plain kernel's units and window
-// samples.  The tile's walk is what costs at many modes and long windows: 1000
-// samples of one point at K = 3, M = 21, n_t = 800 (6e7 units) take 87 us in the
-// plain kernel and 236 sorted, 3333 of them 239 and 237, 10^4 samples at M = 2,
-// K = 2 (4.9e7) 73 and 57.  Where one of the 170 went to the slower form it lost
-// 20 % at most, one per cent on average (by units alone 59 %).
+// Forward: from 4e7 units (K = 3: 6e7) on, where the sorted form's time is the
+// shorter one by a model of both (us), fitted to 670 calls of 1e7 to 4e8 units.
+// Sorted: the sort's launches, a wavefront's walk over the blocks of the window,
+// and the tiles, one of them not full in every bin that the delays of one source
+// reach.  Plain: the rounds of its workgroups through the compute units (TS
+// samples each, some at a time).  By the units alone 41 of 500 calls were more
+// than 10 % slower sorted than plain: 1000 samples at K = 3, M = 21, n_t = 800
+// take 87 us plain and 236 sorted, 2 x 2506 at K = 3, M = 5, n_t = 569 76 and 110,
+// 3333 at K = 3, M = 21, n_t = 800 239 and 237, 10007 at K = 2, M = 2, n_t = 410
+// 73 and 57.  By the model none of 670 calls (nor of 200 of windows below 100) is
+// more than 10 % slower than plain; six go to the plain form although the sorted
+// one is 10 to 22 % faster.
 bool use_sorted64(const rift_ile *h, const Items &it, int64_t stride, bool bwd) {
   if (h->dmarg && !bwd) return false;
-  if (stride > (int64_t)INT32_MAX || plain_samples(h, 8, bwd) == 0) return false;
-  double work = 0.0, window = 0.0, tiles = 0.0, walk = 0.0, walk_p = 0.0;
-  int K = 1;
+  const int TS = plain_samples(h, 8, bwd);
+  if (stride > (int64_t)INT32_MAX || TS == 0) return false;
+  double work = 0.0, samples = 0.0, walk = 0.0, tiles = 0.0, groups = 0.0, group_us = 0.0;
+  int most_det = 1;
   for (size_t i = 0; i < it.point.size(); i++) {
     const PointDev &p = h->hp[it.point[i]];
     if (p.n_bins_key > (1 << 16)) return false;
-    const double n = (double)it.cnt[i], unit = (double)p.K * p.n_t * (p.M + 4);
+    const double n = (double)it.cnt[i], K = p.K, M = p.M, nt = p.n_t, unit = K * nt * (M + 4.0);
+    if (n == 0.0) continue;
     work += n * unit;
-    if (bwd || n == 0.0) continue;
-    // bins along a detector's delays, and those that delays of one source and
-    // window offset reach together
+    most_det = std::max(most_det, p.K);
+    if (bwd) continue;
+    // bins along one detector's delays, and those reached by the delays of one
+    // source to all of them and the offsets of the window
     double r = 0.0;
     for (int k = 0; k < p.K; k++)
       r = std::max(r, std::sqrt(p.rc[k][0] * p.rc[k][0] + p.rc[k][1] * p.rc[k][1] + p.rc[k][2] * p.rc[k][2]));
     const double nl = 2.0 * r * p.f_s / p.bin_w + 1.0, spread = 1.0 + h->tau_width * p.f_s / p.bin_w;
-    const double bins = std::min<double>(p.n_bins_key, spread * (p.K == 1 ? nl : (p.K == 2 ? 0.45 : 1.6) * nl * nl));
-    const double blocks = p.n_t / 16.0 + 1.0;
-    window += n * p.n_t;
-    tiles += unit * (n + 16.0 * std::min(n, bins));
-    walk = std::max(walk, blocks * (0.28 + 0.039 * p.K * (p.Mp >> 1)));
-    walk_p = std::max(walk_p, blocks * p.K);
-    K = std::max(K, p.K);
+    const double bins = std::min<double>(p.n_bins_key, spread * (p.K == 1 ? nl : (p.K == 2 ? 0.71 : 3.5) * nl * nl));
+    samples += n;
+    walk = std::max(walk, (nt / 16.0 + 1.0) * K * (0.13 + 0.052 * (p.Mp >> 1)));
+    tiles += unit * (n / 16.0 + bins * (1.0 - std::exp(-n / bins)));
+    const double g = std::ceil(n / TS);
+    groups += g;
+    group_us += g * (3.1 + 0.17 * K * std::ceil((nt + 60.0) / 256.0) * M +
+                     1e-3 * TS * (1.55 * K * nt + 0.49 * nt + 1.36 * K * M * M));
   }
-  if (bwd) return work >= 3.0e7;
-  const double sorted = 53.0 + 5.0 * K + walk + 1.4e-7 * tiles;
-  const double plain = 31.0 + 0.93e-6 * work + 5.0e-6 * window + 0.1 * walk_p;
-  return work >= (K == 3 ? 6.0e7 : 4.0e7) && sorted < plain;
+  if (work < (bwd ? 3.0e7 : most_det == 3 ? 6.0e7 : 4.0e7)) return false;
+  if (bwd) return true;
+  const double sorted = 59.0 + walk + 1.5e-6 * tiles + 3.0e-4 * samples;
+  const int at_once = std::max(1, std::min(8, (int)((h->lds_max + 1024) / plain_lds_bytes(8, TS, h->max_L, h->max_nt, false))));
+  const double load = groups / h->n_cu, full = std::floor(load / at_once), rest = std::ceil(load - full * at_once);
+  auto round = [&](double k) { return k > 0.0 ? group_us / groups * (0.48 + 0.52 * k) : 0.0; };
+  return sorted < 21.0 + full * round(at_once) + round(rest);
 }
 
 template <typename R>

@@ -326,8 +326,9 @@ def test_gradient_of_partly_refined_units(ile):
     h.close()
 
 
-@pytest.mark.parametrize("K,M,n_t,n,sorted_form", [(3, 21, 800, 1020, False), (2, 21, 800, 1100, False), (3, 9, 400, 3900, False),
-                                                   (2, 2, 410, 10007, True), (3, 21, 800, 20000, True)])
+@pytest.mark.parametrize("K,M,n_t,n,sorted_form", [
+    (3, 21, 800, 1020, False), (2, 21, 800, 1100, False), (3, 9, 400, 3900, False), (3, 5, 569, 5012, False),
+    (2, 2, 410, 10007, True), (3, 21, 800, 20000, True)])
 def test_fp64_form_by_size(ile, K, M, n_t, n, sorted_form):
     """Which form an FP64 forward call takes: at long windows and many modes
     the sorted form pays later than its units of work say (1000 samples at K =
