@@ -366,13 +366,16 @@ rift_status rift_ile_set_autotune(rift_ile *h, int mode);
 rift_status rift_ile_autotune_table(const rift_ile *h, int *modes);
 
 /* Persisted autotuning.  path: a text file of lines
- * "<arch> <T> <K> <n_t bucket> <configuration>" (arch: the device's gfx
- * name).  The lines for this device's arch are read now (later lines win;
- * malformed lines are skipped; a missing file is not an error) and every
- * configuration the handle measures from now on is appended, so another
- * handle or process that loads the file starts with those classes measured.
- * NULL: stop appending.  Errors: RIFT_E_INVALID for a NULL handle or a file
- * that exists but cannot be read; a failed append is skipped silently. */
+ * "<arch>/<kernels> <T> <K> <n_t bucket> <configuration>" (arch: the device's
+ * gfx name; kernels: the number of the evaluation kernels measured, which
+ * changes with them).  The lines for this device's arch and this library's
+ * kernels are read now (later lines win; other and malformed lines are skipped,
+ * among them those of files without the number, of earlier kernels; a missing
+ * file is not an error) and every configuration the handle measures from now on
+ * is appended, so another handle or process that loads the file starts with
+ * those classes measured.  NULL: stop appending.  Errors: RIFT_E_INVALID for a
+ * NULL handle or a file that exists but cannot be read; a failed append is
+ * skipped silently. */
 rift_status rift_ile_set_autotune_cache(rift_ile *h, const char *path);
 
 /* Extrinsic sample draw (Sec. II.A; Sec. III.B: random numbers generated on

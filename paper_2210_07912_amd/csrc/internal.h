@@ -53,6 +53,7 @@ constexpr int kCtlUnits2 = 2 + kMaxClasses;  // first of the unit counters of a 
 constexpr int kCtlWords = kCtlUnits2 + kMaxClasses;
 constexpr int kNtBuckets = 17;   // autotuner key: floor(log2 n_t) of a class's longest window
 constexpr int kFeedConfigs = 7;  // launch configurations the autotuner measures per class
+constexpr int kTuneKernels = 2;  // the evaluation kernels that persisted measurements are of: raised when these change
 
 // samples per sort block: 4096, or less for a call that would not fill the
 // device with those (64 blocks at 2^18 samples; more, smaller blocks are more

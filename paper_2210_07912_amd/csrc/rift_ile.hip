@@ -76,7 +76,7 @@ struct rift_ile {
   int kmode[kMaxT + 1][kMaxDet + 1] = {};
   int tune[kMaxT + 1][kMaxDet + 1][kNtBuckets] = {};
   std::string tune_path;
-  std::string arch;
+  std::string arch;  // gfx name, '/' and kTuneKernels: what measurements are valid for
   double ws_budget = 6.0e9;
   // FP64 refinement of the matrix-core adjoint (rift_ile_set_grad_refine)
   bool refine = true;
@@ -1306,6 +1306,7 @@ rift_status rift_ile_create(rift_ile **out, const rift_ile_desc *desc, void *str
       h->arch = an.substr(0, an.find(':'));
     }
     if (h->arch.empty()) h->arch = "unknown";
+    h->arch += "/" + std::to_string(kTuneKernels);
   }
   if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device) == hipSuccess && v > 0)
     h->lds_max = std::min(v, 160 * 1024) - 1024;

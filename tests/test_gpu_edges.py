@@ -347,3 +347,30 @@ def test_fp64_form_by_size(ile, K, M, n_t, n, sorted_form):
     h.close()
     assert np.array_equal(out, parts) != sorted_form
     assert np.allclose(out, parts, rtol=1e-12, atol=1e-11)
+
+
+def test_autotune_cache_of_earlier_kernels(ile, tmp_path):
+    """Lines of a cache file that name no kernels, or other ones, are of
+    evaluation kernels that are gone: the class is measured again and its line
+    appended; the lines appended are read back."""
+    d = synth.make_point(synth.workload("tiny").points[0])
+    th = torch.tensor(synth.mixed_samples(d, 48, 500))
+    T, K, bucket = (len(d["ell"]) + 1) // 2, len(d["det_pos"]), int(np.log2(d["n_t"]))
+    path = tmp_path / "tune.txt"
+    h = _handle(ile, [d], "fp32")
+    h.set_autotune_cache(path)
+    h.lnL(th)
+    h.close()
+    tag = path.read_text().split()[0]
+    arch = tag.split("/")[0]
+    text = f"{arch} {T} {K} {bucket} 3\n{arch}/1 {T} {K} {bucket} 3\n"
+    path.write_text(text)
+    _say(f"autotune cache of earlier kernels, tag {tag}")
+    for again in range(2):
+        h = _handle(ile, [d], "fp32")
+        h.set_autotune_cache(path)
+        ref = h.lnL(th)
+        assert torch.equal(h.lnL(th), ref)
+        h.close()
+        new = path.read_text()[len(text):].split()
+        assert path.read_text().startswith(text) and len(new) == 5 and new[0] == tag and tag != arch, again
