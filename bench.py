@@ -30,7 +30,8 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK = {"fp32_mfma_tflops": 157.3, "fp64_tflops": 78.6, "hbm_gbs": 8000.0}
+PEAK = {"fp32_mfma_tflops": 157.3, "bf16_mfma_tflops": 2516.6, "fp64_tflops": 78.6, "hbm_gbs": 8000.0}
+BF16_PRODUCTS = 6  # BF16 products that the FP32 evaluation executes for each FP32 one
 
 # HBM bytes per step of the evaluation kernels, from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE passes (KiB per dispatch, summed over a step's dispatches, scaled
@@ -38,10 +39,10 @@ PEAK = {"fp32_mfma_tflops": 157.3, "fp64_tflops": 78.6, "hbm_gbs": 8000.0}
 # size on the same box), keyed by workload, with the SHA-256 of the kernel
 # source they were taken with.  Reported only while that source is unchanged.
 MEASURED_TRAFFIC = {
-    # profiles/mfma_kernel_batched_512pts.md: 19,761,493 KiB x 2.0 + 6,617,605 KiB x 1.0 over the 8 class dispatches
-    "batched": {"sha256": "c3e061b9d552391d41c590262f4b80b34a8e358ac83bd7d2a4343f7db9ddf69d", "bytes_per_step": 47247965568.0},
-    # profiles/mfma_kernel_single_1e6.md: 167,358 KiB x 2.0 + 33,832 KiB x 1.0
-    "single": {"sha256": "c3e061b9d552391d41c590262f4b80b34a8e358ac83bd7d2a4343f7db9ddf69d", "bytes_per_step": 377393120.0},
+    # profiles/mfma_kernel_batched_512pts.md: 24,795,150 KiB x 2.0 + 14,652,605 KiB x 1.0 over the 8 class dispatches
+    "batched": {"sha256": "656d4afba4e4cdb203d9ff8b5e688c2c8023035d0b2fa76765eea9bddb57d224", "bytes_per_step": 65784734720.0},
+    # profiles/mfma_kernel_single_1e6.md: 414,241 KiB x 2.0 + 429,256 KiB x 1.0
+    "single": {"sha256": "656d4afba4e4cdb203d9ff8b5e688c2c8023035d0b2fa76765eea9bddb57d224", "bytes_per_step": 1287923712.0},
 }
 KERNEL_SOURCE = os.path.join(ROOT, "paper_2210_07912_amd", "csrc", "k_eval.hip")
 
@@ -134,19 +135,22 @@ def measure_forward(name, steps, warmup, graph=True, n_override=0):
     fl_per_launch = fl * steps / max(k_launches, 1)
     k_avg_ms = k_ms / max(k_launches, 1)
     achieved = fl_per_launch / (k_avg_ms * 1e-3) / 1e12 if k_launches else None
-    peak = PEAK["fp32_mfma_tflops"] if fp32 else PEAK["fp64_tflops"]
+    # FP32 products on the BF16 matrix cores, six each; FP64 on the vector or matrix cores (the same peak)
+    peak = PEAK["bf16_mfma_tflops"] / BF16_PRODUCTS if fp32 else PEAK["fp64_tflops"]
     classes = sorted({((len(p["ell"]) + 1) // 2, p["det_pos"].shape[0]) for p in pts})
     roof = {"bound": "mfma" if fp32 else "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
             "frac": (achieved / peak) if achieved else None, "traffic": None,
-            "kernel": ("mfma_kernel<T,K>" if fp32 else "plain_kernel<double>"),
+            "kernel": ("mfma_kernel<G,K>" if fp32 else "eval64_kernel<T,K> or plain_kernel<double>"),
             "classes": [f"T{t}K{k}" for t, k in classes] if fp32 else None,
             "kernel_ms": k_avg_ms, "launches_per_step": k_launches / steps,
             "flops_per_eval": fl / max(evals, 1), "flops_per_launch": fl_per_launch}
     if fp32:
-        # matrix-core FLOP the kernels execute per evaluation: 16-row blocks
-        # 0..ceil(n_t/16) of every detector times 2 M_p elements
-        ex = [2 * p["det_pos"].shape[0] * 16 * ((p["n_t"] + 15) // 16 + 1) * 2 * ((len(p["ell"]) + 1) // 2 * 2)
-              for p in pts]
+        roof["fp32_mfma_frac"] = achieved / PEAK["fp32_mfma_tflops"] if achieved else None
+        # BF16 matrix-core FLOP the kernels execute per evaluation: 32-row blocks
+        # 0..ceil(n_t/32) of every detector times the mode elements in groups of
+        # 8, six products each
+        ex = [2 * p["det_pos"].shape[0] * 32 * ((p["n_t"] + 31) // 32 + 1) * 8 * ((len(p["ell"]) + 3) // 4)
+              * BF16_PRODUCTS for p in pts]
         roof["mfma_executed_per_eval"] = sum(c * e for c, e in zip(counts, ex)) / max(sum(counts), 1)
     tr = MEASURED_TRAFFIC.get(name)
     if tr and not n_override and tr["sha256"] == _sha(KERNEL_SOURCE) and k_launches:
@@ -220,7 +224,7 @@ def measure_grad(steps, warmup, with_errors=True):
     k_avg = k_ms / max(k_launches, 1)
     achieved = fl * steps / max(k_launches, 1) / (k_avg * 1e-3) / 1e12 if k_launches else None
     out = {"value": n / dt, "unit": "gradient evals/s", "ms_per_step": dt * 1e3, "samples": n,
-           "roofline": {"bound": "mfma", "kernel": "mfma_bwd_kernel<11,3>", "achieved": achieved,
+           "roofline": {"bound": "mfma", "kernel": "mfma_bwd_kernel<11,3> + refine_kernel<11>", "achieved": achieved,
                         "peak": PEAK["fp32_mfma_tflops"], "unit": "TFLOP/s",
                         "frac": achieved / PEAK["fp32_mfma_tflops"] if achieved else None, "kernel_ms": k_avg,
                         "flops_per_eval": flops_per_grad(K, M, n_t)}}
@@ -429,7 +433,7 @@ def main():
         N, df = 32768, 0.125
         data, psd, modes, _ = synth.fd_inputs(synth.BASE_SEED + 50, n_det=3, n_modes=21, N=N, df=df, f_low=20.0)
         L = pts[0]["n_t"] + 2 * pts[0]["pad"] + 3
-        ile.precompute(data, psd, modes, df, 20.0, 0, L)  # warm-up (FFT plan, code objects)
+        ile.precompute(data, psd, modes, df, 20.0, 0, L)  # warm-up (code objects)
         t2 = time.perf_counter()
         reps = 5
         for _ in range(reps):
@@ -529,13 +533,14 @@ def main():
         torch.cuda.synchronize()
         t3 = time.perf_counter()
         r32, r64 = h.reduce(l32), h64.reduce(l64)
+        # (an FP64 handle: the sorted matrix-core form at this size)
         out["fp64_plain"] = {"evals_per_s": nn / (t3 - t2), "samples": nn,
                              "lnL_marg_fp32": r32["lnL_marg"], "lnL_marg_fp64": r64["lnL_marg"],
                              "abs_delta_lnL_marg": abs(r32["lnL_marg"] - r64["lnL_marg"]),
                              "max_abs_delta_lnL_t": float((l32.double() - l64a).abs().max())}
         h64.close()
 
-    # the estimate against the FP64 plain form on the very same samples (their
+    # the estimate against FP64 handles on the very same samples (their
     # samples and proposal ratios replayed): for the adaptive workload the
     # first 4 points and the 15 loudest (SNR >= 50) over all rounds, for the
     # batched workload 32 of its points
