@@ -214,6 +214,7 @@ __device__ __forceinline__ V block_scan(V v, V *wsum, V &total) {
   __syncthreads();
   V before = 0;
   total = 0;
+#pragma unroll 4  // (whole, the scheduler of this file loads all at once and spills 14 registers)
   for (int i = 0; i < 16; i++) {
     if (i < wave) before += wsum[i];
     total += wsum[i];
