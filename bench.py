@@ -36,13 +36,13 @@ BF16_PRODUCTS = 6  # BF16 products that the FP32 evaluation executes for each FP
 # HBM bytes per step of the evaluation kernels, from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE passes (KiB per dispatch, summed over a step's dispatches, scaled
 # by 2.0 and 1.0: what the same counters read for a plain device copy of known
-# size on the same box), keyed by workload, with the SHA-256 of the kernel
+# size on the same machine), keyed by workload, with the SHA-256 of the kernel
 # source they were taken with.  Reported only while that source is unchanged.
 MEASURED_TRAFFIC = {
     # profiles/mfma_kernel_batched_512pts.md: 24,795,150 KiB x 2.0 + 14,652,605 KiB x 1.0 over the 8 class dispatches
-    "batched": {"sha256": "656d4afba4e4cdb203d9ff8b5e688c2c8023035d0b2fa76765eea9bddb57d224", "bytes_per_step": 65784734720.0},
+    "batched": {"sha256": "da901b3c2aba284530546e36af3f617785e81f18f61b221e33f52bb4b81dd41d", "bytes_per_step": 65784734720.0},
     # profiles/mfma_kernel_single_1e6.md: 414,241 KiB x 2.0 + 429,256 KiB x 1.0
-    "single": {"sha256": "656d4afba4e4cdb203d9ff8b5e688c2c8023035d0b2fa76765eea9bddb57d224", "bytes_per_step": 1287923712.0},
+    "single": {"sha256": "da901b3c2aba284530546e36af3f617785e81f18f61b221e33f52bb4b81dd41d", "bytes_per_step": 1287923712.0},
 }
 KERNEL_SOURCE = os.path.join(ROOT, "paper_2210_07912_amd", "csrc", "k_eval.hip")
 

@@ -25,9 +25,9 @@ namespace rift {
 //
 // A wavefront takes 32 samples (two tiles) of one delay bin, a workgroup four
 // such pairs of tiles.  Base row of detector k: the lower edge of the bin, so
-// every sample's stencil starts 0..bin_w-1 rows above it.  Per block of 32 rows and detector: the products, then the window
-// samples of the block before it, through a 48-row buffer in LDS that the
-// wavefront writes (the previous block's rows, kept in registers, and the
+// every sample's stencil starts 0..bin_w-1 rows above it.  Per block of 32
+// rows and detector: the products, then the window samples of the block
+// before it, through a 48-row buffer in LDS that the wavefront writes (the previous block's rows, kept in registers, and the
 // first half of this block's) and reads at each sample's own row offset.
 // Rows are 32 floats, one per sample, so every access is free of bank
 // conflicts whatever the offsets, and a lane reads 19 rows for 16 consecutive
@@ -45,9 +45,9 @@ namespace rift {
 //    blocks; a workgroup takes four consecutive pairs of tiles whatever their
 //    bins, so that sparse bins do not leave wavefronts idle (with many samples
 //    the pairs mostly are of one bin, and three of the four reads hit in L1).
-// Bound: the matrix cores (52 % busy at K = 3, M = 21, where the direct feed
-// keeps the L1's 64 bytes per cycle 78 % busy) and, at few modes, the vector
-// work of the window.  Kernel time of 5e5 samples, before (FP32 instructions,
+// Bound: the matrix cores (49 % busy at K = 3, M = 21, where the direct feed
+// makes 0.76 L1 accesses per cycle and compute unit) and, at few modes, the
+// vector work of the window.  Kernel time of 5e5 samples, before (FP32 instructions,
 // 16 x 16 tiles) and now: K = 3: M = 21, n_t = 820 1294 -> 756 us; n_t = 500:
 // M = 9 442 -> 316, M = 5 441 -> 255, M = 2 269 -> 212; K = 2: 818 -> 500,
 // 294 -> 206, 257 -> 169, 200 -> 145.
@@ -73,6 +73,8 @@ namespace rift {
 //    per wavefront, so nowhere else;
 //  * ahead (1 or K): row operands are loaded one detector or, where registers
 //    allow, one whole block ahead.
+// It is an estimate: at K = 3, M = 21 the direct form still keeps 232 bytes a
+// lane in scratch memory.
 constexpr int n_rows_op(int G) { return 3 * (G / 2) + 2 * (G & 1); }
 constexpr int est_regs(int G, int K, int mode, bool lds, int ahead) {
   return 12 * K * ((G + 1) / 2) + 16 * (lds ? 1 : K) + 4 * n_rows_op(G) * ahead + 4 * K + 60 +

@@ -27,8 +27,8 @@
 // and none is started in vain.  The samples of a tile share their
 // delay bin, so the blocks that one of them needs start at the same rows for
 // all, and they mostly need the same ones: the workgroup walks the union of
-// their blocks (2.8 for the 12 of 10.5 samples, at the size below),
-// the contraction and G_k = Q_k^T c_k on the FP64 matrix cores as in the FP64
+// their blocks (a sample takes part in its own only, so that its result does
+// not depend on its neighbours), the contraction and G_k = Q_k^T c_k on the FP64 matrix cores as in the FP64
 // path (k_eval64.hip), with Q from the FP32 matrix-core layout (FP32 values,
 // exact in FP64); ell_j is summed over the detectors through LDS.  U and V
 // enter as one real matrix per detector,
